@@ -184,3 +184,85 @@ def tolerance(case):
     if case["dtype"] == "bf16":
         return {"rel": 6e-3, "max": 0.03}
     return {"rel": 4e-6, "max": 2e-4}
+
+
+def _scan64(a, u):
+    """f_t = a_t f_{t-1} + u_t from f_{-1} = 0 along the last axis, by doubling; also the products of a."""
+    s, L = 1, a.shape[-1]
+    while s < L:
+        u = torch.cat([u[..., :s], u[..., s:] + a[..., s:] * u[..., :-s]], -1)
+        a = torch.cat([a[..., :s], a[..., s:] * a[..., :-s]], -1)
+        s *= 2
+    return u, a
+
+
+def _lbscan64(window, x, delta, A, Bm, Cm, Dskip, z, delta_bias, h0=None):
+    """The definition (include/lbscan.h) in the scanned order, 64 bits: the output and the leaving state."""
+    L = x.shape[-1]
+    dt = torch.nn.functional.softplus(delta + delta_bias[:, None])
+    a = torch.exp(dt[:, :, None] * A[:, :, None])                        # (B, D, N, L)
+    u = dt[:, :, None] * Bm[:, None] * x[:, :, None]
+    f, prod = _scan64(a, u)
+    if h0 is not None:
+        f = f + prod * h0[..., None]
+    pad = -L % window
+    aw, uw = (torch.nn.functional.pad(v, (0, pad)).unflatten(-1, (-1, window)) for v in (a, u))
+    g = [torch.zeros_like(uw[..., 0])]
+    for t in range(window - 2, -1, -1):
+        g.append(aw[..., t] * (g[-1] + uw[..., t + 1]))
+    g = torch.stack(g[::-1], -1).flatten(-2)[..., :L]
+    y = (Cm[:, None] * (f + g)).sum(2) + Dskip[:, None] * x
+    return y * torch.nn.functional.silu(z), f[..., -1]
+
+
+def exact(case, seed):
+    t = {k: v.double() for k, v in _tensors(case, seed).items()}
+    op, L = case["op"], case["seqlen"]
+    if op == "conv_train":
+        flip = (lambda v: v.flip(-1)) if case["reverse"] else (lambda v: v)
+        x, weight, bias = (t[k].requires_grad_(True) for k in ("x", "weight", "bias"))
+        pre = torch.nn.functional.pad(flip(x), (3, 0))
+        pre = sum(weight[:, k, None] * pre[..., k:k + L] for k in range(4)) + bias[:, None]
+        out = flip(torch.nn.functional.silu(pre))
+        return out.detach(), torch.autograd.grad(out, [x, weight, bias], t["dout"])
+    order = torch.arange(L, device="cuda")
+    if op.startswith("columns"):
+        h, w, first = case["grid_h"], case["grid_w"], case["grid_prefix"]
+        order[first:first + h * w] = order[first:first + h * w].reshape(h, w).t().flatten()
+    if case["reverse"]:
+        order = order.flip(0)
+    back = order.argsort()
+    along = [k for k in ("x", "delta", "Bm", "Cm", "z", "dout") if k in t]
+    for k in along:
+        t[k] = t[k][..., order]
+    # slices of the batch and the channels, small enough for the doubling's steps
+    B, D, N = case["batch"], case["dim"], case["dstate"]
+    most = 32 << 20
+    nb = max(1, min(B, most // (D * N * L)))
+    nd = max(1, min(D, most // (nb * N * L)))
+    dout = t.pop("dout", None)
+    out = torch.empty_like(t["x"])
+    state = torch.empty(B, D, N, device="cuda", dtype=torch.float64)
+    grads = {k: torch.zeros_like(v) for k, v in t.items()}
+    for b in range(0, B, nb):
+        for d in range(0, D, nd):
+            bs, ds = slice(b, b + nb), slice(d, d + nd)
+            where = {k: (bs, ds) if k in ("x", "delta", "z", "h0") else (bs,) if k in ("Bm", "Cm") else (ds,) for k in t}
+            part = {k: v[where[k]].clone().requires_grad_(dout is not None) for k, v in t.items()}
+            y, left = _lbscan64(case["window"], **part)
+            out[bs, ds], state[bs, ds] = y.detach(), left.detach()
+            if dout is not None:
+                for k, v in zip(part, torch.autograd.grad(y, list(part.values()), dout[bs, ds])):
+                    grads[k][where[k]] += v
+            del y, left
+    out = out[..., back]
+    for k in along:
+        if k in grads:
+            grads[k] = grads[k][..., back]
+    if op in ("fwd", "columns"):
+        return out
+    if op == "stream":
+        return out, state
+    if op == "train":
+        return out, tuple(grads.values())
+    return out, {"d" + k: grads[k] for k in ("x", "delta", "z", "Bm", "Cm", "A", "Dskip", "delta_bias")}
