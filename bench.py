@@ -378,7 +378,7 @@ def main():
             torch.cuda.empty_cache()
 
         # the vertical scan of the Vim-small token grid (14 x 14 patches, class token last):
-        # the same kernels gathering token by token (paper Sec. 4.5 / Appendix D)
+        # the same kernels on copies in scanned order (paper Sec. 4.5 / Appendix D)
         wl = WORKLOADS["vim_small"]
         ss = [device_inputs(wl, BASE_SEED + 900 + i) for i in range(nsets_for(wl))]
         r = measure_workload(lb, lib, "vim_small_columns", wl, ss, max(a.steps // 2, 1), max(a.warmup // 2, 1),

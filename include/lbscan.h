@@ -107,8 +107,10 @@ typedef struct lbscan_args {
        row and are scanned column by column, top to bottom; tokens before and after the
        grid (class tokens) are scanned in place, before and after it.  The operator is
        applied to the sequence in that order and every (B,D,L) / (B,N,L) tensor, inputs
-       and outputs alike, stays in stored order: no reordered copy exists.  reverse = 1
-       reverses the scanned sequence.  Kernels then gather token by token.  lbscan_fwd
+       and outputs alike, stays in stored order.  reverse = 1
+       reverses the scanned sequence.  Kernels then gather token by token; a call whose
+       workspace holds LBSCAN_WS_FWD_ORDER / LBSCAN_WS_BWD_ORDER bytes (up to 4096 tokens)
+       works on reordered copies in it instead, which is faster.  lbscan_fwd
        with a window length outside {1,2,4,8,16} and lbscan_bidir_fwd support only the
        stored order (LBSCAN_EUNSUPPORTED otherwise); lbscan_bwd supports every window. */
     int32_t scan_order;
@@ -122,6 +124,11 @@ typedef struct lbscan_args {
 #define LBSCAN_WS_BWD   1
 #define LBSCAN_WS_BIDIR 2
 #define LBSCAN_WS_SAVED 3   /* size of lbscan_args.saved_state (0: these shapes do not use it) */
+/* Optional larger workspace of lbscan_fwd / lbscan_bwd for a scan order other than the
+   stored one (0: no such path for these sizes).  Includes LBSCAN_WS_FWD / LBSCAN_WS_BWD;
+   for the backward size, args->z says whether there is a gate. */
+#define LBSCAN_WS_FWD_ORDER 4
+#define LBSCAN_WS_BWD_ORDER 5
 
 /* Forward pass of the locally bi-directional scan (Sec. 3.2, Eq. 7-8, on top of
  * the global forward scan of Eq. 1-3; gate and skip of Algorithm 1 fused in). */

@@ -14,7 +14,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "liblbscan.so")
 
 LBSCAN_FP32, LBSCAN_BF16 = 0, 1
-WS_FWD, WS_BWD, WS_BIDIR, WS_SAVED = 0, 1, 2, 3
+WS_FWD, WS_BWD, WS_BIDIR, WS_SAVED, WS_FWD_ORDER, WS_BWD_ORDER = 0, 1, 2, 3, 4, 5
 OK, EINVAL, EUNSUPPORTED, EWORKSPACE, EHIP = 0, -1, -2, -3, -4
 
 EXPORTS = (
@@ -200,9 +200,19 @@ def _workspace_for(args, which, like, stream=None):
     stream as well, so that it is not handed out again while the kernels use it."""
     import torch
     need = lbscan_workspace_bytes(args, which)
-    if need == 0:
-        return None
-    ws = torch.empty((need + 3) // 4, dtype=torch.float32, device=like.device)
+    ws = None
+    if args.scan_order:
+        # the larger scratch of the reordered copies, when the device has it
+        more = lbscan_workspace_bytes(args, {WS_FWD: WS_FWD_ORDER, WS_BWD: WS_BWD_ORDER}[which])
+        if more > need:
+            try:
+                ws = torch.empty((more + 3) // 4, dtype=torch.float32, device=like.device)
+            except torch.cuda.OutOfMemoryError:
+                pass
+    if ws is None:
+        if need == 0:
+            return None
+        ws = torch.empty((need + 3) // 4, dtype=torch.float32, device=like.device)
     _tie_to_stream(stream, ws)
     args.workspace = ws.data_ptr()
     args.workspace_bytes = ws.numel() * 4

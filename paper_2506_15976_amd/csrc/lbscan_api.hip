@@ -226,7 +226,12 @@ int fwd_with_scratch(const lbscan_args* args, void* scratch, size_t scratch_byte
         if (sneed && (args->saved_state_bytes < sneed || !aligned4(args->saved_state))) return LBSCAN_EWORKSPACE;
         if (sneed) saved = static_cast<float*>(args->saved_state);
     }
-    hipError_t e = lbscan::launch_fwd(p, scratch, saved, static_cast<hipStream_t>(hip_stream));
+    // a scan order: through reordered copies where the scratch holds them
+    const size_t copies = lbscan::fwd_reordered_workspace_bytes(p);
+    const bool reorder = copies && scratch && scratch_bytes >= copies && aligned4(scratch);
+    hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    hipError_t e = reorder ? lbscan::launch_fwd_reordered(p, scratch, saved, s)
+                           : lbscan::launch_fwd(p, scratch, saved, s);
     return e == hipSuccess ? LBSCAN_OK : hip_fail(e, "lbscan_fwd");
 }
 
@@ -337,7 +342,10 @@ int lbscan_bwd_state(const lbscan_args* a, const void* dout, const float* dhT,
         if (sneed && (a->saved_state_bytes < sneed || !aligned4(a->saved_state))) return LBSCAN_EWORKSPACE;
         if (sneed) saved = static_cast<const float*>(a->saved_state);
     }
-    hipError_t e = lbscan::launch_bwd(f, p, dBm, dCm, a->workspace, saved, dhT, s);
+    const size_t copies = lbscan::bwd_reordered_workspace_bytes(f);
+    const bool reorder = copies && a->workspace && a->workspace_bytes >= copies && aligned4(a->workspace);
+    hipError_t e = reorder ? lbscan::launch_bwd_reordered(f, p, dBm, dCm, a->workspace, saved, dhT, s)
+                           : lbscan::launch_bwd(f, p, dBm, dCm, a->workspace, saved, dhT, s);
     return e == hipSuccess ? LBSCAN_OK : hip_fail(e, "lbscan_bwd");
 }
 
@@ -376,7 +384,9 @@ size_t lbscan_workspace_bytes(const lbscan_args* a, int which)
         // two launches each way: the plain scan with window 1 and the local backward part
         if (which == LBSCAN_WS_FWD)
             return lbscan::fwd_generic_workspace_bytes(to_params(a, a->window < a->seqlen ? a->window : a->seqlen));
-        if (which == LBSCAN_WS_SAVED) return 0;
+        if (which == LBSCAN_WS_SAVED || which == LBSCAN_WS_FWD_ORDER) return 0;
+        if (which == LBSCAN_WS_BWD_ORDER)
+            return lbscan::bwd_reordered_workspace_bytes(to_params(a, a->window < a->seqlen ? a->window : a->seqlen));
         if (which == LBSCAN_WS_BWD)
             return lbscan::bwd_workspace_bytes(to_params(a, a->window < a->seqlen ? a->window : a->seqlen));
         M = 1;
@@ -388,6 +398,10 @@ size_t lbscan_workspace_bytes(const lbscan_args* a, int which)
             return lbscan::bwd_workspace_bytes(to_params(a, M));
         case LBSCAN_WS_SAVED:
             return lbscan::saved_state_bytes(to_params(a, M));
+        case LBSCAN_WS_FWD_ORDER:
+            return lbscan::fwd_reordered_workspace_bytes(to_params(a, M));
+        case LBSCAN_WS_BWD_ORDER:
+            return lbscan::bwd_reordered_workspace_bytes(to_params(a, M));
         case LBSCAN_WS_BIDIR:
             return (a->dtype == LBSCAN_FP32 ? 0 : bdl * sizeof(float)) +
                    lbscan::fwd_workspace_bytes(to_params(a, 1));

@@ -324,4 +324,165 @@ hipError_t launch_bwd(const FwdParams& f, BwdParams p, void* dBm, void* dCm, voi
     return e != hipSuccess ? e : finish();
 }
 
+// ---- a scan order through reordered copies --------------------------------------
+//
+// The row-per-lane kernels can gather the tokens of a scan order themselves, which
+// needs no scratch; given scratch, the row tensors are copied into scanned order
+// first, the stored-order path runs on the copies, and its results are copied back.
+// The forward pass leaves z where it is: the scan returns the ungated sum in fp32 and
+// the copy back applies the gate.
+//
+// Measured on MI355X (us, gather / copies; fp32 unless said):
+//   rows x tokens (grid)            forward       backward call
+//   128 x 768, 197 (14 x 14)        362 / 226     1570 / 750
+//   64 x 384, 197                   106 / 71      428 / 243      bf16: 72 / 70, 294 / 236
+//   4 x 768, 1025 (32 x 32)         141 / 77      359 / 209      bf16: 112 / 78, 273 / 212
+//   768, 4096 (64 x 64)             122 / 93      320 / 215      bf16: 118 / 92, 290 / 218
+//   32 x 192, 249 (8 x 31)          40 / 46       160 / 157      bf16: 39 / 47, 154 / 158
+//   16 x 384, 197                   42 / 44       139 / 124
+//   4 x 192, 197                    33 / 30       83 / 79
+//   64, 50 (7 x 7)                  17 / 22       56 / 51
+// The forward call pays for two more launches, so it copies from 2^21 elements on (the
+// line lies between 1.5 and 3.1 million); the backward call always.
+namespace {
+
+constexpr long kReorderFwdElements = 1L << 21;
+
+constexpr size_t kCopyAlign = 256;
+size_t aligned_bytes(size_t n) { return (n + kCopyAlign - 1) / kCopyAlign * kCopyAlign; }
+
+bool reorder_applies(const FwdParams& p)
+{
+    return p.order.kind != 0 && p.seqlen <= kReorderMaxTokens && p.batch > 0 && p.dim > 0 && p.seqlen > 0;
+}
+
+// stored index -> scanned index: the same map with the grid's sides exchanged
+TokenOrder inverse_order(const TokenOrder& o)
+{
+    TokenOrder r = o;
+    r.H = o.W;
+    r.W = o.H;
+    r.rH = 1.0f / (float)r.H;
+    return r;
+}
+
+TokenOrder stored_order()
+{
+    TokenOrder r{};
+    r.H = r.W = r.HW = 1;
+    r.rH = 1.0f;
+    return r;
+}
+
+struct CopySizes {
+    size_t row, mat;      // bytes of a (B,D,L) and of a (B,N,L) tensor in the storage type, rounded up
+    size_t row32;         // of a (B,D,L) tensor in fp32
+};
+CopySizes copy_sizes(const FwdParams& p)
+{
+    const size_t e = p.dtype == 0 ? 4 : 2;
+    const size_t bdl = (size_t)p.batch * p.dim * p.seqlen, bnl = (size_t)p.batch * p.dstate * p.seqlen;
+    return {aligned_bytes(bdl * e), aligned_bytes(bnl * e), aligned_bytes(bdl * 4)};
+}
+
+FwdParams in_stored_order(FwdParams p)
+{
+    p.order = stored_order();
+    return p;
+}
+
+// Copies of one tensor list, filled in the order of the calls.
+struct Copies {
+    ReorderMany m{};
+    int n = 0;
+    void add(const void* src, void* dst, long rows)
+    {
+        if (!src) return;
+        m.src[n] = src; m.dst[n] = dst; m.rows[n] = rows;
+        ++n;
+    }
+};
+
+}  // namespace
+
+size_t fwd_reordered_workspace_bytes(const FwdParams& p)
+{
+    if (!reorder_applies(p) || (long)p.batch * p.dim * p.seqlen < kReorderFwdElements) return 0;
+    const CopySizes c = copy_sizes(p);
+    return aligned_bytes(fwd_workspace_bytes(in_stored_order(p))) + 2 * c.row + 2 * c.mat + c.row32;
+}
+
+hipError_t launch_fwd_reordered(FwdParams p, void* workspace, float* saved, hipStream_t stream)
+{
+    const CopySizes c = copy_sizes(p);
+    FwdParams q = in_stored_order(p);
+    const long rows = (long)p.batch * p.dim, mats = (long)p.batch * p.dstate;
+    char* at = static_cast<char*>(workspace) + aligned_bytes(fwd_workspace_bytes(q));
+    auto take = [&](size_t n) { char* r = at; at += n; return r; };
+    Copies in;
+    q.x = take(c.row);     in.add(p.x, const_cast<void*>(q.x), rows);
+    q.delta = take(c.row); in.add(p.delta, const_cast<void*>(q.delta), rows);
+    q.Bm = take(c.mat);    in.add(p.Bm, const_cast<void*>(q.Bm), mats);
+    q.Cm = take(c.mat);    in.add(p.Cm, const_cast<void*>(q.Cm), mats);
+    hipError_t e = launch_reorder(in.m, p.dtype, p.seqlen, p.order, stream);
+    if (e != hipSuccess) return e;
+    q.z = nullptr;
+    q.y = take(c.row32);
+    q.y_is_f32 = 1;
+    e = launch_fwd(q, workspace, saved, stream);
+    if (e != hipSuccess) return e;
+    Copies out;
+    out.add(q.y, p.y, rows);
+    out.m.gate = p.z;
+    return launch_reorder_gate(out.m, p.dtype, p.seqlen, inverse_order(p.order), stream);
+}
+
+size_t bwd_reordered_workspace_bytes(const FwdParams& f)
+{
+    if (!reorder_applies(f)) return 0;
+    const CopySizes c = copy_sizes(f);
+    return aligned_bytes(bwd_workspace_bytes(in_stored_order(f))) + (5 + (f.z ? 2 : 0)) * c.row + 4 * c.mat;
+}
+
+hipError_t launch_bwd_reordered(FwdParams f, BwdParams p, void* dBm, void* dCm, void* workspace,
+                                const float* saved, const float* dhT, hipStream_t stream)
+{
+    const CopySizes c = copy_sizes(f);
+    FwdParams q = in_stored_order(f);
+    BwdParams r = p;
+    r.order = q.order;
+    const long rows = (long)f.batch * f.dim, mats = (long)f.batch * f.dstate;
+    char* at = static_cast<char*>(workspace) + aligned_bytes(bwd_workspace_bytes(q));
+    auto take = [&](size_t n) { char* t = at; at += n; return t; };
+    Copies in, out;
+    auto copy_in = [&](const void* src, size_t bytes, long n) -> const void* {
+        if (!src) return nullptr;
+        void* d = take(bytes);
+        in.add(src, d, n);
+        return d;
+    };
+    auto copy_out = [&](void* dst, size_t bytes, long n) -> void* {
+        if (!dst) return nullptr;
+        void* t = take(bytes);
+        out.add(t, dst, n);
+        return t;
+    };
+    q.x = r.x = copy_in(f.x, c.row, rows);
+    q.delta = r.delta = copy_in(f.delta, c.row, rows);
+    q.z = r.z = copy_in(f.z, c.row, rows);
+    r.dout = copy_in(p.dout, c.row, rows);
+    q.Bm = r.Bm = copy_in(f.Bm, c.mat, mats);
+    q.Cm = r.Cm = copy_in(f.Cm, c.mat, mats);
+    r.dx = copy_out(p.dx, c.row, rows);
+    r.ddelta = copy_out(p.ddelta, c.row, rows);
+    r.dz = copy_out(p.dz, c.row, rows);
+    void* dB = copy_out(dBm, c.mat, mats);
+    void* dC = copy_out(dCm, c.mat, mats);
+    hipError_t e = launch_reorder(in.m, f.dtype, f.seqlen, f.order, stream);
+    if (e != hipSuccess) return e;
+    e = launch_bwd(q, r, dB, dC, workspace, saved, dhT, stream);
+    if (e != hipSuccess) return e;
+    return launch_reorder(out.m, f.dtype, f.seqlen, inverse_order(f.order), stream);
+}
+
 }  // namespace lbscan

@@ -176,6 +176,30 @@ hipError_t launch_bwd(const FwdParams& f, BwdParams p, void* dBm, void* dCm, voi
                       const float* saved, const float* dhT, hipStream_t stream);
 size_t bwd_workspace_bytes(const FwdParams& f);
 
+// Passes over reordered copies instead of gathers, for a scan order other than the
+// stored one: bytes of scratch they take (0: they do not apply to p), and the launches.
+size_t fwd_reordered_workspace_bytes(const FwdParams& p);
+size_t bwd_reordered_workspace_bytes(const FwdParams& f);
+hipError_t launch_fwd_reordered(FwdParams p, void* workspace, float* saved, hipStream_t stream);
+hipError_t launch_bwd_reordered(FwdParams f, BwdParams p, void* dBm, void* dCm, void* workspace,
+                                const float* saved, const float* dhT, hipStream_t stream);
+
+// Reordering of up to kReorderMany (rows, L) tensors in one launch (lbscan_order.hip):
+// dst[i][row, t] = src[i][row, map(t)] for every entry whose src is set, L at most
+// kReorderMaxTokens.  Sources and destinations do not overlap.
+constexpr int kReorderMany = 6;
+constexpr int kReorderMaxTokens = 4096;
+struct ReorderMany {
+    const void* src[kReorderMany];
+    void* dst[kReorderMany];
+    long rows[kReorderMany];
+    const void* gate;             // launch_reorder_gate: z of entry 0 (rows as dst[0]), nullable
+    long blocks[kReorderMany];    // set by the launcher
+};
+hipError_t launch_reorder(const ReorderMany& m, int dtype, int L, const TokenOrder& map, hipStream_t stream);
+// The same from fp32 to the storage type, times SiLU(gate) where there is one.
+hipError_t launch_reorder_gate(const ReorderMany& m, int dtype, int L, const TokenOrder& map, hipStream_t stream);
+
 // Depthwise causal convolution + SiLU along the sequence and its gradient.
 hipError_t launch_conv1d_fwd(const ConvParams& p, hipStream_t stream);
 hipError_t launch_conv1d_bwd(const ConvParams& p, hipStream_t stream);

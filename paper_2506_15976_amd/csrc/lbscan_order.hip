@@ -1,0 +1,139 @@
+// Reordering of row tensors between the stored token order and the scanned one
+// (TokenOrder): every row of up to kReorderMany (rows, L) tensors is permuted the same
+// way in one launch.
+//
+// Why copies: the row-per-lane kernels can gather token by token, but a wave's 64 lanes
+// then touch 64 sectors with every 4-byte load and the same lines are fetched again by
+// every tile of the row.  Copying first moves each tensor once more, in whole lines.
+// (The two ways are compared beside launch_fwd_reordered in lbscan_dispatch.hip.)
+//
+// What bounds it: HBM traffic, one read and one write; 5.5 TB/s measured (four row
+// tensors of 128 x 768 x 197 fp32 and Bm, Cm: 115 us).  A block takes an even number of
+// whole consecutive rows, which are one contiguous piece of memory: all its loads (up
+// to 32 elements a thread in quads) are in flight together, go to LDS as fp32, and are
+// written out token by token, 64 neighbouring tokens of a row per wave.  A lane keeps
+// its tokens' places in the LDS row in registers and walks the block's rows, so the
+// index arithmetic is paid once per block and not once per element.
+#include "lbscan_device.h"
+#include "lbscan_internal.h"
+
+namespace lbscan {
+namespace {
+
+constexpr int kReThreads = 256;
+constexpr int kReFloats = 32 * kReThreads;            // elements of a block's rows
+constexpr int kReQuads = kReFloats / 4 / kReThreads;  // quads per thread
+constexpr int kReCols = 4;                            // tokens a lane holds at a time (256 of a row per wave)
+
+// one float of padding every 32: a column of a grid whose width is a multiple of 16
+// would otherwise sit in two banks
+__device__ __forceinline__ int pad_slot(int i) { return i + (i >> 5); }
+
+// dst[row, t] = src[row, map(t)]; with GATE also times SiLU(gate[row, t])
+template <typename TS, typename TD, bool GATE>
+__global__ void __launch_bounds__(kReThreads)
+reorder_kernel(const ReorderMany m, const int L, const int rows_per_block, const TokenOrder map)
+{
+    __shared__ float buf[kReFloats + kReFloats / 32];
+    int which = 0;
+    long block = blockIdx.x;
+#pragma unroll
+    for (int i = 0; i + 1 < kReorderMany; ++i)
+        if (which == i && block >= m.blocks[i]) { block -= m.blocks[i]; which = i + 1; }
+    const long row0 = block * rows_per_block;
+    const long left = m.rows[which] - row0;
+    const int nrows = left < rows_per_block ? (int)left : rows_per_block;
+    const int n = nrows * L;                                  // <= kReFloats
+    const TS* __restrict__ src = static_cast<const TS*>(m.src[which]) + row0 * L;
+    TD* __restrict__ dst = static_cast<TD*>(m.dst[which]) + row0 * L;
+    const TD* __restrict__ gate = GATE ? static_cast<const TD*>(m.gate) + row0 * L : nullptr;
+
+    // the block's first element is an even one (even rows per block), so quads are
+    // 4-byte aligned for 2-byte types too; a last quad that is not whole is loaded
+    // element by element
+    Quad<TS> q[kReQuads];
+#pragma unroll
+    for (int i = 0; i < kReQuads; ++i) {
+        const int k = ((int)threadIdx.x + i * kReThreads) * 4;
+        if (k + 4 <= n) q[i] = quad_raw_fast<TS>(src, k);
+    }
+#pragma unroll
+    for (int i = 0; i < kReQuads; ++i) {
+        const int k = ((int)threadIdx.x + i * kReThreads) * 4;
+        if (k + 4 <= n) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) buf[pad_slot(k + e)] = to_f32(q[i].v[e]);
+        } else {
+            for (int e = k; e < n; ++e) buf[pad_slot(e)] = to_f32(src[e]);
+        }
+    }
+    __syncthreads();
+
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int t0 = 0; t0 < L; t0 += 64 * kReCols) {
+        int from[kReCols];
+#pragma unroll
+        for (int j = 0; j < kReCols; ++j) {
+            const int t = t0 + 64 * j + lane;
+            from[j] = map(t < L ? t : L - 1);
+        }
+        for (int r = wave; r < nrows; r += kReThreads / 64) {
+            float g[kReCols];
+            if (GATE) {
+#pragma unroll
+                for (int j = 0; j < kReCols; ++j) {
+                    const int t = t0 + 64 * j + lane;
+                    g[j] = to_f32(gate[r * L + (t < L ? t : L - 1)]);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < kReCols; ++j) {
+                const int t = t0 + 64 * j + lane;
+                float v = buf[pad_slot(r * L + from[j])];
+                if (GATE) v *= g[j] * sigmoid_f32(g[j]);
+                if (t < L) dst[r * L + t] = from_f32<TD>(v);
+            }
+        }
+    }
+}
+
+template <typename TS, typename TD, bool GATE>
+hipError_t launch_reorder_t(ReorderMany m, int L, const TokenOrder& map, hipStream_t s)
+{
+    // few rows: fewer of them to a block, down to two, so that about four blocks a CU start
+    long rows = 0, total = 0;
+    for (int i = 0; i < kReorderMany; ++i) rows += m.src[i] ? m.rows[i] : 0;
+    long rpb_want = (rows / 1024) & ~1L;
+    const int rpb_most = (kReFloats / L) & ~1;                // >= 2 for L <= kReorderMaxTokens
+    const int rpb = rpb_want < 2 ? 2 : (rpb_want < rpb_most ? (int)rpb_want : rpb_most);
+    for (int i = 0; i < kReorderMany; ++i) {
+        m.blocks[i] = m.src[i] ? (m.rows[i] + rpb - 1) / rpb : 0;
+        total += m.blocks[i];
+    }
+    if (total == 0) return hipSuccess;
+    if (total > 0x7fffffffL) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((reorder_kernel<TS, TD, GATE>), dim3((unsigned)total), dim3(kReThreads), 0, s,
+                       m, L, rpb, map);
+    return hipGetLastError();
+}
+
+static_assert(2 * kReorderMaxTokens <= kReFloats, "two rows fit a block's LDS");
+
+}  // namespace
+
+hipError_t launch_reorder(const ReorderMany& m, int dtype, int L, const TokenOrder& map, hipStream_t stream)
+{
+    return dtype == 0 ? launch_reorder_t<float, float, false>(m, L, map, stream)
+                      : launch_reorder_t<bf16_t, bf16_t, false>(m, L, map, stream);
+}
+
+hipError_t launch_reorder_gate(const ReorderMany& m, int dtype, int L, const TokenOrder& map, hipStream_t stream)
+{
+    if (dtype == 0)
+        return m.gate ? launch_reorder_t<float, float, true>(m, L, map, stream)
+                      : launch_reorder_t<float, float, false>(m, L, map, stream);
+    return m.gate ? launch_reorder_t<float, bf16_t, true>(m, L, map, stream)
+                  : launch_reorder_t<float, bf16_t, false>(m, L, map, stream);
+}
+
+}  // namespace lbscan

@@ -90,3 +90,53 @@ def test_full_size_vim_small_column_order(lb, oracle):
     w = WORKLOADS["vim_small"]
     s = make_workload("vim_small")
     _check(lb, oracle, s, (14, 14, 0), window=w["window"], bwd=False)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("B, D, N, L, grid, window, gate", [
+    (3, 5, 16, 6, (2, 3), 4, True),             # 15 rows: an odd number, and more rows than one block's waves
+    (2, 33, 8, 77, (7, 10, 3), 2, False),       # tokens before and after the grid, no gate
+    (1, 70, 16, 257, (16, 16, 1), 8, True),     # one token past a wave's 256
+    (1, 3, 16, 1025, (32, 32), 16, True),       # columns of a width that the LDS banks divide
+    (2, 1, 4, 4096, (64, 64), 4, True),         # the longest row that is copied, odd rows
+    (1, 2, 16, 4097, (64, 64), 4, True),        # one token longer: gathered
+    # sizes from which the forward pass copies too
+    (9, 61, 16, 4096, (64, 64), 4, True),
+    (130, 83, 4, 197, (14, 14, 1), 8, True),    # an even number of rows to a block, an odd number left
+    (8, 257, 8, 1025, (32, 32), 16, False),
+])
+def test_reordered_copies_match_the_gather(lb, monkeypatch, B, D, N, L, grid, window, gate, dtype):
+    """With scratch for copies and without: the same operation, on the same kernels where
+    the rows are not handed to another family; fp32 sums in another order differ by a few
+    2^-24 of the sum, bf16 results by one rounding (2^-8)."""
+    import torch
+    from gpu_util import fwd_inputs, to_device
+    from paper_2506_15976_amd import binding
+    from paper_2506_15976_amd.inputs import make_inputs
+    s = make_inputs(B, D, N, L, seed=3400 + L, with_dout=True, random_A=True, dtype=dtype)
+    if not gate:
+        s["z"] = None
+    dev = to_device(s, dtype)
+    rel = 2e-5 if dtype == "fp32" else 2 ** -7
+
+    def both():
+        out = lb.lbscan_fwd(**fwd_inputs(dev), window=window, grid=grid, reverse=bool(L & 1))
+        g = lb.lbscan_bwd(**fwd_inputs(dev), dout=dev["dout"], window=window, grid=grid, reverse=bool(L & 1))
+        torch.cuda.synchronize()
+        return {"out": out, **g}
+
+    a = binding.make_args(**fwd_inputs(dev), window=window, grid=grid)
+    assert (binding.lbscan_workspace_bytes(a, binding.WS_BWD_ORDER) > 0) == (L <= 4096)
+    assert (binding.lbscan_workspace_bytes(a, binding.WS_FWD_ORDER) > 0) == (L <= 4096 and B * D * L >= 1 << 21)
+    copied = both()
+    size = binding.lbscan_workspace_bytes
+    monkeypatch.setattr(binding, "lbscan_workspace_bytes",
+                        lambda a, which: 0 if which in (binding.WS_FWD_ORDER, binding.WS_BWD_ORDER) else size(a, which))
+    gathered = both()
+    for k, v in gathered.items():
+        if v is None:
+            assert copied[k] is None
+            continue
+        r = v.float()
+        bound = rel * torch.maximum(r.abs(), r.square().mean().sqrt())
+        assert bool(((copied[k].float() - r).abs() <= bound).all()), k
