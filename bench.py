@@ -185,7 +185,7 @@ def measure_workload(lb, lib, name, w, sets, steps, warmup, with_bwd, per_launch
     ys = [torch.empty_like(s["x"]) for s in sets]
     mk = lambda s, **kw: lb.make_args(**{k: s[k] for k in FWD_KEYS}, grid=grid, **kw)
     fwd_args = [mk(s, window=w["window"], y=y) for s, y in zip(sets, ys)]
-    need = lb.lbscan_workspace_bytes(fwd_args[0], binding.WS_FWD)
+    need = max(lb.lbscan_workspace_bytes(fwd_args[0], w) for w in (binding.WS_FWD, binding.WS_FWD_ORDER))
     ws_fwd = torch.empty(max(need // 4, 1), dtype=torch.float32, device="cuda:0")
     for ar in fwd_args:
         ar.workspace, ar.workspace_bytes = ws_fwd.data_ptr(), need
@@ -233,7 +233,7 @@ def measure_workload(lb, lib, name, w, sets, steps, warmup, with_bwd, per_launch
             outs = [torch.empty_like(s_["x"]) for _ in range(3)] + [torch.empty_like(s_["Bm"]) for _ in range(2)] + \
                    [torch.empty_like(s_["A"]), torch.empty_like(s_["Dskip"]), torch.empty_like(s_["delta_bias"])]
             g_args.append((ar, s_["dout"], outs))
-        bneed = lb.lbscan_workspace_bytes(fwd_args[0], binding.WS_BWD)
+        bneed = max(lb.lbscan_workspace_bytes(fwd_args[0], w) for w in (binding.WS_BWD, binding.WS_BWD_ORDER))
         ws_bwd = torch.empty(max(bneed // 4, 1), dtype=torch.float32, device="cuda:0")
 
         def bwd_call(ar, dout, outs):

@@ -7,9 +7,9 @@
 // Both kernels are bound by HBM traffic, so the mapping serves the memory system:
 // a wave takes chunks of 64 consecutive quads (256 tokens) of one row, every lane
 // loads its quad once with one 16-byte load, and the K-1 neighbouring inputs an
-// output needs from the quad next to it come from the neighbouring lane through a
-// wave shuffle instead of a second load; only the lane at the end of the wave loads
-// its three halo elements itself.  A wave works on one channel and walks several
+// output needs from the quad next to it come from the neighbouring lane (a wave shift
+// in the lane crossbar) instead of a second load; the quad beyond the wave's edge is
+// one more load of a single sector.  A wave works on one channel and walks several
 // (batch entry, chunk) items of it, so that the filter is read once, waves live
 // long enough to keep loads in flight, and the backward kernel's sums over batch
 // and time are folded in registers before they reach an atomic.
@@ -22,77 +22,91 @@ namespace {
 constexpr int kConvWaves = 4;          // waves per block
 constexpr int kConvUnroll = 4;         // items whose loads a wave issues together
 
-// x[row, t] for t in [0, L), 0 outside
+// How the quads of a row may be loaded.  rows of four tokens and more: one load from a
+// position clamped into the row, whole for fp32 and for 2-byte rows of even length, the
+// 12 aligned bytes around it for 2-byte rows of odd length (which reach up to two
+// elements past the quad: not on the tensor's last row).  Otherwise element by element.
+enum ConvLoads { kLoadQuads, kLoadUnaligned, kLoadElements };
 template <typename T>
-__device__ __forceinline__ float load_or_zero(const T* __restrict__ row, int t, int L)
+__device__ __forceinline__ ConvLoads conv_loads(const ConvParams& p, int b, int d)
 {
-    const int tc = t < 0 ? 0 : (t >= L ? L - 1 : t);
-    const float v = to_f32(row[tc]);
-    return t == tc ? v : 0.0f;
+    if (p.seqlen < 4) return kLoadElements;
+    if (sizeof(T) == 4 || p.seqlen % 2 == 0) return kLoadQuads;
+    return b == p.batch - 1 && d == p.dim - 1 ? kLoadElements : kLoadUnaligned;
 }
 
-// A lane's quad is fetched in two steps so that a wave can have the loads of
-// several items in flight.  quad_issue is one unconditional 16-byte load from an
-// address clamped into the row (no load sits behind a divergent branch);
-// quad_finish turns it into the four values x[t0 .. t0+3], zero outside the row,
-// and only the lane holding a ragged last quad (and every lane when quads cannot
-// be loaded whole: rows shorter than 4, or 2-byte rows starting at odd elements)
-// goes back to memory element by element.
+// A lane's quad x[t0 .. t0+3], zero outside the row, is fetched in two steps so that a
+// wave can have the loads of several items in flight: quad_issue loads without a
+// lane-divergent branch, quad_finish moves the elements of a clamped quad into place
+// (t0 is a multiple of four, so a quad before the row holds none of its tokens).
+// Going back to memory for the ragged last quad and for the halo instead cost one
+// memory latency each per item, on every row whose length is not a multiple of 256.
 template <typename T>
-__device__ __forceinline__ Quad<T> quad_issue(const T* __restrict__ row, int t0, int L, bool vec_ok)
+__device__ __forceinline__ Quad<T> quad_issue(const T* __restrict__ row, int t0, int L, ConvLoads how)
 {
-    if (!vec_ok) return Quad<T>{};                               // uniform
     const int tc = t0 < 0 ? 0 : (t0 > L - 4 ? L - 4 : t0);
-    return quad_raw_fast<T>(row, tc);
+    if (how == kLoadQuads) return quad_raw_fast<T>(row, tc);            // (uniform branches)
+    if (how == kLoadUnaligned) return quad_raw_unaligned(row + tc);
+    return quad_raw_checked<T>(row, t0, t0, L);
 }
 
 template <typename T>
-__device__ __forceinline__ void quad_finish(const Quad<T>& raw, const T* __restrict__ row, int t0, int L,
-                                            bool vec_ok, float (&cur)[4])
+__device__ __forceinline__ void quad_finish(const Quad<T>& raw, int t0, int L, ConvLoads how, float (&cur)[4])
 {
-    const bool whole = vec_ok && t0 >= 0 && t0 + 4 <= L;
-    float slow[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (!whole && t0 >= 0 && t0 < L) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) slow[e] = load_or_zero<T>(row, t0 + e, L);
+    for (int e = 0; e < 4; ++e) cur[e] = to_f32(raw.v[e]);
+    if (how == kLoadElements) return;                                   // uniform; zeros are in place
+    // element e is loaded element e + s; s is 0 inside the row, 1..3 for its ragged last
+    // quad, anything else for a quad outside
+    const int s = t0 < 0 ? 4 : (t0 > L - 4 ? t0 - (L - 4) : 0);
+    const bool one = (s & 1) != 0, two = (s & 2) != 0, none = s >= 4;
+    float v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = one ? (e < 3 ? cur[e < 3 ? e + 1 : 3] : 0.0f) : cur[e];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float w = two ? (e < 2 ? v[e < 2 ? e + 2 : 3] : 0.0f) : v[e];
+        cur[e] = none ? 0.0f : w;
     }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) cur[e] = whole ? to_f32(raw.v[e]) : slow[e];
+}
+
+// The value of the lane before (wave_shr:1) or after (wave_shl:1) this one; the lane at
+// the wave's edge gets `edge`.
+__device__ __forceinline__ float from_lane_before(float v, float edge)
+{
+    return __uint_as_float(__builtin_amdgcn_update_dpp(__float_as_uint(edge), __float_as_uint(v), 0x138, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float from_lane_after(float v, float edge)
+{
+    return __uint_as_float(__builtin_amdgcn_update_dpp(__float_as_uint(edge), __float_as_uint(v), 0x130, 0xF, 0xF, false));
 }
 
 // The lane's own quad and the three inputs on the side the filter reaches to:
 // win[0..2] = x[t0-3 .. t0-1], win[3..6] = x[t0 .. t0+3] (forward direction), or
 // win[0..3] = x[t0 .. t0+3], win[4..6] = x[t0+4 .. t0+6] (reversed direction).
-// Lanes whose quad lies outside the row hold zeros.  Every lane of the wave calls it.
-template <typename T, bool REV>
-__device__ __forceinline__ void make_window(const float (&cur)[4], const T* __restrict__ row, int t0, int L,
-                                            int lane, float (&win)[7])
+// edge: the quad beyond the wave's first (last) one.  Every lane of the wave calls it.
+template <bool REV>
+__device__ __forceinline__ void make_window(const float (&cur)[4], const float (&edge)[4], float (&win)[7])
 {
-    const bool active = t0 >= 0 && t0 < L;
-    float halo[3];
     if (!REV) {
 #pragma unroll
-        for (int j = 0; j < 3; ++j) halo[j] = __shfl_up(cur[1 + j], 1, 64);
-        if (lane == 0) {
-#pragma unroll
-            for (int j = 0; j < 3; ++j) halo[j] = active ? load_or_zero<T>(row, t0 - 3 + j, L) : 0.0f;
-        }
-#pragma unroll
-        for (int j = 0; j < 3; ++j) win[j] = halo[j];
+        for (int j = 0; j < 3; ++j) win[j] = from_lane_before(cur[1 + j], edge[1 + j]);
 #pragma unroll
         for (int e = 0; e < 4; ++e) win[3 + e] = cur[e];
     } else {
 #pragma unroll
-        for (int j = 0; j < 3; ++j) halo[j] = __shfl_down(cur[j], 1, 64);
-        if (lane == 63) {
-#pragma unroll
-            for (int j = 0; j < 3; ++j) halo[j] = active ? load_or_zero<T>(row, t0 + 4 + j, L) : 0.0f;
-        }
-#pragma unroll
         for (int e = 0; e < 4; ++e) win[e] = cur[e];
 #pragma unroll
-        for (int j = 0; j < 3; ++j) win[4 + j] = halo[j];
+        for (int j = 0; j < 3; ++j) win[4 + j] = from_lane_after(cur[j], edge[j]);
     }
+}
+
+// Four outputs of a row: one store where the quad lies inside the row.
+template <typename T>
+__device__ __forceinline__ void conv_store(T* __restrict__ row, int t0, int L, ConvLoads how, const float (&v)[4])
+{
+    if (how == kLoadUnaligned && t0 + 4 <= L) { quad_store_unaligned(row + t0, v); return; }
+    quad_store<T>(row, t0, how == kLoadQuads && t0 + 4 <= L, t0, L, v);
 }
 
 // pre-activation of output e of the quad from the window above
@@ -121,7 +135,7 @@ __device__ __forceinline__ ConvWave conv_wave(const ConvParams& p, int chunks)
     const unsigned items = (unsigned)p.batch * (unsigned)chunks;
     const unsigned per = (unsigned)p.items_per_wave;
     const unsigned groups = (items + per - 1) / per;
-    const unsigned wid = blockIdx.x * kConvWaves + (threadIdx.x >> 6);
+    const unsigned wid = blockIdx.x * kConvWaves + (unsigned)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     ConvWave w;
     w.any = wid < (unsigned)p.dim * groups;
     w.d = (int)(wid % (unsigned)p.dim);
@@ -143,7 +157,6 @@ conv1d_fwd_kernel(const ConvParams p)
     const ConvWave cw = conv_wave(p, chunks);
     if (!cw.any) return;                                        // whole wave
     const int d = cw.d;
-    const bool vec_ok = L >= 4 && (sizeof(T) == 4 || L % 2 == 0);   // quads can be loaded whole
     const bool act = p.activation != 0;
     const T* __restrict__ xg = static_cast<const T*>(p.x);
     T* __restrict__ yg = static_cast<T*>(p.y);
@@ -156,13 +169,17 @@ conv1d_fwd_kernel(const ConvParams p)
     int b = cw.b, ch = cw.ch;
     for (int i = 0; i < cw.n; i += U) {
         long roff[U];
-        int t0[U];
-        Quad<T> raw[U];
+        int t0[U], th[U];                                       // th: the quad beyond the wave's edge
+        ConvLoads how[U];
+        Quad<T> raw[U], rawh[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             roff[u] = ((long)b * p.dim + d) * L;
             t0[u] = (ch * 64 + lane) * 4;
-            raw[u] = quad_issue<T>(xg + roff[u], t0[u], L, vec_ok);
+            th[u] = (ch * 64 + (REV ? 64 : -1)) * 4;
+            how[u] = conv_loads<T>(p, b, d);
+            raw[u] = quad_issue<T>(xg + roff[u], t0[u], L, how[u]);
+            rawh[u] = quad_issue<T>(xg + roff[u], th[u], L, how[u]);
             if (i + u + 1 < cw.n) {                             // uniform; else repeat the last item
                 if (++ch == chunks) { ch = 0; ++b; }
             }
@@ -170,9 +187,10 @@ conv1d_fwd_kernel(const ConvParams p)
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (i + u < cw.n) {                                 // uniform
-                float cur[4], win[7];
-                quad_finish<T>(raw[u], xg + roff[u], t0[u], L, vec_ok, cur);
-                make_window<T, REV>(cur, xg + roff[u], t0[u], L, lane, win);
+                float cur[4], edge[4], win[7];
+                quad_finish<T>(raw[u], t0[u], L, how[u], cur);
+                quad_finish<T>(rawh[u], th[u], L, how[u], edge);
+                make_window<REV>(cur, edge, win);
                 if (t0[u] < L) {
                     float out[4];
 #pragma unroll
@@ -180,7 +198,7 @@ conv1d_fwd_kernel(const ConvParams p)
                         const float pre = conv_at<K, REV>(win, w, bias, e);
                         out[e] = act ? pre * sigmoid_f32(pre) : pre;
                     }
-                    quad_store<T>(yg + roff[u], t0[u], vec_ok && t0[u] + 4 <= L, t0[u], L, out);
+                    conv_store<T>(yg + roff[u], t0[u], L, how[u], out);
                 }
             }
         }
@@ -205,7 +223,6 @@ conv1d_bwd_kernel(const ConvParams p)
     const ConvWave cw = conv_wave(p, chunks);
     if (!cw.any) return;                                        // whole wave
     const int d = cw.d;
-    const bool vec_ok = L >= 4 && (sizeof(T) == 4 || L % 2 == 0);   // quads can be loaded whole
     const bool act = p.activation != 0;
     const bool owner_lane = REV ? lane >= 1 : lane <= 62;
     const T* __restrict__ xg = static_cast<const T*>(p.x);
@@ -224,14 +241,18 @@ conv1d_bwd_kernel(const ConvParams p)
     int b = cw.b, ch = cw.ch;
     for (int i = 0; i < cw.n; i += U) {
         long roff[U];
-        int t0s[U];
-        Quad<T> rawx[U], rawg[U];
+        int t0s[U], th[U];                                      // th: the quad beyond the wave's edge
+        ConvLoads how[U];
+        Quad<T> rawx[U], rawh[U], rawg[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             roff[u] = ((long)b * p.dim + d) * L;
             t0s[u] = (ch * 63 - (REV ? 1 : 0) + lane) * 4;
-            rawx[u] = quad_issue<T>(xg + roff[u], t0s[u], L, vec_ok);
-            rawg[u] = quad_issue<T>(gg + roff[u], t0s[u], L, vec_ok);
+            th[u] = (ch * 63 + (REV ? 63 : -1)) * 4;
+            how[u] = conv_loads<T>(p, b, d);
+            rawx[u] = quad_issue<T>(xg + roff[u], t0s[u], L, how[u]);
+            rawh[u] = quad_issue<T>(xg + roff[u], th[u], L, how[u]);
+            rawg[u] = quad_issue<T>(gg + roff[u], t0s[u], L, how[u]);
             if (i + u + 1 < cw.n) {                             // uniform; else repeat the last item
                 if (++ch == chunks) { ch = 0; ++b; }
             }
@@ -241,10 +262,11 @@ conv1d_bwd_kernel(const ConvParams p)
             if (i + u < cw.n) {                                 // uniform
                 const int t0 = t0s[u];
                 const bool own = owner_lane && t0 >= 0 && t0 < L;
-                float cur[4], win[7], dy[4];
-                quad_finish<T>(rawx[u], xg + roff[u], t0, L, vec_ok, cur);
-                make_window<T, REV>(cur, xg + roff[u], t0, L, lane, win);
-                quad_finish<T>(rawg[u], gg + roff[u], t0, L, vec_ok, dy);
+                float cur[4], edge[4], win[7], dy[4];
+                quad_finish<T>(rawx[u], t0, L, how[u], cur);
+                quad_finish<T>(rawh[u], th[u], L, how[u], edge);
+                make_window<REV>(cur, edge, win);
+                quad_finish<T>(rawg[u], t0, L, how[u], dy);
 
                 // dpre of the own quad (zero past the end of the row: dy is zero there)
                 float dpre[4];
@@ -264,10 +286,10 @@ conv1d_bwd_kernel(const ConvParams p)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) dwin[e] = dpre[e];
 #pragma unroll
-                    for (int j = 0; j < 3; ++j) dwin[4 + j] = __shfl_down(dpre[j], 1, 64);
+                    for (int j = 0; j < 3; ++j) dwin[4 + j] = from_lane_after(dpre[j], 0.0f);
                 } else {
 #pragma unroll
-                    for (int j = 0; j < 3; ++j) dwin[j] = __shfl_up(dpre[1 + j], 1, 64);
+                    for (int j = 0; j < 3; ++j) dwin[j] = from_lane_before(dpre[1 + j], 0.0f);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) dwin[3 + e] = dpre[e];
                 }
@@ -287,7 +309,7 @@ conv1d_bwd_kernel(const ConvParams p)
                             acc[k] = fmaf(dpre[e], REV ? win[e + (K - 1) - k] : win[3 + e - (K - 1) + k], acc[k]);
                         acc[K] += dpre[e];
                     }
-                    quad_store<T>(dxg + roff[u], t0, vec_ok && t0 + 4 <= L, t0, L, dx);
+                    conv_store<T>(dxg + roff[u], t0, L, how[u], dx);
                 }
             }
         }
@@ -353,8 +375,8 @@ hipError_t launch_conv1d_fwd(const ConvParams& p, hipStream_t stream)
 
 hipError_t launch_conv1d_bwd(const ConvParams& p, hipStream_t stream)
 {
-    hipError_t e = launch_zero(p.dweight, (long)p.dim * p.width, stream);
-    if (e == hipSuccess) e = launch_zero(p.dbias, p.dim, stream);
+    const ZeroMany zero{{p.dweight, p.dbias, nullptr, nullptr, nullptr}, {(long)p.dim * p.width, p.dim, 0, 0, 0}};
+    hipError_t e = launch_zero_many(zero, stream);
     if (e != hipSuccess || (long)p.batch * p.dim * p.seqlen == 0) return e;
     return p.dtype == 0 ? launch_conv_t<float>(p, true, stream) : launch_conv_t<bf16_t>(p, true, stream);
 }

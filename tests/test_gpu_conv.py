@@ -82,6 +82,15 @@ def test_bf16_storage(lb, oracle, L):
     _check(lb, oracle, _inputs(2, 8, L, 4, 6401 + L, dtype="bf16"), dtype="bf16", reverse=True)
 
 
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("B, D, L", [(1, 1, 253), (1, 2, 255), (2, 1, 257), (2, 3, 505), (1, 3, 3), (3, 1, 4)])
+def test_halo_and_last_row_edges(lb, oracle, B, D, L, dtype):
+    """Chunks of 252 and 256 tokens meet here with one to three tokens left; the last row of
+    a 2-byte tensor of odd rows may not be read past its end; rows of fewer than four."""
+    for reverse in (False, True):
+        _check(lb, oracle, _inputs(B, D, L, 4, 6600 + L, dtype=dtype), dtype=dtype, reverse=reverse)
+
+
 def test_vim_small_shape(lb, oracle):
     """The (B, D, L) of the vim_small workload, as the benchmark would run it."""
     _check(lb, oracle, _inputs(128, 768, 197, 4, 6500))
