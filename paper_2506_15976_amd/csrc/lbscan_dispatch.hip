@@ -1,6 +1,8 @@
 // Launch-shape heuristics of the forward path.
 #include "lbscan_internal.h"
 
+#include <limits.h>
+
 namespace lbscan {
 namespace {
 
@@ -332,21 +334,54 @@ hipError_t launch_bwd(const FwdParams& f, BwdParams p, void* dBm, void* dCm, voi
 // The forward pass leaves z where it is: the scan returns the ungated sum in fp32 and
 // the copy back applies the gate.
 //
-// Measured on MI355X (us, gather / copies; fp32 unless said):
-//   rows x tokens (grid)            forward       backward call
-//   128 x 768, 197 (14 x 14)        362 / 226     1570 / 750
-//   64 x 384, 197                   106 / 71      428 / 243      bf16: 72 / 70, 294 / 236
-//   4 x 768, 1025 (32 x 32)         141 / 77      359 / 209      bf16: 112 / 78, 273 / 212
-//   768, 4096 (64 x 64)             122 / 93      320 / 215      bf16: 118 / 92, 290 / 218
-//   32 x 192, 249 (8 x 31)          40 / 46       160 / 157      bf16: 39 / 47, 154 / 158
-//   16 x 384, 197                   42 / 44       139 / 124
-//   4 x 192, 197                    33 / 30       83 / 79
-//   64, 50 (7 x 7)                  17 / 22       56 / 51
-// The forward call pays for two more launches, so it copies from 2^21 elements on (the
-// line lies between 1.5 and 3.1 million); the backward call always.
+// What a gather costs depends on how far apart the tokens of a tile lie and on how much
+// of the rows the caches hold between tiles: rows of few bytes, grids of few rows or few
+// columns and small calls gather well.  Measured on MI355X (us, gather / copies):
+//   rows x tokens (grid)            forward fp32   forward bf16   backward fp32  backward bf16
+//   128 x 384, 50 (7 x 7)           27 / 43        27 / 42        154 / 180      158 / 167
+//   1042 x 384, 50                  180 / 276      185 / 244      824 / 983      877 / 862
+//   88 x 384, 65 (8 x 8)            34 / 50        34 / 48        161 / 181      179 / 174
+//   127 x 384, 82 (9 x 9)           44 / 73        39 / 60        229 / 229      217 / 209
+//   103 x 384, 101 (10 x 10)        60 / 75        50 / 63        261 / 239      243 / 226
+//   72 x 384, 145 (12 x 12)         66 / 72        52 / 61        277 / 202      214 / 197
+//   90 x 384, 145                   96 / 84        65 / 72        414 / 289      346 / 283
+//   29 x 384, 197 (14 x 14)         82 / 59        56 / 58        233 / 164      195 / 158
+//   106 x 384, 197                  162 / 119      99 / 108       708 / 397      526 / 367
+//   132 x 384, 197                  227 / 145      149 / 135      906 / 480      609 / 430
+//   128 x 768, 197                  351 / 226      207 / 194      1540 / 771     1017 / 677
+//   30 x 384, 257 (16 x 16)         92 / 71        62 / 67        358 / 196      272 / 189
+//   35 x 384, 257                   117 / 76       80 / 71        404 / 207      298 / 201
+//   32 x 384, 325 (18 x 18)         148 / 84       86 / 73        513 / 233      328 / 225
+//   4 x 768, 1025 (32 x 32)         141 / 77       112 / 78       359 / 209      273 / 212
+//   768, 4096 (64 x 64)             120 / 97       119 / 91       321 / 220      278 / 220
+//   119 x 384, 197 (2 x 98)         96 / 125       92 / 112       413 / 422      470 / 375
+//   119 x 384, 197 (65 x 3)         130 / 125      93 / 112       442 / 420      464 / 383
+//   8 x 384, 1025 (4 x 256)         65 / 82        64 / 78        219 / 214      223 / 216
+//   30 x 384, 1025 (4 x 256)        240 / 193      227 / 189      689 / 632      758 / 592
+// (8 x 384, 1025 with 8 x 128 is on the wrong side: 73 / 79, 68 / 78 forward.)
 namespace {
 
-constexpr long kReorderFwdElements = 1L << 21;
+// Elements of a (B,D,L) tensor from which the forward pass copies.  Never below 2^21:
+// it pays for two more launches.
+long reorder_fwd_elements(const FwdParams& p)
+{
+    const int L = p.seqlen, side = p.order.H < p.order.W ? p.order.H : p.order.W;
+    const long never = LONG_MAX;
+    if (side <= 2) return never;
+    long line;
+    if (p.dtype == 0) line = L >= 160 ? 1L << 21 : (L >= 112 ? 4500000L : never);
+    else line = L >= 320 ? 1L << 21 : (L >= 208 ? 3250000L : (L >= 160 ? 9500000L : never));
+    return side <= 4 && line < 8000000L ? 8000000L : line;
+}
+
+// The backward call makes several launches anyway; it moves more per token, so copies
+// win from shorter rows on, and also where the call is too small to fill the chip.
+bool reorder_bwd(const FwdParams& p)
+{
+    const int side = p.order.H < p.order.W ? p.order.H : p.order.W;
+    if ((long)p.batch * p.dim * p.seqlen < 400000L) return true;
+    return p.dtype == 0 ? p.seqlen >= 80 && side > 2 : p.seqlen >= 60;
+}
 
 constexpr size_t kCopyAlign = 256;
 size_t aligned_bytes(size_t n) { return (n + kCopyAlign - 1) / kCopyAlign * kCopyAlign; }
@@ -407,7 +442,7 @@ struct Copies {
 
 size_t fwd_reordered_workspace_bytes(const FwdParams& p)
 {
-    if (!reorder_applies(p) || (long)p.batch * p.dim * p.seqlen < kReorderFwdElements) return 0;
+    if (!reorder_applies(p) || (long)p.batch * p.dim * p.seqlen < reorder_fwd_elements(p)) return 0;
     const CopySizes c = copy_sizes(p);
     return aligned_bytes(fwd_workspace_bytes(in_stored_order(p))) + 2 * c.row + 2 * c.mat + c.row32;
 }
@@ -439,7 +474,7 @@ hipError_t launch_fwd_reordered(FwdParams p, void* workspace, float* saved, hipS
 
 size_t bwd_reordered_workspace_bytes(const FwdParams& f)
 {
-    if (!reorder_applies(f)) return 0;
+    if (!reorder_applies(f) || !reorder_bwd(f)) return 0;
     const CopySizes c = copy_sizes(f);
     return aligned_bytes(bwd_workspace_bytes(in_stored_order(f))) + (5 + (f.z ? 2 : 0)) * c.row + 4 * c.mat;
 }

@@ -61,3 +61,31 @@ def test_scan_order_validation(tmp_path):
     a.grid_h, a.grid_prefix, a.window = 14, 1, 3                    # two-pass forward path: stored order only
     assert lib.lbscan_fwd(ctypes.byref(a), None) == binding.EUNSUPPORTED
     assert lib.lbscan_bidir_fwd(ctypes.byref(a), ctypes.byref(a), None) == binding.EUNSUPPORTED
+
+
+@pytest.mark.parametrize("dtype, B, D, L, grid, fwd, bwd", [
+    # calls that gather faster than they copy, and their neighbours that do not
+    ("fp32", 128, 384, 50, (7, 7), False, False), ("bf16", 128, 384, 50, (7, 7), False, False),
+    ("fp32", 1042, 384, 50, (7, 7), False, False),
+    ("fp32", 88, 384, 65, (8, 8), False, False), ("bf16", 88, 384, 65, (8, 8), False, True),
+    ("fp32", 103, 384, 101, (10, 10), False, True), ("bf16", 516, 384, 101, (10, 10), False, True),
+    ("fp32", 72, 384, 145, (12, 12), False, True), ("fp32", 90, 384, 145, (12, 12), True, True),
+    ("bf16", 359, 384, 145, (12, 12), False, True),
+    ("fp32", 29, 384, 197, (14, 14), True, True), ("bf16", 106, 384, 197, (14, 14), False, True),
+    ("bf16", 132, 384, 197, (14, 14), True, True), ("fp32", 128, 768, 197, (14, 14), True, True),
+    ("bf16", 30, 384, 257, (16, 16), False, True), ("bf16", 35, 384, 257, (16, 16), True, True),
+    ("bf16", 32, 384, 325, (18, 18), True, True), ("bf16", 1, 768, 4096, (64, 64), True, True),
+    ("fp32", 119, 384, 197, (2, 98), False, False), ("bf16", 119, 384, 197, (98, 2), False, True),
+    ("fp32", 40, 384, 197, (65, 3), False, True), ("fp32", 119, 384, 197, (65, 3), True, True),
+    ("fp32", 8, 384, 1025, (4, 256), False, True), ("bf16", 30, 384, 1025, (4, 256), True, True),
+    ("fp32", 1, 64, 50, (7, 7), False, True),               # too small to fill the chip
+    ("fp32", 16, 384, 4097, (64, 64), False, False),        # longer than a block's LDS holds
+])
+def test_copies_only_where_they_are_faster(dtype, B, D, L, grid, fwd, bwd):
+    """Which calls in column order take scratch for reordered copies (both sides of each
+    line as measured, beside the rule in lbscan_dispatch.hip)."""
+    from paper_2506_15976_amd import binding
+    a = binding.LbscanArgs(B, D, 16, L, 4, binding.LBSCAN_FP32 if dtype == "fp32" else binding.LBSCAN_BF16)
+    a.scan_order, (a.grid_h, a.grid_w) = binding.ORDER_COLUMNS, grid
+    assert (binding.lbscan_workspace_bytes(a, binding.WS_FWD_ORDER) > 0) == fwd
+    assert (binding.lbscan_workspace_bytes(a, binding.WS_BWD_ORDER) > 0) == bwd
