@@ -138,18 +138,22 @@ __device__ __forceinline__ Quad<T> quad_raw_fast(const T* __restrict__ base, lon
 // covers the 12 bytes from the address rounded down to 4: the caller guarantees that
 // they lie inside the tensor (one element before an odd address always does; up to
 // two elements after the quad must).
-__device__ __forceinline__ Quad<bf16_t> quad_raw_unaligned(const bf16_t* __restrict__ p)
+struct __attribute__((packed, aligned(4))) Words3 { uint32_t v[3]; };
+// the quad at p from the words around it
+__device__ __forceinline__ Quad<bf16_t> quad_of_words(const Words3& w, const bf16_t* p)
 {
-    struct __attribute__((packed, aligned(4))) Words3 { uint32_t v[3]; };
-    const uintptr_t u = reinterpret_cast<uintptr_t>(p);
-    const Words3 w = *reinterpret_cast<const Words3*>(u & ~static_cast<uintptr_t>(3));
-    const uint32_t sh = (static_cast<uint32_t>(u) & 2u) * 8u;           // 0 or 16
+    const uint32_t sh = (static_cast<uint32_t>(reinterpret_cast<uintptr_t>(p)) & 2u) * 8u;      // 0 or 16
     const uint32_t lo = __builtin_amdgcn_alignbit(w.v[1], w.v[0], sh);
     const uint32_t hi = __builtin_amdgcn_alignbit(w.v[2], w.v[1], sh);
     Quad<bf16_t> q;
     q.v[0].bits = (uint16_t)lo; q.v[1].bits = (uint16_t)(lo >> 16);
     q.v[2].bits = (uint16_t)hi; q.v[3].bits = (uint16_t)(hi >> 16);
     return q;
+}
+__device__ __forceinline__ Quad<bf16_t> quad_raw_unaligned(const bf16_t* __restrict__ p)
+{
+    const uintptr_t u = reinterpret_cast<uintptr_t>(p);
+    return quad_of_words(*reinterpret_cast<const Words3*>(u & ~static_cast<uintptr_t>(3)), p);
 }
 // (fp32 rows need no such path; the overload keeps templates uniform)
 __device__ __forceinline__ Quad<float> quad_raw_unaligned(const float* __restrict__ p)
