@@ -329,11 +329,19 @@ __device__ __forceinline__ void conv_bwd_items(const ConvParams& p, int d, int c
                         for (int k = 0; k < K; ++k)
                             sum = fmaf(w[k], REV ? dwin[3 + e - (K - 1) + k] : dwin[e + (K - 1) - k], sum);
                         dx[e] = sum;
-#pragma unroll
-                        for (int k = 0; k < K; ++k)
-                            acc[k] = fmaf(dpre[e], REV ? win[e + (K - 1) - k] : win[3 + e - (K - 1) + k], acc[k]);
-                        acc[K] += dpre[e];
                     }
+                    // the quad's share is summed by itself first: a quarter of the additions into
+                    // the running sums (error of dweight against 64 bits at 128 x 768 x 197:
+                    // 1.8e-7 -> 1.4e-7, same time)
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        float part = 0.0f;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            part = fmaf(dpre[e], REV ? win[e + (K - 1) - k] : win[3 + e - (K - 1) + k], part);
+                        acc[k] += part;
+                    }
+                    acc[K] += (dpre[0] + dpre[1]) + (dpre[2] + dpre[3]);
                     conv_store<T, HOW>(dxg + roff[u], t0, L, dx);
                 }
             }

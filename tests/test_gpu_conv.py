@@ -96,6 +96,32 @@ def test_vim_small_shape(lb, oracle):
     _check(lb, oracle, _inputs(128, 768, 197, 4, 6500))
 
 
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_filter_gradient_rounding(lb, dtype):
+    """Rounding error of the sums over batch and time against 64 bits, 2-norm over all
+    channels.  A sum of m independent terms, one after the other, has a relative error of
+    c 2^-24 sqrt(m / 2), c about 1/2; stages add in quadrature.  16 x 64 waves' lanes sum
+    16 quads (m = 16) of four products (m = 4), the wave folds them in 6 steps and 8
+    waves' sums meet (m = 8): sqrt(8 + 2 + 6 + 4) / 2 x 2^-24 = 1.33e-7, and a fifth for the
+    estimate of c.  (All 64 products one after the other: 1.9e-7.)"""
+    import torch
+    B, D, L, K = 128, 768, 197, 4
+    g = torch.Generator().manual_seed(6700)
+    x, dy = (torch.randn(B, D, L, generator=g).cuda().to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+             for _ in range(2))
+    w, b = (torch.randn(D, K, generator=g) / 2).cuda(), (torch.randn(D, generator=g) / 4).cuda()
+    got = lb.lbscan_conv1d_bwd(x, w, b, dy=dy)
+    xp = torch.nn.functional.pad(x.double(), (K - 1, 0))
+    pre = sum(w.double()[:, k, None] * xp[..., k:k + L] for k in range(K)) + b.double()[:, None]
+    sg = torch.sigmoid(pre)
+    dpre = dy.double() * sg * (1 + pre * (1 - sg))
+    ref = dict(dweight=torch.stack([(dpre * xp[..., k:k + L]).sum((0, 2)) for k in range(K)], 1),
+               dbias=dpre.sum((0, 2)))
+    for k, r in ref.items():
+        err = float((got[k].double() - r).norm() / r.norm())
+        assert err <= 1.6e-7, f"{k}: {err:.3e}"
+
+
 def test_unsupported_width_and_empty(lb):
     import torch
     x = torch.zeros((1, 2, 8), device="cuda")
