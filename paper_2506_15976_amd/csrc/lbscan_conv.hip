@@ -389,20 +389,10 @@ hipError_t launch_conv_krh(ConvParams p, bool bwd, hipStream_t s)
 {
     const long nq = (p.seqlen + 3) / 4;
     const long chunks = bwd ? (nq + 62) / 63 : (nq + 63) / 64;
-    // items per wave: about 8 waves per SIMD of the chip in all, at most 64 items.  The
-    // fp32 backward kernel's registers allow 6: with 8 a quarter of its waves made a
-    // round of their own; its items are whole groups of kConvUnroll where there are
-    // enough (5 items took 24.2 us where 4 take 23.1, 16 x 384 x 1025).  Measured, 8 against 6:
-    // 128 x 768 x 197 62.8 -> 57.7 us, 64 x 384 x 197 22.3 -> 19.6, 32 x 768 x 577
-    // 52.2 -> 45.4; the bf16 kernel (7 fit) lost with 7: 64.4 -> 74.5
     const long items = (long)p.batch * chunks;
     if (items > 0x7fffffffL) return hipErrorInvalidConfiguration;
-    const bool six = bwd && sizeof(T) == 4;
-    const long resident = six ? 6144 : 8192;
-    long per_wave = ((long)p.dim * items + resident - 1) / resident;
-    if (six && per_wave > kConvUnroll) per_wave = (per_wave + 1) / kConvUnroll * kConvUnroll;
-    per_wave = per_wave < 1 ? 1 : (per_wave > 64 ? 64 : per_wave);
-    p.items_per_wave = (int)per_wave;
+    p.items_per_wave = conv_items_per_wave(bwd, p.dim, items);
+    const long per_wave = p.items_per_wave;
     const long waves = (long)p.dim * ((items + per_wave - 1) / per_wave);
     const long blocks = (waves + kConvWaves - 1) / kConvWaves;
     if (blocks > 0x3fffffffL) return hipErrorInvalidConfiguration;     // wave ids fit 32 bits

@@ -38,4 +38,26 @@ LBSCAN_PLAN_FN int conv_last_row_items(int d, int dim, unsigned i0, int n, unsig
     return d != dim - 1 || in <= 0 ? 0 : (in < n ? (int)in : n);
 }
 
+// Items ((batch entry, chunk) pairs of a channel) per wave.  Forward: about 8 waves per
+// SIMD of the chip in all.  Backward: one group of the four items whose loads are in flight
+// together, two groups where that still makes 8 waves per SIMD and more: shorter waves fill
+// the chip's last round better than waves that fit it in one round.  Measured (fp32, K = 4,
+// us, 4 / 8 / one round of 6 waves per SIMD): 48 x 768 x 197 23.2 / 24.1 / 24.1,
+// 72 x 768 x 197 30.7 / 32.2 / 32.6 and 26.8 / 25.5 / 25.3 with inputs in the Infinity
+// Cache, 128 x 768 x 197 48.2 / 50.5 / 51.6 and 41.5 / 41.3 / 41.4, 16 x 384 x 1025
+// 21.7 / 21.2 / 22.8, 512 x 768 x 197 171 / 183 / 199; K = 1..3 and bf16 alike within 3%.
+// Each wave adds its sums to the channel's with fp32 atomics: at most 64 of them meet there
+// (until waves are 64 items long), or their rounding would outgrow that of longer waves.
+LBSCAN_PLAN_FN int conv_items_per_wave(bool bwd, long dim, long items)
+{
+    const long resident = bwd ? 6 * 1024 : 8 * 1024;
+    long per = (dim * items + resident - 1) / resident;
+    if (bwd && per > 4) {
+        const long meet = (items + 255) / 256 * 4;          // whole groups, 64 sums
+        per = per < 8 ? 4 : 8;
+        per = per < meet ? meet : per;
+    }
+    return (int)(per < 1 ? 1 : (per > 64 ? 64 : per));
+}
+
 }  // namespace lbscan

@@ -47,6 +47,7 @@ extern "C" int check_last_row(int batch, int dim, int chunks, int per)
         }
     return 0;
 }
+extern "C" int per_wave(int bwd, long dim, long items) { return conv_items_per_wave(bwd, dim, items); }
 extern "C" int way(int two_byte, long rows, int L) { return conv_loads(two_byte, rows, L); }
 """
 
@@ -82,3 +83,19 @@ def test_ways_of_loading(plan):
     assert [plan.way(1, 2, L) for L in (3, 4, 5, 196, 197)] == [elements, quads, unaligned, quads, unaligned]
     assert [plan.way(0, 1, L) for L in (3, 4, 5, 197)] == [elements, quads, quads, quads]
     assert plan.way(1, 1, 197) == elements                  # a single odd row: nothing after it to reach into
+
+
+def test_items_per_wave(plan):
+    """Backward: one or two groups of four, whatever the type and the filter width, and few
+    enough sums per channel; small calls one item per wave until the chip is full."""
+    plan.per_wave.argtypes = [ctypes.c_int, ctypes.c_long, ctypes.c_long]
+    for (B, D, chunks), want in {(1, 64, 1): 1, (24, 768, 1): 3, (48, 768, 1): 4, (56, 768, 1): 4, (72, 768, 1): 8,
+                                 (80, 768, 1): 8, (128, 768, 1): 8, (512, 768, 1): 8, (96, 384, 1): 4,
+                                 (16, 384, 5): 4, (1, 512, 1041): 20, (256, 768, 5): 20, (4096, 768, 4): 64}.items():
+        assert plan.per_wave(1, D, B * chunks) == want, (B, D, chunks)
+    for dim in (1, 3, 64, 768):
+        for items in list(range(1, 300)) + [4096, 5000, 1 << 20]:
+            n = plan.per_wave(1, dim, items)
+            assert 1 <= n <= 64 and (n <= 4 or n % 4 == 0)
+            if dim * items > 4 * 6144:
+                assert n == 64 or -(-items // n) <= 64

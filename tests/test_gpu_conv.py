@@ -100,10 +100,10 @@ def test_vim_small_shape(lb, oracle):
 def test_filter_gradient_rounding(lb, dtype):
     """Rounding error of the sums over batch and time against 64 bits, 2-norm over all
     channels.  A sum of m independent terms, one after the other, has a relative error of
-    c 2^-24 sqrt(m / 2), c about 1/2; stages add in quadrature.  16 x 64 waves' lanes sum
-    16 quads (m = 16) of four products (m = 4), the wave folds them in 6 steps and 8
-    waves' sums meet (m = 8): sqrt(8 + 2 + 6 + 4) / 2 x 2^-24 = 1.33e-7, and a fifth for the
-    estimate of c.  (All 64 products one after the other: 1.9e-7.)"""
+    c 2^-24 sqrt(m / 2), c about 1/2; stages add in quadrature.  A lane sums 8 quads (m = 8)
+    of four products (m = 4), the wave folds its lanes in 6 steps and 16 waves' sums meet
+    (m = 16): sqrt(4 + 2 + 6 + 8) / 2 x 2^-24 = 1.33e-7, and a fifth for the estimate of c.
+    (64 products one after the other in a lane, 8 waves: 1.9e-7.)"""
     import torch
     B, D, L, K = 128, 768, 197, 4
     g = torch.Generator().manual_seed(6700)
