@@ -194,6 +194,39 @@ def lbscan_version() -> str:
     return load().lbscan_version().decode()
 
 
+# Devices whose last attempt at an optional block failed.  They are asked what is left before
+# the next attempt (about 20 us of host time, which other calls do not pay).
+_short_of_memory = set()
+
+
+def _room_for(nbytes, device):
+    """Whether the device can give a block of nbytes now."""
+    import torch
+    free, total = torch.cuda.mem_get_info(device)
+    stats = torch.cuda.memory_stats_as_nested_dict(device)
+    reserved, active = (stats.get(k, {}).get("all", {}).get("current", 0)
+                        for k in ("reserved_bytes", "active_bytes"))
+    may_grow = min(free, total * torch.cuda.get_per_process_memory_fraction(device) - reserved)
+    return nbytes <= may_grow + reserved - active
+
+
+def _optional_block(nbytes, device):
+    """A block that the call can do without, or None.  The caching allocator gives all its
+    cached blocks back before it reports that it cannot serve a request, and the next
+    allocations fetch them anew (2.5 ms a call): near the memory limit that may happen
+    once, not on every call."""
+    import torch
+    if device in _short_of_memory and not _room_for(nbytes, device):
+        return None
+    try:
+        block = torch.empty((nbytes + 3) // 4, dtype=torch.float32, device=device)
+    except torch.cuda.OutOfMemoryError:
+        _short_of_memory.add(device)
+        return None
+    _short_of_memory.discard(device)
+    return block
+
+
 def _workspace_for(args, which, like, stream=None):
     """Scratch for one call.  It is allocated from torch's caching allocator on the
     current stream; when the call runs on another stream the block is tied to that
@@ -205,10 +238,7 @@ def _workspace_for(args, which, like, stream=None):
         # the larger scratch of the reordered copies, when the device has it
         more = lbscan_workspace_bytes(args, {WS_FWD: WS_FWD_ORDER, WS_BWD: WS_BWD_ORDER}[which])
         if more > need:
-            try:
-                ws = torch.empty((more + 3) // 4, dtype=torch.float32, device=like.device)
-            except torch.cuda.OutOfMemoryError:
-                pass
+            ws = _optional_block(more, like.device)
     if ws is None:
         if need == 0:
             return None
