@@ -86,7 +86,8 @@ def test_bf16_storage(lb, oracle, L):
 @pytest.mark.parametrize("B, D, L", [(1, 1, 253), (1, 2, 255), (2, 1, 257), (2, 3, 505), (1, 3, 3), (3, 1, 4)])
 def test_halo_and_last_row_edges(lb, oracle, B, D, L, dtype):
     """Chunks of 252 and 256 tokens meet here with one to three tokens left; the last row of
-    a 2-byte tensor of odd rows may not be read past its end; rows of fewer than four."""
+    a 2-byte tensor of odd rows, loaded in its own way (that no load leaves the tensor is
+    checked in test_conv_plan.py); a single such row; rows of fewer than four."""
     for reverse in (False, True):
         _check(lb, oracle, _inputs(B, D, L, 4, 6600 + L, dtype=dtype), dtype=dtype, reverse=reverse)
 

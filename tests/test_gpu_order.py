@@ -142,3 +142,129 @@ def test_reordered_copies_match_the_gather(lb, monkeypatch, B, D, N, L, grid, wi
         r = v.float()
         bound = rel * torch.maximum(r.abs(), r.square().mean().sqrt())
         assert bool(((copied[k].float() - r).abs() <= bound).all()), k
+
+
+# ---- column order with everything else a call can take, gathers and copies ----------
+
+@pytest.fixture
+def route(monkeypatch):
+    """route(False): calls get no scratch for reordered copies, as on a full device."""
+    from paper_2506_15976_amd import binding
+    have = binding._optional_block
+    return lambda copies: monkeypatch.setattr(binding, "_optional_block", have if copies else lambda n, device: None)
+
+
+def _states(B, D, N, seed):
+    r = np.random.default_rng(seed)
+    return (r.standard_normal((B, D, N)).astype(np.float32), r.standard_normal((B, D, N)).astype(np.float32))
+
+
+def _scanned(s, grid, reverse):
+    """Inputs as the oracle takes them, and the way back to stored order."""
+    from gpu_util import flip_time
+    from paper_2506_15976_amd.inputs import column_order
+    perm = column_order(s["x"].shape[-1], *grid)
+    seq = _reordered(s, perm)
+    inv = np.argsort(perm)
+    return (flip_time(seq) if reverse else seq), lambda v: (v[..., ::-1] if reverse else v)[..., inv]
+
+
+PAIRS = [(True, True), (False, False), (True, False), (False, True)]
+
+
+@pytest.mark.parametrize("shape, grid, dtype, pairs", [
+    # the forward call gathers, the backward call copies (when it may); with checkpoints
+    ((3, 70, 16, 50), (7, 7), "fp32", [(True, True), (True, False)]),
+    ((3, 70, 16, 50), (7, 7, 1), "bf16", [(True, True), (True, False)]),
+    # both copy, rows not cut: with checkpoints
+    ((130, 83, 16, 197), (14, 14, 1), "fp32", PAIRS),
+    # both copy, rows cut into segments: no checkpoints
+    ((9, 61, 16, 4096), (64, 64), "bf16", [(True, True), (False, True)]),
+])
+@pytest.mark.parametrize("reverse", [False, True])
+def test_states_and_checkpoints(lb, oracle, route, shape, grid, dtype, pairs, reverse):
+    """The state entering and leaving the call, its gradients, and checkpoints that one
+    route leaves and the other one reads, on a stream of the caller's."""
+    import torch
+    from gpu_util import assert_close, fwd_inputs, to_device, to_numpy
+    from paper_2506_15976_amd.inputs import make_inputs
+    B, D, N, L = shape
+    s = make_inputs(B, D, N, L, seed=3500 + L, with_dout=True, random_A=True, dtype=dtype)
+    h0, dhT = _states(B, D, N, 3501 + L)
+    src, back = _scanned(s, grid, reverse)
+    ref, ref_hT = oracle.fwd(**fwd_inputs(src), window=4, h0=h0, return_state=True)
+    gr = oracle.bwd(**fwd_inputs(src), dout=src["dout"], window=4, h0=h0, dhT=dhT)
+    dev = to_device(s, dtype)
+    h0d, dhTd = torch.from_numpy(h0).cuda(), torch.from_numpy(dhT).cuda()
+    stream = torch.cuda.Stream()
+    for fwd_copies, bwd_copies in pairs:
+        saved = lb.lbscan_saved_state(dev["x"], dev["A"], window=4)
+        assert (saved is not None) == (L < 4096)
+        torch.cuda.synchronize()
+        route(fwd_copies)
+        out, hT = lb.lbscan_fwd(**fwd_inputs(dev), window=4, reverse=reverse, grid=grid, h0=h0d, saved_state=saved,
+                                return_state=True, stream=stream)
+        route(bwd_copies)
+        g = lb.lbscan_bwd(**fwd_inputs(dev), dout=dev["dout"], window=4, reverse=reverse, grid=grid, h0=h0d,
+                          dhT=dhTd, saved_state=saved, stream=stream)
+        torch.cuda.synchronize()
+        assert_close(to_numpy(out), back(ref), dtype, "out")
+        assert_close(to_numpy(hT), ref_hT, "fp32", "hT")
+        for k, r in gr.items():
+            assert_close(to_numpy(g[k]), back(r) if k in GRADS3 else r, "fp32" if k == "dh0" else dtype, k)
+
+
+@pytest.mark.parametrize("copies", [True, False])
+@pytest.mark.parametrize("window", [3, 12, 1000])
+def test_backward_windows_without_a_compiled_kernel(lb, oracle, route, window, copies):
+    import torch
+    from gpu_util import assert_close, fwd_inputs, to_device, to_numpy
+    from paper_2506_15976_amd.inputs import make_inputs
+    s = make_inputs(2, 70, 16, 101, seed=3600 + window, with_dout=True, random_A=True)
+    src, back = _scanned(s, (10, 10), False)
+    gr = oracle.bwd(**fwd_inputs(src), dout=src["dout"], window=window)
+    dev = to_device(s, "fp32")
+    route(copies)
+    g = lb.lbscan_bwd(**fwd_inputs(dev), dout=dev["dout"], window=window, grid=(10, 10))
+    torch.cuda.synchronize()
+    for k, r in gr.items():
+        if r is not None:
+            assert_close(to_numpy(g[k]), back(r) if k in GRADS3 else r, "fp32", k)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_copies_replay_from_a_graph(lb, dtype):
+    """Forward call with checkpoints and backward call from them, both on copies, recorded
+    once; every replay against the eager results, with eager work in between."""
+    import torch
+    from gpu_util import fwd_inputs, to_device
+    from paper_2506_15976_amd import binding
+    from paper_2506_15976_amd.inputs import make_inputs
+    s = make_inputs(67, 83, 4, 401, seed=3700, with_dout=True, dtype=dtype)
+    dev = to_device(s, dtype)
+    a = binding.make_args(**fwd_inputs(dev), window=8, grid=(20, 20, 1))
+    assert all(binding.lbscan_workspace_bytes(a, w) for w in (binding.WS_FWD_ORDER, binding.WS_BWD_ORDER))
+
+    def step():
+        out = lb.lbscan_fwd(**fwd_inputs(dev), window=8, grid=(20, 20, 1))
+        return {"out": out, **lb.lbscan_bwd(**fwd_inputs(dev), dout=dev["dout"], window=8, grid=(20, 20, 1))}
+    eager = {k: v.clone() for k, v in step().items()}
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        recorded = step()
+    summed = ("dA", "dDskip", "ddelta_bias")        # fp32 atomics: their last bits vary
+    for k in range(3):
+        for v in recorded.values():
+            v.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for name, v in recorded.items():
+            if name in summed:
+                assert float((v - eager[name]).norm() / eager[name].norm()) <= 1e-5, (name, k)
+            else:
+                assert torch.equal(v, eager[name]), (name, k)
+        again = step()
+        torch.cuda.synchronize()
+        assert torch.equal(again["out"], eager["out"])
