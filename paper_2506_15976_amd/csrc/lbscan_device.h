@@ -96,35 +96,13 @@ template <typename T> struct Quad;
 template <> struct __attribute__((packed, aligned(4))) Quad<float> { float v[4]; };
 template <> struct __attribute__((packed, aligned(4))) Quad<bf16_t> { bf16_t v[4]; };
 
-// One quad of a (rows, L) tensor.  `base` is uniform, `off` the element offset of
-// quad element 0 and `ph` its token index.  The fast form is one unconditional
-// quad load.  The checked form zeroes elements whose token index ph + e is outside
-// [0, L); it loads from a clamped (always valid) address and selects afterwards,
-// so that no load sits behind a divergent branch: a load that is conditionally
-// re-issued into the same registers would force the compiler to wait for the
-// first one and serialise the prefetch.
-template <typename T>
-__device__ __forceinline__ void quad_load_fast(const T* __restrict__ base, long off, float out[4])
-{
-    const Quad<T> q = *reinterpret_cast<const Quad<T>*>(base + off);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) out[e] = to_f32(q.v[e]);
-}
-
-template <typename T>
-__device__ __forceinline__ void quad_load_checked(const T* __restrict__ base, long off, int ph,
-                                                  int L, float out[4])
-{
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int t = ph + e;
-        const int tc = t < 0 ? 0 : (t >= L ? L - 1 : t);
-        const float v = to_f32(base[off + (tc - ph)]);
-        out[e] = (t == tc) ? v : 0.0f;
-    }
-}
-
-// The same two loads, returning the raw quad (storage type) for later conversion.
+// One quad of a (rows, L) tensor in its storage type, for later conversion.  `base` is
+// uniform, `off` the element offset of quad element 0 and `ph` its token index.  The fast
+// form is one unconditional quad load.  The checked form (further down) zeroes elements
+// whose token index ph + e is outside [0, L); it loads from a clamped (always valid)
+// address and selects afterwards, so that no load sits behind a divergent branch: a load
+// that is conditionally re-issued into the same registers would force the compiler to wait
+// for the first one and serialise the prefetch.
 template <typename T>
 __device__ __forceinline__ Quad<T> quad_raw_fast(const T* __restrict__ base, long off)
 {
