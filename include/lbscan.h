@@ -109,8 +109,8 @@ typedef struct lbscan_args {
        applied to the sequence in that order and every (B,D,L) / (B,N,L) tensor, inputs
        and outputs alike, stays in stored order.  reverse = 1
        reverses the scanned sequence.  Kernels then gather token by token; a call whose
-       workspace holds LBSCAN_WS_FWD_ORDER / LBSCAN_WS_BWD_ORDER bytes (up to 4096 tokens)
-       works on reordered copies in it instead, which is faster.  lbscan_fwd
+       workspace holds LBSCAN_WS_FWD_ORDER / LBSCAN_WS_BWD_ORDER bytes works on reordered
+       copies in it instead, where that is faster.  lbscan_fwd_static gathers.  lbscan_fwd
        with a window length outside {1,2,4,8,16} and lbscan_bidir_fwd support only the
        stored order (LBSCAN_EUNSUPPORTED otherwise); lbscan_bwd supports every window. */
     int32_t scan_order;
@@ -125,8 +125,11 @@ typedef struct lbscan_args {
 #define LBSCAN_WS_BIDIR 2
 #define LBSCAN_WS_SAVED 3   /* size of lbscan_args.saved_state (0: these shapes do not use it) */
 /* Optional larger workspace of lbscan_fwd / lbscan_bwd for a scan order other than the
-   stored one (0: no such path for these sizes).  Includes LBSCAN_WS_FWD / LBSCAN_WS_BWD;
-   for the backward size, args->z says whether there is a gate. */
+   stored one (0: these sizes gather faster, or have more than 4096 tokens).  Includes
+   LBSCAN_WS_FWD / LBSCAN_WS_BWD; for the backward size, args->z says whether there is a
+   gate.  It is large: two (forward; and one in fp32) or seven (backward, with a gate)
+   tensors of x's size and two or four of Bm's, 236 MB and 674 MB at 128 x 768 x 16 x 197
+   in fp32. */
 #define LBSCAN_WS_FWD_ORDER 4
 #define LBSCAN_WS_BWD_ORDER 5
 

@@ -358,7 +358,9 @@ hipError_t launch_bwd(const FwdParams& f, BwdParams p, void* dBm, void* dCm, voi
 //   119 x 384, 197 (65 x 3)         130 / 125      93 / 112       442 / 420      464 / 383
 //   8 x 384, 1025 (4 x 256)         65 / 82        64 / 78        219 / 214      223 / 216
 //   30 x 384, 1025 (4 x 256)        240 / 193      227 / 189      689 / 632      758 / 592
-// (8 x 384, 1025 with 8 x 128 is on the wrong side: 73 / 79, 68 / 78 forward.)
+// (8 x 384, 1025 with 8 x 128 is on the wrong side: 73 / 79, 68 / 78 forward.)  The copies
+// ask for an fp32 result, which the chunk-per-lane kernel gives for bf16 only with window
+// 1: bf16 images of 4096 tokens run the row-per-lane kernels here (8 x 768: 2023 / 379).
 namespace {
 
 // Elements of a (B,D,L) tensor from which the forward pass copies.  Never below 2^21:
