@@ -358,9 +358,16 @@ hipError_t launch_bwd(const FwdParams& f, BwdParams p, void* dBm, void* dCm, voi
 //   119 x 384, 197 (65 x 3)         130 / 125      93 / 112       442 / 420      464 / 383
 //   8 x 384, 1025 (4 x 256)         65 / 82        64 / 78        219 / 214      223 / 216
 //   30 x 384, 1025 (4 x 256)        240 / 193      227 / 189      689 / 632      758 / 592
-// (8 x 384, 1025 with 8 x 128 is on the wrong side: 73 / 79, 68 / 78 forward.)  The copies
-// ask for an fp32 result, which the chunk-per-lane kernel gives for bf16 only with window
-// 1: bf16 images of 4096 tokens run the row-per-lane kernels here (8 x 768: 2023 / 379).
+//   6 x 384, 1025 (8 x 128)         77 / 76        65 / 77        245 / 180      210 / 174
+//   8 x 384, 1025 (8 x 128)         73 / 80        69 / 78        271 / 213      241 / 216
+//   11 x 384, 1025 (8 x 128)        149 / 95       132 / 87       442 / 256      414 / 249
+//   3 x 384, 2049 (8 x 256)         97 / 80        76 / 80        257 / 187      232 / 184
+//   4 x 384, 2049 (8 x 256)         72 / 90        68 / 86        261 / 222      229 / 229
+// (How fast a gather of few long rows is goes up and down with how their blocks fill the
+// chip: fp32 at 8 x 384 and 4 x 384 is on the wrong side of the line.)
+// The copies ask for an fp32 result, which the chunk-per-lane kernel gives for bf16 only
+// with window 1: bf16 images of 4096 tokens run the row-per-lane kernels here (8 x 768:
+// 2023 / 379).
 namespace {
 
 // Elements of a (B,D,L) tensor from which the forward pass copies.  Never below 2^21:
@@ -373,7 +380,8 @@ long reorder_fwd_elements(const FwdParams& p)
     long line;
     if (p.dtype == 0) line = L >= 160 ? 1L << 21 : (L >= 112 ? 4500000L : never);
     else line = L >= 320 ? 1L << 21 : (L >= 208 ? 3250000L : (L >= 160 ? 9500000L : never));
-    return side <= 4 && line < 8000000L ? 8000000L : line;
+    if (side <= 4) return line < 8000000L ? 8000000L : line;
+    return p.dtype != 0 && side <= 8 && L >= 1000 ? 4000000L : line;
 }
 
 // The backward call makes several launches anyway; it moves more per token, so copies

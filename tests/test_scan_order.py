@@ -78,6 +78,8 @@ def test_scan_order_validation(tmp_path):
     ("fp32", 119, 384, 197, (2, 98), False, False), ("bf16", 119, 384, 197, (98, 2), False, True),
     ("fp32", 40, 384, 197, (65, 3), False, True), ("fp32", 119, 384, 197, (65, 3), True, True),
     ("fp32", 8, 384, 1025, (4, 256), False, True), ("bf16", 30, 384, 1025, (4, 256), True, True),
+    ("bf16", 8, 384, 1025, (8, 128), False, True), ("bf16", 11, 384, 1025, (8, 128), True, True),
+    ("fp32", 6, 384, 1025, (8, 128), True, True), ("bf16", 6, 384, 1025, (32, 32), True, True),
     ("fp32", 1, 64, 50, (7, 7), False, True),               # too small to fill the chip
     ("fp32", 16, 384, 4097, (64, 64), False, False),        # longer than a block's LDS holds
 ])
