@@ -1,10 +1,10 @@
-// Row-per-lane backward kernels, bf16 storage (fp32 arithmetic).
+// Backward kernels, bf16 storage (fp32 arithmetic).
 #include "lbscan_device.h"
 #include "lbscan_internal.h"
-#include "lbscan_bwd_rowlane.inc"
+#include "lbscan_bwd_wave.inc"
 
 namespace lbscan {
-hipError_t launch_bwd_rowlane_bf16(const BwdParams& p, hipStream_t stream)
+hipError_t launch_bwd_bf16(const BwdParams& p, hipStream_t stream)
 {
     return launch_bwd_t<bf16_t>(p, stream);
 }

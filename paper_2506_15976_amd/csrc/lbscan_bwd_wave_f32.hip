@@ -1,10 +1,10 @@
-// Row-per-lane backward kernels, fp32 storage.
+// Backward kernels, fp32 storage.
 #include "lbscan_device.h"
 #include "lbscan_internal.h"
-#include "lbscan_bwd_rowlane.inc"
+#include "lbscan_bwd_wave.inc"
 
 namespace lbscan {
-hipError_t launch_bwd_rowlane_f32(const BwdParams& p, hipStream_t stream)
+hipError_t launch_bwd_f32(const BwdParams& p, hipStream_t stream)
 {
     return launch_bwd_t<float>(p, stream);
 }

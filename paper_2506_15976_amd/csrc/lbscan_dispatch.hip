@@ -295,7 +295,7 @@ hipError_t launch_bwd(const FwdParams& f, BwdParams p, void* dBm, void* dCm, voi
         p.ckpt = saved;
         p.cum = nullptr;
         p.carry = nullptr;
-        e = f.dtype == 0 ? launch_bwd_rowlane_f32(p, stream) : launch_bwd_rowlane_bf16(p, stream);
+        e = f.dtype == 0 ? launch_bwd_f32(p, stream) : launch_bwd_bf16(p, stream);
         return e != hipSuccess ? e : finish();
     }
 
@@ -322,7 +322,7 @@ hipError_t launch_bwd(const FwdParams& f, BwdParams p, void* dBm, void* dCm, voi
         if ((e = launch_carry_chain_reverse(q, q.psi, dhT, stream)) != hipSuccess) return e;
     }
 
-    e = f.dtype == 0 ? launch_bwd_rowlane_f32(p, stream) : launch_bwd_rowlane_bf16(p, stream);
+    e = f.dtype == 0 ? launch_bwd_f32(p, stream) : launch_bwd_bf16(p, stream);
     return e != hipSuccess ? e : finish();
 }
 

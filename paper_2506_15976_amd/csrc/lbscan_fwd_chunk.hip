@@ -42,7 +42,7 @@ constexpr int kChunk = 64 * kP;        // tokens per wave and chunk
 #define LBSCAN_CHUNK_MINBLOCKS 3
 #endif
 constexpr int kR = LBSCAN_CHUNK_ROWS;  // rows (waves) per block
-constexpr int kPitch = kP + 4;         // LDS pitch of a lane's tokens (16-byte reads, see lbscan_bwd_rowlane.inc)
+constexpr int kPitch = kP + 4;         // LDS pitch of a lane's tokens (16-byte reads, see lbscan_bwd_wave.inc)
 constexpr int kBuf = 64 * kPitch;      // floats of one staged chunk
 
 __device__ __forceinline__ void lds_get4(const float* a, int o, float (&v)[4])

@@ -150,9 +150,9 @@ size_t fwd_generic_workspace_bytes(const FwdParams& p);
 // pass then needs its own summary pass anyway).
 size_t saved_state_bytes(const FwdParams& p);
 
-// Backward kernels (lbscan_bwd_rowlane.inc), one translation unit per storage type.
-hipError_t launch_bwd_rowlane_f32(const BwdParams& p, hipStream_t stream);
-hipError_t launch_bwd_rowlane_bf16(const BwdParams& p, hipStream_t stream);
+// Backward kernels (lbscan_bwd_wave.inc), one translation unit per storage type.
+hipError_t launch_bwd_f32(const BwdParams& p, hipStream_t stream);
+hipError_t launch_bwd_bf16(const BwdParams& p, hipStream_t stream);
 // dBm, dCm (storage type) = the partial sums of BwdParams::dBpart added over the nbx
 // blocks of 64 channels; bnl = B * N * L.
 hipError_t launch_reduce_f32(const float* part, void* dB, void* dC, long bnl, int nbx, hipStream_t stream);
