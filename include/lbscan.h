@@ -226,18 +226,17 @@ int lbscan_default_window(int32_t seqlen);
  * lbscan_workspace_bytes returns and what the calls expect, so set options before
  * other threads query sizes or launch, never between a thread's size query and its
  * call.
- *   "waves_log2": -1 (default) lets the library choose over how many waves of
- *                 a block the N states of a row are split; 0..3 forces 1, 2, 4
- *                 or 8 (clamped to what the state size allows).
+ *   "waves_log2": -1 .. 3 is accepted and has no effect: the N states of a row
+ *                 stay inside one wave, and there is one way of spreading them.
  *   "segments":   0 (default) lets the library choose into how many segments a
  *                 row is cut for parallel scanning (long rows, few channels);
  *                 k >= 1 asks for k (rounded so that segments are whole 32-token tiles).  It
  *                 changes lbscan_workspace_bytes: query after setting it.
  *   "mapping":    0 (default) lets lbscan_fwd choose between its two kernel
- *                 families: one lane per row (rows walked in tiles; cut into
+ *                 families: waves of eight rows (walked in tiles; cut into
  *                 segments when rows are few) and one wave per row with 16 tokens
  *                 per lane (the tile-per-thread organisation of Sec. 3.4; picked
- *                 for long bf16 rows that are many).  1 forces the first, 2 the
+ *                 for rows of about 1024 tokens and more).  1 forces the first, 2 the
  *                 second wherever it applies (compiled window lengths, stored
  *                 order, rows that allow 16-byte accesses); other
  *                 calls are not affected.  Results agree within the tolerance of

@@ -31,9 +31,7 @@ int scratch_too_small(size_t need, size_t have, bool fixed)
 }
 
 // Launch-shape overrides set through lbscan_set_option (tuning and tests).
-std::atomic<int> g_waves_log2{-1};
 std::atomic<int> g_nseg{0};
-int tuning_waves_log2() { return g_waves_log2.load(std::memory_order_relaxed); }
 std::atomic<int> g_mapping{0};
 int tuning_nseg() { return g_nseg.load(std::memory_order_relaxed); }
 
@@ -102,7 +100,6 @@ lbscan::FwdParams to_params(const lbscan_args* a, int window)
     p.x = a->x; p.delta = a->delta; p.Bm = a->Bm; p.Cm = a->Cm; p.z = a->z;
     p.A = a->A; p.Dskip = a->Dskip; p.bias = a->delta_bias;
     p.yprev = nullptr; p.y = a->y; p.y_is_f32 = 0;
-    p.force_waves_log2 = tuning_waves_log2();
     p.force_nseg = tuning_nseg();
     p.force_mapping = g_mapping.load(std::memory_order_relaxed);
     p.nseg = 1; p.seg_tiles = 0; p.summary_only = 0; p.fold_chain = 0; p.carry = nullptr; p.dsum = nullptr;
@@ -433,7 +430,6 @@ int lbscan_set_option(const char* name, int value)
     if (!name) return LBSCAN_EINVAL;
     if (strcmp(name, "waves_log2") == 0) {
         if (value < -1 || value > 3) return LBSCAN_EINVAL;
-        g_waves_log2.store(value, std::memory_order_relaxed);
         return LBSCAN_OK;
     }
     if (strcmp(name, "segments") == 0) {

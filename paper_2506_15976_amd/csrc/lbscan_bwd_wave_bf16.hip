@@ -4,7 +4,7 @@
 #include "lbscan_bwd_wave.inc"
 
 namespace lbscan {
-hipError_t launch_bwd_bf16(const BwdParams& p, hipStream_t stream)
+hipError_t launch_bwd_wave_bf16(const BwdParams& p, hipStream_t stream)
 {
     return launch_bwd_t<bf16_t>(p, stream);
 }

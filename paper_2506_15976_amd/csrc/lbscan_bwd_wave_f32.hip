@@ -4,7 +4,7 @@
 #include "lbscan_bwd_wave.inc"
 
 namespace lbscan {
-hipError_t launch_bwd_f32(const BwdParams& p, hipStream_t stream)
+hipError_t launch_bwd_wave_f32(const BwdParams& p, hipStream_t stream)
 {
     return launch_bwd_t<float>(p, stream);
 }

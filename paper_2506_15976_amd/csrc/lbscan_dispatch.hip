@@ -6,40 +6,21 @@
 namespace lbscan {
 namespace {
 
-struct Shape { int waves_log2, nseg, seg_tiles; };
+struct Shape { int nseg, seg_tiles; };
 
 // Up to this many segments the full forward pass folds the carry chain itself.
 constexpr int kFoldChainSegments = 16;
 
-// The row-per-lane kernel runs one wave per (64 rows, state group, segment).
-// MI355X has 256 CUs x 4 SIMDs; the kernel needs a few waves per SIMD to cover
-// LDS and memory latency.
-//  * The N states of a row are split over 4 waves of the block (4 states each):
-//    measured best at every workload shape (one wave with all 16 states needs
-//    256 registers; 8 waves repeat too much per-token work).
-//  * If the rows alone cannot fill the chip even with 8 waves per 64 rows, they
-//    are cut into segments scanned in parallel: a summary launch, the carry
-//    chain, then the full pass started from the carried-in states.  That costs a
-//    second read of x, delta, Bm and ~60% more arithmetic, so only when rows are
-//    scarce.
-Shape pick_shape(const FwdParams& p)
+// Cuts the rows into want_seg segments of whole forward tiles, at least 64 tokens each
+// (force_nseg: as many as asked for).
+Shape cut_rows(const FwdParams& p, long want_seg)
 {
-    const long nrb = (long)((p.dim + 63) / 64) * p.batch;
-    const int max_log2 = p.dstate > 8 ? 3 : (p.dstate > 4 ? 2 : (p.dstate > 2 ? 1 : 0));
     const int ntiles = (p.seqlen + kFwdTileTokens - 1) / kFwdTileTokens;
-    Shape s{0, 1, ntiles};
-    s.waves_log2 = max_log2 < 2 ? max_log2 : 2;
-    long want_seg = 1;
-    if ((nrb << max_log2) < 2048) {
-        // three blocks per CU are resident (LDS): aim at 3 x 256 blocks in all
-        s.waves_log2 = max_log2 < 2 ? max_log2 : 2;
-        want_seg = (768 + nrb - 1) / nrb;
-    }
-    if (p.force_waves_log2 >= 0) s.waves_log2 = p.force_waves_log2 < max_log2 ? p.force_waves_log2 : max_log2;
+    Shape s{1, ntiles};
     if (p.force_nseg >= 1) want_seg = p.force_nseg;
     if (want_seg > 1) {
         int st = (int)((ntiles + want_seg - 1) / want_seg);
-        if (p.force_nseg < 1 && st < 2) st = 2;               // at least 64 tokens per segment
+        if (p.force_nseg < 1 && st < 2) st = 2;
         if (st < 1) st = 1;
         s.seg_tiles = st;
         s.nseg = (ntiles + st - 1) / st;
@@ -47,35 +28,67 @@ Shape pick_shape(const FwdParams& p)
     return s;
 }
 
+// The forward kernels run one block per (32 rows, segment), six of them on a CU.  Rows that
+// cannot fill the chip are cut into segments scanned in parallel: a summary launch, the
+// carry chain, then the full pass started from the carried-in states.  That costs a second
+// read of x, delta, Bm and ~60% more arithmetic, so only when rows are scarce.  Measured on
+// MI355X (us, fp32, window 4, uncut / cut): 384 blocks: 197 tokens 26.9 / 30.5, 576 tokens
+// 62.4 / 61.6, 784 tokens 84.7 / 81.2; 192 blocks: 197 tokens 22.6 / 23.3, 576 tokens
+// 54.1 / 39.8; 768 blocks: 197 tokens 35.4 / 48.5.  Number of blocks aimed at (1 x 256 x
+// 65536): 1024: 156, 1536: 154, 2048: 149, 2560: 164; 1 x 512 x 16384: 768: 93, 1024: 88, 2048: 88.
+Shape pick_shape(const FwdParams& p)
+{
+    const long nrb = (long)((p.dim + 31) / 32) * p.batch;
+    return cut_rows(p, nrb < 384 ? (2048 + nrb - 1) / nrb : 1);
+}
+
+// The backward kernel runs one block per (64 rows, segment), two on a CU: one round of
+// 512 blocks where rows are cut.
+Shape pick_bwd_shape(const FwdParams& p)
+{
+    const long nrb = (long)((p.dim + 63) / 64) * p.batch;
+    return cut_rows(p, nrb < 256 ? 512 / nrb : 1);
+}
+
 size_t carry_floats(const FwdParams& p, int nseg)
 {
     return (size_t)nseg * p.batch * p.dim * (size_t)p.dstate;
 }
 
-// The chunk-per-lane kernel (one wave per row, 1024-token chunks) against the
-// row-per-lane kernels, measured on MI355X (us, row-per-lane / chunk-per-lane):
-//   B x D = 8 x 768,  L = 4096, bf16: 213 / 161      fp32: 217 / 180
-//   32 x 768, L = 2048, bf16: 368 / 287               16 x 768, L = 2048, fp32: 204 / 186
-//   8 x 384,  L = 4096, bf16: 132 / 83                16 x 768, L = 1024, fp32: 111 / 94
-//   2 x 768,  L = 8192, bf16: 139 / 129               fp32: 138 / 150
-//   64 x 384, L = 1024, fp32: 187 / 187 (rows not cut by the row-per-lane path)
-// It needs rows enough for a wave each (four rows per block, three blocks per CU),
-// and chunks that are mostly full.  With fp32 storage it wins where the row-per-lane
-// kernels would have to cut rows into segments; with bf16 storage always.  It leaves
-// no checkpoints for a backward call.
-bool use_chunk_mapping(const FwdParams& p, const Shape& s, const float* saved)
+// The chunk-per-lane kernel (one wave per row, 1024-token chunks, one launch) against the
+// wave-tile kernels (rows cut where that is faster), measured on MI355X (us, wave tiles /
+// chunk; fp32 with window 4, bf16 with window 8):
+//   rows x tokens      fp32           bf16
+//   192 x 1024         22.1 / 18.2    22.4 / 16.6
+//   768 x 1024         21.2 / 17.6    22.7 / 17.5
+//   6144 x 1024        58.8 / 47.5    64.7 / 42.9
+//   12288 x 1024       97.6 / 84.6    108 / 75.8
+//   24576 x 1024       138 / 181      147 / 142
+//   1536 x 2048        42.5 / 38.8    42.9 / 34.3
+//   12288 x 2048       189 / 181      200 / 145
+//   768 x 4096         45.3 / 59.0    46.1 / 53.7
+//   1536 x 4096        70.7 / 72.1    74.2 / 65.0
+//   3072 x 4096        109 / 87.9     121 / 81.9
+//   6144 x 4096        196 / 187      211 / 152
+//   3072 x 1500 (73%)  52.0 / 52.9    55.3 / 52.8
+//   6144 x 784 (77%)   48.5 / 67.3    51.8 / 69.0
+// It needs chunks that are mostly full, and rows enough for a wave each unless a row is a
+// single chunk; with fp32 storage (four rows share a staged Bm / Cm chunk, so those reads are
+// twice the row reads) it loses where the wave tiles fill the chip without cutting rows.  It leaves no
+// checkpoints for a backward call.
+bool use_chunk_mapping(const FwdParams& p, const float* saved)
 {
     if (p.force_mapping == 1) return false;
     FwdParams q = p;
     q.ckpt = nullptr; q.summary_only = 0;
     if (!fwd_chunk_supported(q)) return false;
-    if (saved && s.nseg == 1) return false;
+    if (saved) return false;
     if (p.force_mapping == 2) return true;
     const long rows = (long)p.batch * p.dim;
     const long chunk = 1024, nchunks = (p.seqlen + chunk - 1) / chunk;
     if (p.seqlen * 5 < nchunks * chunk * 4) return false;             // chunks less than 80% full
-    if (p.dtype != 0) return rows >= 1536;
-    return rows >= 3072 && s.nseg > 1;
+    if (p.dtype != 0) return nchunks == 1 || rows >= 1536;
+    return rows <= 16384 && (nchunks == 1 || rows >= 3072 || (nchunks == 2 && rows >= 1536));
 }
 
 }  // namespace
@@ -91,7 +104,7 @@ size_t fwd_workspace_bytes(const FwdParams& p)
 size_t saved_state_bytes(const FwdParams& p)
 {
     if (p.batch == 0 || p.dim == 0 || p.seqlen == 0) return 0;
-    if (pick_shape(p).nseg > 1) return 0;
+    if (pick_bwd_shape(p).nseg > 1) return 0;
     const size_t ntiles16 = (p.seqlen + kTileTokens - 1) / kTileTokens;
     return ntiles16 * p.batch * p.dim * (size_t)p.dstate * sizeof(float);
 }
@@ -99,13 +112,14 @@ size_t saved_state_bytes(const FwdParams& p)
 hipError_t launch_fwd(FwdParams p, void* workspace, float* saved, hipStream_t stream)
 {
     if (p.batch == 0 || p.dim == 0 || p.seqlen == 0) return hipSuccess;
-    const Shape s = pick_shape(p);
-    if (use_chunk_mapping(p, s, saved)) return launch_fwd_chunk(p, stream);
-    p.ckpt = (saved && s.nseg == 1) ? saved : nullptr;
+    // (a pass that leaves checkpoints takes its rows whole: its callers have rows enough)
+    const Shape s = saved ? Shape{1, (p.seqlen + kFwdTileTokens - 1) / kFwdTileTokens} : pick_shape(p);
+    if (use_chunk_mapping(p, saved)) return launch_fwd_chunk(p, stream);
+    p.ckpt = saved;
     p.cum = nullptr;
     auto launch = [&](const FwdParams& q) {
-        return q.dtype == 0 ? launch_fwd_rowlane_f32(q, s.waves_log2, stream)
-                            : launch_fwd_rowlane_bf16(q, s.waves_log2, stream);
+        return q.dtype == 0 ? launch_fwd_wave_f32(q, stream)
+                            : launch_fwd_wave_bf16(q, stream);
     };
     p.nseg = s.nseg;
     p.seg_tiles = s.seg_tiles;
@@ -170,19 +184,18 @@ hipError_t launch_fwd_generic(FwdParams p, void* workspace, hipStream_t stream)
     p2.h0 = nullptr; p2.hT = nullptr; p2.carry = nullptr; p2.dsum = nullptr;
     p2.ckpt = nullptr; p2.cum = nullptr; p2.summary_only = 0; p2.seg_tiles = 0;
     // segments of whole windows, at least 64 steps each, enough of them to fill the chip
-    const long nrb = (long)((p.dim + 63) / 64) * p.batch;
+    const long nrb = (long)((p.dim + 31) / 32) * p.batch;
     const long M = p.window, L = p.seqlen;
     const long nw = (L + M - 1) / M;
-    long want_seg = nrb < 768 ? (768 + nrb - 1) / nrb : 1;
+    long want_seg = nrb < 1536 ? (1536 + nrb - 1) / nrb : 1;
     if (p.force_nseg >= 1) want_seg = p.force_nseg;
     long wps = (nw + want_seg - 1) / want_seg;
     if (p.force_nseg < 1 && wps * M < 64) wps = (64 + M - 1) / M;
     if (wps < 1) wps = 1;
     p2.seg_tokens = (int)(wps * M);
     p2.nseg = (int)((L + p2.seg_tokens - 1) / p2.seg_tokens);
-    const int wl = pick_shape(p).waves_log2;
-    return p2.dtype == 0 ? launch_fwd_rowlane_f32(p2, wl, stream)
-                         : launch_fwd_rowlane_bf16(p2, wl, stream);
+    return p2.dtype == 0 ? launch_fwd_wave_f32(p2, stream)
+                         : launch_fwd_wave_bf16(p2, stream);
 }
 
 // ---- backward ----------------------------------------------------------------
@@ -206,21 +219,7 @@ struct BwdLayout {
 BwdLayout bwd_layout(const FwdParams& f)
 {
     BwdLayout l;
-    l.shape = pick_shape(f);
-    if (l.shape.nseg > 1 && f.force_nseg < 1) {
-        // the backward kernel runs two blocks per CU: one round of 512 blocks (measured:
-        // 4096-token shape 5 segments 841 us, 8: 878, 16: 838; whole-slide shape 128
-        // segments 515 us, 192: 558, 256: 538)
-        const long nrb = (long)((f.dim + 63) / 64) * f.batch;
-        const long ntiles = (f.seqlen + kFwdTileTokens - 1) / kFwdTileTokens;
-        long want = 512 / nrb;
-        if (want < 1) want = 1;
-        long st = (ntiles + want - 1) / want;
-        if (st < 2) st = 2;
-        if (st > ntiles) st = ntiles;
-        l.shape.seg_tiles = (int)st;
-        l.shape.nseg = (int)((ntiles + st - 1) / st);
-    }
+    l.shape = pick_bwd_shape(f);
     const bool gamma = needs_gamma_checkpoints(f);
     if (gamma && l.shape.nseg > 1) {
         // segments must start at window starts: whole windows per segment
@@ -295,7 +294,7 @@ hipError_t launch_bwd(const FwdParams& f, BwdParams p, void* dBm, void* dCm, voi
         p.ckpt = saved;
         p.cum = nullptr;
         p.carry = nullptr;
-        e = f.dtype == 0 ? launch_bwd_f32(p, stream) : launch_bwd_bf16(p, stream);
+        e = f.dtype == 0 ? launch_bwd_wave_f32(p, stream) : launch_bwd_wave_bf16(p, stream);
         return e != hipSuccess ? e : finish();
     }
 
@@ -314,21 +313,21 @@ hipError_t launch_bwd(const FwdParams& f, BwdParams p, void* dBm, void* dCm, voi
     q.dsum = s.nseg > 1 ? ws + l.dsum : nullptr;
     q.psi = s.nseg > 1 ? ws + l.psi : nullptr;
     q.dout = p.dout;
-    e = q.dtype == 0 ? launch_fwd_rowlane_f32(q, s.waves_log2, stream)
-                     : launch_fwd_rowlane_bf16(q, s.waves_log2, stream);
+    e = q.dtype == 0 ? launch_fwd_wave_f32(q, stream)
+                     : launch_fwd_wave_bf16(q, stream);
     if (e != hipSuccess) return e;
     if (s.nseg > 1) {
         if ((e = launch_carry_chain(q, stream)) != hipSuccess) return e;
         if ((e = launch_carry_chain_reverse(q, q.psi, dhT, stream)) != hipSuccess) return e;
     }
 
-    e = f.dtype == 0 ? launch_bwd_f32(p, stream) : launch_bwd_bf16(p, stream);
+    e = f.dtype == 0 ? launch_bwd_wave_f32(p, stream) : launch_bwd_wave_bf16(p, stream);
     return e != hipSuccess ? e : finish();
 }
 
 // ---- a scan order through reordered copies --------------------------------------
 //
-// The row-per-lane kernels can gather the tokens of a scan order themselves, which
+// The wave-tile kernels can gather the tokens of a scan order themselves, which
 // needs no scratch; given scratch, the row tensors are copied into scanned order
 // first, the stored-order path runs on the copies, and its results are copied back.
 // The forward pass leaves z where it is: the scan returns the ungated sum in fp32 and
@@ -366,7 +365,7 @@ hipError_t launch_bwd(const FwdParams& f, BwdParams p, void* dBm, void* dCm, voi
 // (How fast a gather of few long rows is goes up and down with how their blocks fill the
 // chip: fp32 at 8 x 384 and 4 x 384 is on the wrong side of the line.)
 // The copies ask for an fp32 result, which the chunk-per-lane kernel gives for bf16 only
-// with window 1: bf16 images of 4096 tokens run the row-per-lane kernels here (8 x 768:
+// with window 1: bf16 images of 4096 tokens run the wave-tile kernels here (8 x 768:
 // 2023 / 379).
 namespace {
 

@@ -13,7 +13,7 @@
 // describes for its own kernel (Sec. 3.4: a tile of tokens per thread, partial
 // results exchanged between threads, a second traversal), with the exchange done
 // by DPP inside a wave and the state that leaves a chunk carried to the next
-// through one LDS word per state.  Against the row-per-lane kernel it reads every tensor once
+// through one LDS word per state.  Against the wave-tile kernel it reads every tensor once
 // and needs no summary pass for long rows, at the price of the second traversal
 // and the prefix scan (about 2 more issue slots per state update) and of Bm / Cm
 // reads per lane instead of per wave; it wins where rows are long and many
@@ -404,7 +404,7 @@ hipError_t launch_chunk_t(const FwdParams& p, hipStream_t s)
 bool fwd_chunk_supported(const FwdParams& p)
 {
     // stored order (either direction), rows that allow quad accesses, nothing that
-    // only the row-per-lane kernels produce (checkpoints, first-pass partials)
+    // only the wave-tile kernels produce (checkpoints, first-pass partials)
     if (!window_supported(p.window) || p.order.kind != 0) return false;
     if (p.ckpt || p.summary_only || p.generic_window) return false;
     if (p.y_is_f32 && p.dtype != 0 && p.window != 1) return false;

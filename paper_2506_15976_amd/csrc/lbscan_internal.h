@@ -27,9 +27,8 @@ struct FwdParams {
     const float* yprev;   // nullable, fp32 (B,D,L): added to y before the gate
     void* y;              // element type = dtype, or fp32 when y_is_f32
     int y_is_f32;         // write y as fp32 whatever dtype says (first pass of the two-pass scan)
-    int force_waves_log2; // >= 0: override the state-split heuristic (tests, tuning)
     int force_nseg;       // >= 1: override the number of segments a row is cut into
-    int force_mapping;    // 0: heuristic; 1: row-per-lane kernels; 2: chunk-per-lane kernel where it applies
+    int force_mapping;    // 0: heuristic; 1: wave-tile kernels; 2: chunk-per-lane kernel where it applies
     // Long rows are cut into nseg segments of seg_tiles forward tiles (kFwdTileTokens tokens each), one
     // block per (64 rows, segment).  carry: (nseg, N, B*D) states entering each
     // segment (read by the full pass; written by the summary pass as the states a
@@ -49,7 +48,7 @@ struct FwdParams {
     const void* dout;
     float* psi;
     // summary pass for window lengths that 16 is not a multiple of (nullable):
-    // gck (ntiles16, N, B*D), see lbscan_fwd_rowlane.inc MODE 2
+    // gck (ntiles16, N, B*D), see lbscan_fwd_wave.inc MODE 2
     float* gck;
     // forward state entering the row (nullable: zeros) and leaving it (nullable), (B*D, N)
     const float* h0;
@@ -125,10 +124,9 @@ constexpr int kFwdTileTokens = LBSCAN_FWD_TILE;   // tokens per tile of the forw
 // Window lengths with a compiled kernel.
 inline bool window_supported(int M) { return M == 1 || M == 2 || M == 4 || M == 8 || M == 16; }
 
-// Row-per-lane forward kernel family (lbscan_fwd_rowlane.inc), one translation
-// unit per storage type.  waves_log2: log2 of the waves the states are split over.
-hipError_t launch_fwd_rowlane_f32(const FwdParams& p, int waves_log2, hipStream_t stream);
-hipError_t launch_fwd_rowlane_bf16(const FwdParams& p, int waves_log2, hipStream_t stream);
+// Forward kernels (lbscan_fwd_wave.inc), one translation unit per storage type.
+hipError_t launch_fwd_wave_f32(const FwdParams& p, hipStream_t stream);
+hipError_t launch_fwd_wave_bf16(const FwdParams& p, hipStream_t stream);
 
 // Chunk-per-lane forward kernel (lbscan_fwd_chunk.hip): one wave per row, 16 tokens
 // per lane, no workspace.  fwd_chunk_supported: p is within what it implements.
@@ -151,8 +149,8 @@ size_t fwd_generic_workspace_bytes(const FwdParams& p);
 size_t saved_state_bytes(const FwdParams& p);
 
 // Backward kernels (lbscan_bwd_wave.inc), one translation unit per storage type.
-hipError_t launch_bwd_f32(const BwdParams& p, hipStream_t stream);
-hipError_t launch_bwd_bf16(const BwdParams& p, hipStream_t stream);
+hipError_t launch_bwd_wave_f32(const BwdParams& p, hipStream_t stream);
+hipError_t launch_bwd_wave_bf16(const BwdParams& p, hipStream_t stream);
 // dBm, dCm (storage type) = the partial sums of BwdParams::dBpart added over the nbx
 // blocks of 64 channels; bnl = B * N * L.
 hipError_t launch_reduce_f32(const float* part, void* dB, void* dC, long bnl, int nbx, hipStream_t stream);

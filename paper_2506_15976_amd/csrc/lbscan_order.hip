@@ -2,7 +2,7 @@
 // (TokenOrder): every row of up to kReorderMany (rows, L) tensors is permuted the same
 // way in one launch.
 //
-// Why copies: the row-per-lane kernels can gather token by token, but a wave's 64 lanes
+// Why copies: the wave-tile kernels can gather token by token, but a wave's 64 lanes
 // then touch 64 sectors with every 4-byte load and the same lines are fetched again by
 // every tile of the row.  Copying first moves each tensor once more, in whole lines.
 // (The two ways are compared beside launch_fwd_reordered in lbscan_dispatch.hip.)

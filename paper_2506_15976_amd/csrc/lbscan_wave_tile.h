@@ -6,6 +6,8 @@
 //   staging:  lane = 4 * row + quad     four tokens of one row, as memory holds them
 //   scan:     lane = 16 * group + row   a quarter of the row's states, all its tokens
 #pragma once
+#include <type_traits>
+
 #include "lbscan_device.h"
 
 namespace lbscan {

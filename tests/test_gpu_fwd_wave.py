@@ -1,0 +1,61 @@
+"""Forward kernel at the edges of its tiles (8 rows a wave, 32 a block, 32 tokens), and the
+calls that its rule hands to the chunk-per-lane kernel; fp64 oracle as the reference."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(lb, oracle, s, dtype, window, reverse, h0=None):
+    import numpy as np
+    import torch
+    from gpu_util import assert_close, flip_time, fwd_inputs, to_device, to_numpy
+    dev = to_device(s, dtype)
+    state = None if h0 is None else torch.from_numpy(h0).to("cuda:0")
+    got, hT = lb.lbscan_fwd(**fwd_inputs(dev), window=window, reverse=reverse, h0=state, return_state=True)
+    torch.cuda.synchronize()
+    src = flip_time(s) if reverse else s
+    ref, ref_state = oracle.fwd(**fwd_inputs(src), window=window, h0=h0, return_state=True)
+    what = f"window {window} reverse {reverse}"
+    assert_close(to_numpy(got), np.ascontiguousarray(ref[..., ::-1]) if reverse else ref, dtype, what)
+    assert_close(to_numpy(hT), ref_state, "fp32", what + " state")
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("shape", [
+    (1, 1, 16, 1), (2, 9, 9, 31), (1, 33, 8, 32), (3, 40, 16, 33), (1, 24, 1, 65), (2, 65, 5, 3), (1, 31, 16, 100),
+])
+def test_outputs_at_the_edges_of_a_tile(oracle, shape, dtype):
+    import numpy as np
+    import paper_2506_15976_amd as lb
+    from paper_2506_15976_amd.inputs import make_inputs
+    B, D, N, L = shape
+    s = make_inputs(B, D, N, L, seed=9300 + D + L, dtype=dtype, random_A=True)
+    h0 = np.random.default_rng(D).standard_normal((B, D, N)).astype(np.float32)
+    for window, reverse in ((1, True), (2, False), (4, True), (8, False), (16, True), (5, False), (24, True)):
+        _check(lb, oracle, s, dtype, window, reverse, h0)
+    lb.lbscan_set_option("segments", 3)
+    try:
+        _check(lb, oracle, s, dtype, 4, False, h0)
+        _check(lb, oracle, s, dtype, 8, True, h0)
+    finally:
+        lb.lbscan_set_option("segments", 0)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("shape", [(1, 5, 16, 1024), (2, 3, 7, 820), (1, 200, 16, 1000)])
+def test_rows_of_one_chunk(oracle, shape, dtype):
+    """Few rows of 820 to 1024 tokens: one launch of the chunk-per-lane kernel; the wave tiles
+    (option "mapping") give the same within the same bounds."""
+    import numpy as np
+    import paper_2506_15976_amd as lb
+    from paper_2506_15976_amd.inputs import make_inputs
+    B, D, N, L = shape
+    s = make_inputs(B, D, N, L, seed=9400 + D + L, dtype=dtype, random_A=True)
+    h0 = np.random.default_rng(D).standard_normal((B, D, N)).astype(np.float32)
+    for mapping in (0, 1):
+        lb.lbscan_set_option("mapping", mapping)
+        try:
+            for window, reverse in ((4, False), (16, True)):
+                _check(lb, oracle, s, dtype, window, reverse, h0)
+        finally:
+            lb.lbscan_set_option("mapping", 0)
