@@ -6,54 +6,88 @@
 // recurrence of Eq. 1 (Sec. 3.1) is linear, so the state entering segment s+1
 // is  c_{s+1} = exp(A S_s) c_s + e_s  with c_0 = 0: the product of the
 // segment's abar factors is exp(A * sum of dt).  A step of that chain is the
-// affine map c -> P c + e, and affine maps compose associatively, so a group of
-// G lanes (G a power of two, at most a wave) takes G consecutive segments of one
-// (row, n) pair, forms the running composition with a shuffle scan, and each
-// lane overwrites its e_s by the state c_s entering its segment.  Chains longer
-// than G are walked in chunks of G with the carried state passed along.  The
-// backward pass's right-to-left recurrence psi_t = abar_t (e_t + psi_{t+1})
-// chains the same way with the segments walked from the last to the first.
+// affine map c -> P c + e, and affine maps compose associatively.  The summaries lie as
+// (segment, n, row): a lane takes one row, so that a wave reads 256 contiguous bytes, and
+// the segments of a (64 rows, n) block are shared out to its waves, kPerWave consecutive
+// ones each, all loaded at once.  The waves' compositions meet in LDS, every wave folds
+// those before its own, and walks its segments again from the state that enters them,
+// overwriting e_s by c_s.  Chains longer than a block are walked block by block with the
+// carried state passed along.  The backward pass's right-to-left recurrence
+// psi_t = abar_t (e_t + psi_{t+1}) chains the same way with the segments walked from the
+// last to the first, in the same launch (blockIdx.y).
+// Bound by the latency of two trips to memory.  MI355X, with a lane per segment before (every lane
+// touched a line of its own) against now: forward call, 1 x 256 x 65536 (234 segments) 152 -> 146 us, 1 x 256 x
+// 8192 35 -> 31; training step, which chains twice more, 563 -> 543.
 #include "lbscan_device.h"
 #include "lbscan_internal.h"
 
 namespace lbscan {
 namespace {
 
-__global__ void __launch_bounds__(256)
-carry_chain_kernel(float* __restrict__ carry, const float* __restrict__ dsum,
-                   const float* __restrict__ A, const float* __restrict__ init,
-                   int rows, int D, int N, int nseg, int nsum, int reverse, int G)
+constexpr int kPerWave = 16;          // segments of a wave
+constexpr int kChainWaves = 16;       // waves of a block, at most
+
+// One chain: buf (nseg, N, rows) holds e_s and receives c_s; segments from the nsum-th of
+// the walk on hold the identity map (their summary was not computed: nothing follows them).
+struct Chain {
+    float* buf;
+    const float* init;                // (rows, N): the state entering the walk, nullable: zeros
+    int nsum, reverse;
+};
+struct Chains { Chain c[2]; };
+
+__global__ void __launch_bounds__(64 * kChainWaves)
+carry_chain_kernel(const Chains chains, const float* __restrict__ dsum, const float* __restrict__ A,
+                   int rows, int D, int N, int nseg)
 {
-    const long npairs = (long)rows * N;
-    const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    const int g = (int)(t % G);                       // segment within the chunk
-    const long pair = t / G;                          // (row, n)
-    const bool valid = pair < npairs;
-    const long i = valid ? pair : npairs - 1;         // clamped: every lane shuffles
-    const int row = (int)(i / N), n = (int)(i % N);
-    const float a2 = A[(long)(row % D) * N + n] * kLog2e;
-    float cin = init ? init[i] : 0.0f;                // state entering the chunk
-    for (int base = 0; base < nseg; base += G) {
-        const int ss = base + g;
-        const bool on = ss < nseg;
-        const int s = reverse ? nseg - 1 - (on ? ss : 0) : (on ? ss : 0);
-        const long k = ((long)s * N + n) * rows + row;        // (segment, n, row)
-        // lanes past the end of the chain, and segments whose summary was not
-        // computed (ss >= nsum: the last one, which nothing follows), hold the
-        // identity map
-        const bool have = on && ss < nsum;
-        float e = have ? carry[k] : 0.0f;
-        float P = have ? fast_exp2(a2 * dsum[(long)s * rows + row]) : 1.0f;
-        // inclusive scan: lane g ends with the composition of segments base..base+g
-        for (int d = 1; d < G; d <<= 1) {
-            const float Pp = __shfl_up(P, d, G), ep = __shfl_up(e, d, G);
-            if (g >= d) { e = fmaf(P, ep, e); P *= Pp; }
+    __shared__ float sP[kChainWaves][64], sE[kChainWaves][64];
+    const Chain ch = chains.c[blockIdx.y];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const int n = blockIdx.x % N;
+    const long r0 = (long)(blockIdx.x / N) * 64 + lane;
+    const bool valid = r0 < rows;
+    const long row = valid ? r0 : rows - 1;
+    const float a2 = A[(row % D) * N + n] * kLog2e;
+    float cin = ch.init ? ch.init[row * N + n] : 0.0f;          // state entering the block's segments
+    for (int base = 0; base < nseg; base += nw * kPerWave) {
+        const int first = base + wv * kPerWave;
+        float P[kPerWave], e[kPerWave];
+#pragma unroll
+        for (int k = 0; k < kPerWave; ++k) {
+            const int ss = first + k;
+            const bool have = ss < ch.nsum;
+            const long s = have ? (ch.reverse ? nseg - 1 - ss : ss) : 0;
+            e[k] = ch.buf[(s * N + n) * rows + row];
+            P[k] = dsum[s * rows + row];
         }
-        const float Pm = __shfl_up(P, 1, G), em = __shfl_up(e, 1, G);
-        const float c = g == 0 ? cin : fmaf(Pm, cin, em);
-        if (on && valid) carry[k] = c;
-        const float Pl = __shfl(P, G - 1, G), el = __shfl(e, G - 1, G);
-        cin = fmaf(Pl, cin, el);
+        float Pw = 1.0f, ew = 0.0f;
+#pragma unroll
+        for (int k = 0; k < kPerWave; ++k) {
+            const bool have = first + k < ch.nsum;
+            P[k] = have ? fast_exp2(a2 * P[k]) : 1.0f;
+            e[k] = have ? e[k] : 0.0f;
+            ew = fmaf(P[k], ew, e[k]);
+            Pw *= P[k];
+        }
+        sP[wv][lane] = Pw;
+        sE[wv][lane] = ew;
+        __syncthreads();
+        float c = cin;
+        for (int w = 0; w < nw; ++w) {
+            if (w == wv) {
+                float v = c;
+#pragma unroll
+                for (int k = 0; k < kPerWave; ++k) {
+                    const int ss = first + k;
+                    const long s = ch.reverse ? nseg - 1 - ss : ss;
+                    if (ss < nseg && valid) ch.buf[(s * N + n) * rows + row] = v;
+                    v = fmaf(P[k], v, e[k]);
+                }
+            }
+            c = fmaf(sP[w][lane], c, sE[w][lane]);
+        }
+        cin = c;
+        __syncthreads();                  // before the compositions are overwritten
     }
 }
 
@@ -87,13 +121,16 @@ copy_kernel(float* __restrict__ dst, const float* __restrict__ src, long n)
     if (i < n) dst[i] = src[i];
 }
 
-// lanes per (row, n) pair: the smallest power of two that covers the chain, one
-// wave at most
-int chain_group(int nseg)
+hipError_t launch_chains(const FwdParams& p, const Chains& chains, int count, hipStream_t stream)
 {
-    int G = 1;
-    while (G < nseg && G < 64) G <<= 1;
-    return G;
+    const long rows = (long)p.batch * p.dim;
+    const long blocks = (rows + 63) / 64 * p.dstate;
+    if (blocks == 0) return hipSuccess;
+    if (blocks > 0x7fffffffL) return hipErrorInvalidConfiguration;
+    const int waves = (p.nseg + kPerWave - 1) / kPerWave;
+    hipLaunchKernelGGL(carry_chain_kernel, dim3((unsigned)blocks, count), dim3(64 * (waves < kChainWaves ? waves : kChainWaves)),
+                       0, stream, chains, p.dsum, p.A, (int)rows, p.dim, p.dstate, p.nseg);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -128,28 +165,14 @@ hipError_t launch_copy(float* dst, const float* src, long n, hipStream_t stream)
 
 hipError_t launch_carry_chain(const FwdParams& p, hipStream_t stream)
 {
-    const int rows = p.batch * p.dim;
-    const long n = (long)rows * p.dstate;
-    if (n == 0) return hipSuccess;
-    const int G = chain_group(p.nseg);
-    const unsigned blocks = (unsigned)((n * G + 255) / 256);
-    hipLaunchKernelGGL(carry_chain_kernel, dim3(blocks), dim3(256), 0, stream,
-                       p.carry, p.dsum, p.A, p.h0, rows, p.dim, p.dstate, p.nseg,
-                       p.ckpt ? p.nseg : p.nseg - 1, 0, G);
-    return hipGetLastError();
+    const Chains c{{{p.carry, p.h0, p.ckpt ? p.nseg : p.nseg - 1, 0}, {}}};
+    return launch_chains(p, c, 1, stream);
 }
 
-hipError_t launch_carry_chain_reverse(const FwdParams& p, float* buf, const float* init,
-                                      hipStream_t stream)
+hipError_t launch_carry_chains(const FwdParams& p, float* psi, const float* psi_init, hipStream_t stream)
 {
-    const int rows = p.batch * p.dim;
-    const long n = (long)rows * p.dstate;
-    if (n == 0) return hipSuccess;
-    const int G = chain_group(p.nseg);
-    const unsigned blocks = (unsigned)((n * G + 255) / 256);
-    hipLaunchKernelGGL(carry_chain_kernel, dim3(blocks), dim3(256), 0, stream,
-                       buf, p.dsum, p.A, init, rows, p.dim, p.dstate, p.nseg, p.nseg, 1, G);
-    return hipGetLastError();
+    const Chains c{{{p.carry, p.h0, p.ckpt ? p.nseg : p.nseg - 1, 0}, {psi, psi_init, p.nseg, 1}}};
+    return launch_chains(p, c, 2, stream);
 }
 
 }  // namespace lbscan

@@ -9,7 +9,14 @@ namespace {
 struct Shape { int nseg, seg_tiles; };
 
 // Up to this many segments the full forward pass folds the carry chain itself.
+// (Measured, up to 16 / up to 4, us: 4 x 384 x 576 22.6 / 25.1, 16 x 384 x 576 41.9 / 43.9,
+// 8 x 384 x 1500 51.8 / 57.1.)
 constexpr int kFoldChainSegments = 16;
+
+// Blocks that the summary pass of a backward call is cut for (blocks of 32 rows, five
+// to a CU).  Training step, one summary segment to a segment / 2048 / 4096 blocks: 8 x 768 x
+// 4096 bf16 792 / 780 / 816 us, 1 x 256 x 65536 fp32 543 / 546 / 561 us.
+constexpr long kSummaryBlocks = 2048;
 
 // Cuts the rows into want_seg segments of whole forward tiles, at least 64 tokens each
 // (force_nseg: as many as asked for).
@@ -210,7 +217,8 @@ bool needs_gamma_checkpoints(const FwdParams& f)
 }
 
 struct BwdLayout {
-    Shape shape;            // segments in forward tiles (32 tokens)
+    Shape shape;            // segments of the backward kernel in forward tiles (32 tokens)
+    Shape sum;              // and of the summary pass: a whole number of them to one of those
     size_t ntiles16;        // backward tiles (16 tokens) per row
     size_t ckpt, cum, gck, carry, dsum, psi, part;   // float offsets into the workspace
     size_t total;           // floats
@@ -221,16 +229,27 @@ BwdLayout bwd_layout(const FwdParams& f)
     BwdLayout l;
     l.shape = pick_bwd_shape(f);
     const bool gamma = needs_gamma_checkpoints(f);
-    if (gamma && l.shape.nseg > 1) {
-        // segments must start at window starts: whole windows per segment
-        long g = f.window, r = kFwdTileTokens;
-        while (r) { const long t = g % r; g = r; r = t; }          // gcd(window, 32)
-        const long unit = f.window / g;                            // forward tiles per window period
+    l.sum = l.shape;
+    if (l.shape.nseg > 1) {
         const long ntiles = (f.seqlen + kFwdTileTokens - 1) / kFwdTileTokens;
-        long st = ((l.shape.seg_tiles + unit - 1) / unit) * unit;
-        if (st >= ntiles) st = ntiles;
-        l.shape.seg_tiles = (int)st;
-        l.shape.nseg = (int)((ntiles + st - 1) / st);
+        const long nrb = (long)((f.dim + 31) / 32) * f.batch;
+        long fine = f.force_nseg >= 1 ? 1 : kSummaryBlocks / (nrb * l.shape.nseg);
+        if (fine < 1) fine = 1;
+        if (fine > l.shape.seg_tiles / 2) fine = l.shape.seg_tiles / 2 > 0 ? l.shape.seg_tiles / 2 : 1;
+        long st = (l.shape.seg_tiles + fine - 1) / fine;
+        if (gamma) {
+            // segments must start at window starts: whole windows per segment
+            long g = f.window, r = kFwdTileTokens;
+            while (r) { const long t = g % r; g = r; r = t; }      // gcd(window, 32)
+            const long unit = f.window / g;                        // forward tiles per window period
+            st = (st + unit - 1) / unit * unit;
+        }
+        if (st > ntiles) st = ntiles;
+        fine = (l.shape.seg_tiles + st - 1) / st;
+        l.sum.seg_tiles = (int)st;
+        l.sum.nseg = (int)((ntiles + st - 1) / st);
+        l.shape.seg_tiles = (int)(st * fine < ntiles ? st * fine : ntiles);
+        l.shape.nseg = (int)((ntiles + st * fine - 1) / (st * fine));
     }
     const size_t rows = (size_t)f.batch * f.dim, N = f.dstate;
     l.ntiles16 = (f.seqlen + kTileTokens - 1) / kTileTokens;
@@ -238,7 +257,7 @@ BwdLayout bwd_layout(const FwdParams& f)
     l.ckpt = o; o += l.ntiles16 * rows * N;
     l.cum = o;  o += l.ntiles16 * rows;
     l.gck = o;  if (gamma) o += l.ntiles16 * rows * N;
-    const size_t ns = l.shape.nseg > 1 ? l.shape.nseg : 0;
+    const size_t ns = l.sum.nseg > 1 ? l.sum.nseg : 0;
     l.carry = o; o += ns * rows * N;
     l.dsum = o;  o += ns * rows;
     l.psi = o;   o += ns * rows * N;
@@ -272,10 +291,12 @@ hipError_t launch_bwd(const FwdParams& f, BwdParams p, void* dBm, void* dCm, voi
     p.gck = gamma ? ws + l.gck : nullptr;
     p.nseg = s.nseg;
     p.seg_tiles = s.seg_tiles * (kFwdTileTokens / kTileTokens);
+    p.nsum = l.sum.nseg;
+    p.sum_tiles = l.sum.seg_tiles * (kFwdTileTokens / kTileTokens);
     // uncut rows: the entering state and the gradient arriving at the leaving state
     // take the places of the chained values
-    p.carry = s.nseg > 1 ? ws + l.carry : f.h0;
-    p.psi_in = s.nseg > 1 ? ws + l.psi : dhT;
+    p.carry = p.nsum > 1 ? ws + l.carry : f.h0;
+    p.psi_in = p.nsum > 1 ? ws + l.psi : dhT;
 
     hipError_t e;
     const ZeroMany z{{p.dA, p.dDskip, p.dbias, nullptr, nullptr},
@@ -289,7 +310,7 @@ hipError_t launch_bwd(const FwdParams& f, BwdParams p, void* dBm, void* dCm, voi
                             : launch_reduce_bf16(p.dBpart, dBm, dCm, bnl, nbx, stream);
     };
 
-    if (saved && s.nseg == 1 && !gamma) {
+    if (saved && p.nsum == 1 && !gamma) {
         // the forward call left the checkpoints (entering state included): no summary pass
         p.ckpt = saved;
         p.cum = nullptr;
@@ -303,22 +324,21 @@ hipError_t launch_bwd(const FwdParams& f, BwdParams p, void* dBm, void* dCm, voi
     // forward and of the right-to-left recurrence; for windows that straddle tile
     // starts also the checkpoints of the adjoint of the local backward state
     FwdParams q = f;
-    q.nseg = s.nseg;
-    q.seg_tiles = s.seg_tiles;
+    q.nseg = l.sum.nseg;
+    q.seg_tiles = l.sum.seg_tiles;
     q.summary_only = 1;
     q.ckpt = ws + l.ckpt;
     q.cum = ws + l.cum;
     q.gck = gamma ? ws + l.gck : nullptr;
-    q.carry = s.nseg > 1 ? ws + l.carry : nullptr;
-    q.dsum = s.nseg > 1 ? ws + l.dsum : nullptr;
-    q.psi = s.nseg > 1 ? ws + l.psi : nullptr;
+    q.carry = q.nseg > 1 ? ws + l.carry : nullptr;
+    q.dsum = q.nseg > 1 ? ws + l.dsum : nullptr;
+    q.psi = q.nseg > 1 ? ws + l.psi : nullptr;
     q.dout = p.dout;
     e = q.dtype == 0 ? launch_fwd_wave_f32(q, stream)
                      : launch_fwd_wave_bf16(q, stream);
     if (e != hipSuccess) return e;
-    if (s.nseg > 1) {
-        if ((e = launch_carry_chain(q, stream)) != hipSuccess) return e;
-        if ((e = launch_carry_chain_reverse(q, q.psi, dhT, stream)) != hipSuccess) return e;
+    if (q.nseg > 1) {
+        if ((e = launch_carry_chains(q, q.psi, dhT, stream)) != hipSuccess) return e;
     }
 
     e = f.dtype == 0 ? launch_bwd_wave_f32(p, stream) : launch_bwd_wave_bf16(p, stream);

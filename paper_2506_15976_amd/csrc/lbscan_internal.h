@@ -86,12 +86,13 @@ struct BwdParams {
     float* dDskip;        // (D) zeroed, nullable
     float* dbias;         // (D) zeroed, nullable
     const float* ckpt;    // (ntiles, N, B*D): f at the first step of every tile, counted
-                          // from the start of the tile's segment
-    // rows cut into nseg segments of seg_tiles backward tiles (16 tokens each):
-    int nseg, seg_tiles;
-    const float* cum;     // (ntiles, B*D): time-step sum from the segment start to the tile
-    const float* carry;   // (nseg, B*D, N): forward state entering each segment (null: zeros)
-    const float* psi_in;  // (nseg, B*D, N): psi entering each segment from the right
+                          // from the start of the tile's summary segment
+    // rows cut into nseg segments of seg_tiles backward tiles (16 tokens each), a segment
+    // into whole summary segments of sum_tiles (nsum of them in a row):
+    int nseg, seg_tiles, nsum, sum_tiles;
+    const float* cum;     // (ntiles, B*D): time-step sum from the summary segment's start to the tile
+    const float* carry;   // (nsum, N, B*D): forward state entering each summary segment (null: zeros)
+    const float* psi_in;  // (nsum, N, B*D): psi entering each summary segment from the right
     const float* gck;     // (ntiles, N, B*D), nullable: abar_{t-1} gamma_{t-1} entering each tile
                           // (windows that straddle tile starts)
     float* dh0;           // (B*D, N), nullable: psi leaving the row on the left
@@ -206,10 +207,9 @@ hipError_t launch_conv1d_bwd(const ConvParams& p, hipStream_t stream);
 // (lbscan_carry.hip): carry[s] <- exclusive scan over s of (exp(A*dsum), carry),
 // started from p.h0 (zeros when null).
 hipError_t launch_carry_chain(const FwdParams& p, hipStream_t stream);
-// The same chain over `buf` (nseg, B*D, N) walking the segments right to left,
-// started from init (B*D, N), zeros when null.
-hipError_t launch_carry_chain_reverse(const FwdParams& p, float* buf, const float* init,
-                                      hipStream_t stream);
+// The same and, in the same launch, the chain over psi (nseg, N, B*D) walking the segments
+// right to left, started from psi_init (B*D, N), zeros when null.
+hipError_t launch_carry_chains(const FwdParams& p, float* psi, const float* psi_init, hipStream_t stream);
 // dst[i] = src[i] (zeros when src is null), n floats.
 hipError_t launch_copy(float* dst, const float* src, long n, hipStream_t stream);
 

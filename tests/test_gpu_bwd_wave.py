@@ -30,3 +30,32 @@ def test_gradients_at_the_edges_of_a_tile(oracle, shape, dtype):
             # parameter gradients of a single row are sums of a few terms: the elementwise
             # bounds of the other parity tests hold for them as they do for long rows
             assert_close(to_numpy(got[k]), r, dtype, f"{k} window {window} reverse {reverse}")
+
+
+@pytest.mark.parametrize("tokens, segments", [(97, 2), (1100, 17), (9000, 282)])
+def test_carry_chains_of_any_length(oracle, tokens, segments):
+    """Chains folded in the pass, of more segments than a wave takes, and of more than a block
+    takes (256): forward states and the right-to-left recurrence."""
+    import numpy as np
+    import torch
+    import paper_2506_15976_amd as lb
+    from gpu_util import assert_close, fwd_inputs, to_device, to_numpy
+    from paper_2506_15976_amd.inputs import make_inputs
+    s = make_inputs(1, 35, 5, tokens, seed=9500 + tokens, with_dout=True)
+    dev = to_device(s, "fp32")
+    rng = np.random.default_rng(tokens)
+    h0, dhT = (rng.standard_normal((1, 35, 5)).astype(np.float32) for _ in range(2))
+    lb.lbscan_set_option("segments", segments)
+    try:
+        out, hT = lb.lbscan_fwd(**fwd_inputs(dev), window=4, h0=torch.from_numpy(h0).cuda(), return_state=True)
+        got = lb.lbscan_bwd(**fwd_inputs(dev), dout=dev["dout"], window=4, h0=torch.from_numpy(h0).cuda(),
+                            dhT=torch.from_numpy(dhT).cuda())
+        torch.cuda.synchronize()
+    finally:
+        lb.lbscan_set_option("segments", 0)
+    ref, ref_state = oracle.fwd(**fwd_inputs(s), window=4, h0=h0, return_state=True)
+    assert_close(to_numpy(out), ref, "fp32", "out")
+    assert_close(to_numpy(hT), ref_state, "fp32", "state")
+    grads = oracle.bwd(**fwd_inputs(s), dout=s["dout"], window=4, h0=h0, dhT=dhT)
+    for k in GRADS + ("dh0",):
+        assert_close(to_numpy(got[k]), grads[k], "fp32", k)
