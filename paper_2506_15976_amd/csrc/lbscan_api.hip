@@ -97,6 +97,7 @@ lbscan::FwdParams to_params(const lbscan_args* a, int window)
     p.order.W = a->scan_order ? a->grid_w : 1;
     p.order.HW = p.order.H * p.order.W;
     p.order.rH = 1.0f / (float)p.order.H;
+    p.pitch = a->seqlen;
     p.x = a->x; p.delta = a->delta; p.Bm = a->Bm; p.Cm = a->Cm; p.z = a->z;
     p.A = a->A; p.Dskip = a->Dskip; p.bias = a->delta_bias;
     p.yprev = nullptr; p.y = a->y; p.y_is_f32 = 0;
@@ -325,6 +326,7 @@ int lbscan_bwd_state(const lbscan_args* a, const void* dout, const float* dhT,
     p.batch = f.batch; p.dim = f.dim; p.dstate = f.dstate; p.seqlen = f.seqlen;
     p.window = M; p.dtype = f.dtype; p.softplus = f.softplus; p.reverse = f.reverse;
     p.order = f.order;
+    p.pitch = f.pitch;
     p.x = f.x; p.delta = f.delta; p.Bm = f.Bm; p.Cm = f.Cm; p.z = f.z;
     p.A = f.A; p.Dskip = f.Dskip; p.bias = f.bias;
     p.dout = dout; p.dx = dx; p.ddelta = ddelta; p.dz = a->z ? dz : nullptr;

@@ -438,20 +438,25 @@ TokenOrder stored_order()
     return r;
 }
 
+// The rows of the copies start at multiples of 32 elements: a tile is then whole lines of
+// memory, where rows of 197 tokens straddle them (the scan of such rows takes 10% longer).
+int copy_pitch(const FwdParams& p) { return (p.seqlen + 31) / 32 * 32; }
+
 struct CopySizes {
-    size_t row, mat;      // bytes of a (B,D,L) and of a (B,N,L) tensor in the storage type, rounded up
-    size_t row32;         // of a (B,D,L) tensor in fp32
+    size_t row, mat;      // bytes of a (B,D,L) and of a (B,N,L) copy in the storage type, rounded up
+    size_t row32;         // of a (B,D,L) copy in fp32
 };
 CopySizes copy_sizes(const FwdParams& p)
 {
     const size_t e = p.dtype == 0 ? 4 : 2;
-    const size_t bdl = (size_t)p.batch * p.dim * p.seqlen, bnl = (size_t)p.batch * p.dstate * p.seqlen;
+    const size_t bdl = (size_t)p.batch * p.dim * copy_pitch(p), bnl = (size_t)p.batch * p.dstate * copy_pitch(p);
     return {aligned_bytes(bdl * e), aligned_bytes(bnl * e), aligned_bytes(bdl * 4)};
 }
 
 FwdParams in_stored_order(FwdParams p)
 {
     p.order = stored_order();
+    p.pitch = copy_pitch(p);
     return p;
 }
 
@@ -459,10 +464,10 @@ FwdParams in_stored_order(FwdParams p)
 struct Copies {
     ReorderMany m{};
     int n = 0;
-    void add(const void* src, void* dst, long rows)
+    void add(const void* src, int src_pitch, void* dst, long rows)
     {
         if (!src) return;
-        m.src[n] = src; m.dst[n] = dst; m.rows[n] = rows;
+        m.src[n] = src; m.src_pitch[n] = src_pitch; m.dst[n] = dst; m.rows[n] = rows;
         ++n;
     }
 };
@@ -484,10 +489,12 @@ hipError_t launch_fwd_reordered(FwdParams p, void* workspace, float* saved, hipS
     char* at = static_cast<char*>(workspace) + aligned_bytes(fwd_workspace_bytes(q));
     auto take = [&](size_t n) { char* r = at; at += n; return r; };
     Copies in;
-    q.x = take(c.row);     in.add(p.x, const_cast<void*>(q.x), rows);
-    q.delta = take(c.row); in.add(p.delta, const_cast<void*>(q.delta), rows);
-    q.Bm = take(c.mat);    in.add(p.Bm, const_cast<void*>(q.Bm), mats);
-    q.Cm = take(c.mat);    in.add(p.Cm, const_cast<void*>(q.Cm), mats);
+    const int L = p.seqlen;
+    in.m.dst_pitch = q.pitch;
+    q.x = take(c.row);     in.add(p.x, L, const_cast<void*>(q.x), rows);
+    q.delta = take(c.row); in.add(p.delta, L, const_cast<void*>(q.delta), rows);
+    q.Bm = take(c.mat);    in.add(p.Bm, L, const_cast<void*>(q.Bm), mats);
+    q.Cm = take(c.mat);    in.add(p.Cm, L, const_cast<void*>(q.Cm), mats);
     hipError_t e = launch_reorder(in.m, p.dtype, p.seqlen, p.order, stream);
     if (e != hipSuccess) return e;
     q.z = nullptr;
@@ -496,7 +503,8 @@ hipError_t launch_fwd_reordered(FwdParams p, void* workspace, float* saved, hipS
     e = launch_fwd(q, workspace, saved, stream);
     if (e != hipSuccess) return e;
     Copies out;
-    out.add(q.y, p.y, rows);
+    out.add(q.y, q.pitch, p.y, rows);
+    out.m.dst_pitch = L;
     out.m.gate = p.z;
     return launch_reorder_gate(out.m, p.dtype, p.seqlen, inverse_order(p.order), stream);
 }
@@ -515,6 +523,7 @@ hipError_t launch_bwd_reordered(FwdParams f, BwdParams p, void* dBm, void* dCm, 
     FwdParams q = in_stored_order(f);
     BwdParams r = p;
     r.order = q.order;
+    r.pitch = q.pitch;
     const long rows = (long)f.batch * f.dim, mats = (long)f.batch * f.dstate;
     char* at = static_cast<char*>(workspace) + aligned_bytes(bwd_workspace_bytes(q));
     auto take = [&](size_t n) { char* t = at; at += n; return t; };
@@ -522,26 +531,28 @@ hipError_t launch_bwd_reordered(FwdParams f, BwdParams p, void* dBm, void* dCm, 
     auto copy_in = [&](const void* src, size_t bytes, long n) -> const void* {
         if (!src) return nullptr;
         void* d = take(bytes);
-        in.add(src, d, n);
+        in.add(src, f.seqlen, d, n);
         return d;
     };
-    auto copy_out = [&](void* dst, size_t bytes, long n) -> void* {
+    auto copy_out = [&](void* dst, size_t bytes, long n, int pitch) -> void* {
         if (!dst) return nullptr;
         void* t = take(bytes);
-        out.add(t, dst, n);
+        out.add(t, pitch, dst, n);
         return t;
     };
+    in.m.dst_pitch = q.pitch;
+    out.m.dst_pitch = f.seqlen;
     q.x = r.x = copy_in(f.x, c.row, rows);
     q.delta = r.delta = copy_in(f.delta, c.row, rows);
     q.z = r.z = copy_in(f.z, c.row, rows);
     r.dout = copy_in(p.dout, c.row, rows);
     q.Bm = r.Bm = copy_in(f.Bm, c.mat, mats);
     q.Cm = r.Cm = copy_in(f.Cm, c.mat, mats);
-    r.dx = copy_out(p.dx, c.row, rows);
-    r.ddelta = copy_out(p.ddelta, c.row, rows);
-    r.dz = copy_out(p.dz, c.row, rows);
-    void* dB = copy_out(dBm, c.mat, mats);
-    void* dC = copy_out(dCm, c.mat, mats);
+    r.dx = copy_out(p.dx, c.row, rows, q.pitch);
+    r.ddelta = copy_out(p.ddelta, c.row, rows, q.pitch);
+    r.dz = copy_out(p.dz, c.row, rows, q.pitch);
+    void* dB = copy_out(dBm, c.mat, mats, f.seqlen);      // (the sums over channels are dense)
+    void* dC = copy_out(dCm, c.mat, mats, f.seqlen);
     hipError_t e = launch_reorder(in.m, f.dtype, f.seqlen, f.order, stream);
     if (e != hipSuccess) return e;
     e = launch_bwd(q, r, dB, dC, workspace, saved, dhT, stream);

@@ -119,14 +119,15 @@ chunk_fwd_kernel(const FwdParams p)
     const int d = d0 + wv;
     const bool row_ok = d < D;                       // uniform per wave
     const int dc = row_ok ? d : D - 1;
-    const long rowoff = ((long)b * D + dc) * L;
+    const int LP = p.pitch;                          // row stride in elements
+    const long rowoff = ((long)b * D + dc) * LP;
     const T* __restrict__ xg = static_cast<const T*>(p.x) + rowoff;
     const T* __restrict__ dg = static_cast<const T*>(p.delta) + rowoff;
     const T* __restrict__ zg = p.z ? static_cast<const T*>(p.z) + rowoff : nullptr;
     TY* __restrict__ yg = static_cast<TY*>(p.y) + rowoff;
     const float* __restrict__ yprevg = p.yprev ? p.yprev + rowoff : nullptr;   // added to y before the gate
-    const T* __restrict__ Bg = static_cast<const T*>(p.Bm) + (long)b * N * L;
-    const T* __restrict__ Cg = static_cast<const T*>(p.Cm) + (long)b * N * L;
+    const T* __restrict__ Bg = static_cast<const T*>(p.Bm) + (long)b * N * LP;
+    const T* __restrict__ Cg = static_cast<const T*>(p.Cm) + (long)b * N * LP;
     const float bias = p.bias ? p.bias[dc] : 0.0f;
     const float skip = p.Dskip ? p.Dskip[dc] : 0.0f;
     float* wbuf = swave[wv];
@@ -164,7 +165,7 @@ chunk_fwd_kernel(const FwdParams p)
         const bool whole = chunk_is_whole(chunk);
 #pragma unroll
         for (int w = 0; w < 2; ++w) {
-            const T* src = (w ? Cg : Bg) + (long)n * L;
+            const T* src = (w ? Cg : Bg) + (long)n * LP;
 #pragma unroll
             for (int j = 0; j < kBCQ; ++j) {
                 const int t0 = chunk * kChunk + 4 * (tid + 64 * kR * j);
@@ -408,7 +409,7 @@ bool fwd_chunk_supported(const FwdParams& p)
     if (!window_supported(p.window) || p.order.kind != 0) return false;
     if (p.ckpt || p.summary_only || p.generic_window) return false;
     if (p.y_is_f32 && p.dtype != 0 && p.window != 1) return false;
-    if (p.dtype != 0 && (p.seqlen & 1)) return false;
+    if (p.dtype != 0 && ((p.seqlen | p.pitch) & 1)) return false;
     return p.dstate >= 1 && p.dstate <= 16;
 }
 

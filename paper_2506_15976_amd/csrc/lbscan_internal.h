@@ -16,6 +16,7 @@ struct FwdParams {
     int softplus;
     int reverse;
     TokenOrder order;   // scan order of a row's tokens (kind 0: as stored)
+    int pitch;          // elements from one row of a (B,D,L) or (B,N,L) tensor to the next: seqlen, or more
     const void* x;
     const void* delta;
     const void* Bm;
@@ -68,6 +69,7 @@ struct BwdParams {
     int softplus;
     int reverse;
     TokenOrder order;
+    int pitch;            // as in FwdParams; dBpart is dense
     const void* x;
     const void* delta;
     const void* Bm;
@@ -185,13 +187,16 @@ hipError_t launch_bwd_reordered(FwdParams f, BwdParams p, void* dBm, void* dCm, 
 
 // Reordering of up to kReorderMany (rows, L) tensors in one launch (lbscan_order.hip):
 // dst[i][row, t] = src[i][row, map(t)] for every entry whose src is set, L at most
-// kReorderMaxTokens.  Sources and destinations do not overlap.
+// kReorderMaxTokens.  Sources and destinations do not overlap.  Rows lie src_pitch[i]
+// elements apart (a multiple of 4 unless it is L) and dst_pitch in every destination.
 constexpr int kReorderMany = 6;
 constexpr int kReorderMaxTokens = 4096;
 struct ReorderMany {
     const void* src[kReorderMany];
     void* dst[kReorderMany];
     long rows[kReorderMany];
+    int src_pitch[kReorderMany];
+    int dst_pitch;
     const void* gate;             // launch_reorder_gate: z of entry 0 (rows as dst[0]), nullable
     long blocks[kReorderMany];    // set by the launcher
 };

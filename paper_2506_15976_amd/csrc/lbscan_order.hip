@@ -8,7 +8,8 @@
 // (The two ways are compared beside launch_fwd_reordered in lbscan_dispatch.hip.)
 //
 // What bounds it: HBM traffic, one read and one write; 5.5 TB/s measured (four row
-// tensors of 128 x 768 x 197 fp32 and Bm, Cm: 115 us).  A block takes an even number of
+// tensors of 128 x 768 x 197 fp32 and Bm, Cm: 115 us).  Destinations padded to whole lines are written
+// whole: with the padding left out the same launch took 139 us instead of 124.  A block takes an even number of
 // whole consecutive rows, which are one contiguous piece of memory: all its loads (up
 // to 32 elements a thread in quads) are in flight together, go to LDS as fp32, and are
 // written out token by token, 64 neighbouring tokens of a row per wave.  A lane keeps
@@ -43,14 +44,16 @@ reorder_kernel(const ReorderMany m, const int L, const int rows_per_block, const
     const long row0 = block * rows_per_block;
     const long left = m.rows[which] - row0;
     const int nrows = left < rows_per_block ? (int)left : rows_per_block;
-    const int n = nrows * L;                                  // <= kReFloats
-    const TS* __restrict__ src = static_cast<const TS*>(m.src[which]) + row0 * L;
-    TD* __restrict__ dst = static_cast<TD*>(m.dst[which]) + row0 * L;
-    const TD* __restrict__ gate = GATE ? static_cast<const TD*>(m.gate) + row0 * L : nullptr;
+    const int sp = m.src_pitch[which], dp = m.dst_pitch;
+    const int n = nrows * sp;                                 // <= kReFloats
+    const TS* __restrict__ src = static_cast<const TS*>(m.src[which]) + row0 * sp;
+    TD* __restrict__ dst = static_cast<TD*>(m.dst[which]) + row0 * dp;
+    const TD* __restrict__ gate = GATE ? static_cast<const TD*>(m.gate) + row0 * dp : nullptr;
 
     // the block's first element is an even one (even rows per block), so quads are
     // 4-byte aligned for 2-byte types too; a last quad that is not whole is loaded
-    // element by element
+    // element by element.  What lies between padded rows is loaded with them and written with
+    // some token of the row: whole lines move faster than the parts of them that are needed.
     Quad<TS> q[kReQuads];
 #pragma unroll
     for (int i = 0; i < kReQuads; ++i) {
@@ -70,7 +73,7 @@ reorder_kernel(const ReorderMany m, const int L, const int rows_per_block, const
     __syncthreads();
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int t0 = 0; t0 < L; t0 += 64 * kReCols) {
+    for (int t0 = 0; t0 < dp; t0 += 64 * kReCols) {
         int from[kReCols];
 #pragma unroll
         for (int j = 0; j < kReCols; ++j) {
@@ -83,15 +86,15 @@ reorder_kernel(const ReorderMany m, const int L, const int rows_per_block, const
 #pragma unroll
                 for (int j = 0; j < kReCols; ++j) {
                     const int t = t0 + 64 * j + lane;
-                    g[j] = to_f32(gate[r * L + (t < L ? t : L - 1)]);
+                    g[j] = to_f32(gate[r * dp + (t < L ? t : L - 1)]);
                 }
             }
 #pragma unroll
             for (int j = 0; j < kReCols; ++j) {
                 const int t = t0 + 64 * j + lane;
-                float v = buf[pad_slot(r * L + from[j])];
+                float v = buf[pad_slot(r * sp + from[j])];
                 if (GATE) v *= g[j] * sigmoid_f32(g[j]);
-                if (t < L) dst[r * L + t] = from_f32<TD>(v);
+                if (t < dp) dst[r * dp + t] = from_f32<TD>(v);
             }
         }
     }
@@ -102,9 +105,14 @@ hipError_t launch_reorder_t(ReorderMany m, int L, const TokenOrder& map, hipStre
 {
     // few rows: fewer of them to a block, down to two, so that about four blocks a CU start
     long rows = 0, total = 0;
-    for (int i = 0; i < kReorderMany; ++i) rows += m.src[i] ? m.rows[i] : 0;
+    int widest = L;
+    for (int i = 0; i < kReorderMany; ++i) {
+        rows += m.src[i] ? m.rows[i] : 0;
+        if (m.src[i] && m.src_pitch[i] > widest) widest = m.src_pitch[i];
+    }
+    if (2 * widest > kReFloats) return hipErrorInvalidValue;
     long rpb_want = (rows / 1024) & ~1L;
-    const int rpb_most = (kReFloats / L) & ~1;                // >= 2 for L <= kReorderMaxTokens
+    const int rpb_most = (kReFloats / widest) & ~1;           // >= 2 for rows of up to kReorderMaxTokens
     const int rpb = rpb_want < 2 ? 2 : (rpb_want < rpb_most ? (int)rpb_want : rpb_most);
     for (int i = 0; i < kReorderMany; ++i) {
         m.blocks[i] = m.src[i] ? (m.rows[i] + rpb - 1) / rpb : 0;
