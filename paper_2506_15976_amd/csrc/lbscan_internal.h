@@ -35,6 +35,7 @@ struct FwdParams {
     // segment (read by the full pass; written by the summary pass as the states a
     // segment reaches from zero); dsum: (nseg, B*D) sum of time steps per segment.
     int nseg, seg_tiles;
+    int in_block;         // full pass, at most kInBlockSegments segments: they are the waves of a block
     int summary_only;
     int fold_chain;       // full pass: fold the chain over the summaries in the kernel
     float* carry;         // nullable when nseg == 1
@@ -123,6 +124,9 @@ constexpr int kTileTokens = LBSCAN_BWD_TILE;      // tokens per tile of the back
 #define LBSCAN_FWD_TILE 32
 #endif
 constexpr int kFwdTileTokens = LBSCAN_FWD_TILE;   // tokens per tile of the forward kernel (32: 128 bytes of an fp32 row)
+
+// Segments of a row that one block takes (FwdParams::in_block).
+constexpr int kInBlockSegments = 8;
 
 // Window lengths with a compiled kernel.
 inline bool window_supported(int M) { return M == 1 || M == 2 || M == 4 || M == 8 || M == 16; }

@@ -23,6 +23,7 @@ def _check(lb, oracle, s, dtype, window, reverse, h0=None):
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("shape", [
     (1, 1, 16, 1), (2, 9, 9, 31), (1, 33, 8, 32), (3, 40, 16, 33), (1, 24, 1, 65), (2, 65, 5, 3), (1, 31, 16, 100),
+    (2, 21, 16, 197), (1, 8, 7, 256), (1, 17, 16, 257), (2, 3, 16, 509), (1, 9, 16, 512), (1, 9, 16, 513),
 ])
 def test_outputs_at_the_edges_of_a_tile(oracle, shape, dtype):
     import numpy as np
