@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "liblbscan.so")
@@ -127,13 +128,53 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+_raw_stream = None      # device index -> its current stream as an integer, where torch has it
+
+
 def _stream(stream):
+    """The hipStream_t to run on, as an integer.  Without a stream argument: the current stream
+    of the current device, asked for without a torch.cuda.Stream object (2.5 us of a call)."""
+    global _raw_stream
+    if stream is not None:
+        return stream.cuda_stream
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if _raw_stream is None:
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", False)
+    if _raw_stream:
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 ORDER_SEQUENCE, ORDER_COLUMNS = 0, 1
+
+
+def _address(t):
+    return 0 if t is None else t.data_ptr()
+
+
+# struct lbscan_args as make_args fills it: one pack instead of a Python assignment per field
+_ARGS_LAYOUT = struct.Struct("@8i10PNPN2P4i")
+assert _ARGS_LAYOUT.size == ctypes.sizeof(LbscanArgs)
+
+
+def _check_tensors(x, delta, A, Bm, Cm, Dskip, z, delta_bias, y, workspace, saved_state, h0, hT):
+    """Shapes, types, device and layout of what make_args takes; raises on the first that is wrong."""
+    import torch
+    Bsz, D, L = x.shape
+    N = A.shape[1]
+    for name, t, shape in (("delta", delta, (Bsz, D, L)), ("Bm", Bm, (Bsz, N, L)),
+                           ("Cm", Cm, (Bsz, N, L)), ("z", z, (Bsz, D, L)), ("y", y, (Bsz, D, L))):
+        if t is not None and (t.shape != shape or t.dtype != x.dtype):
+            raise LbscanError(EINVAL, f"{name}: expected {shape} {x.dtype}, got {tuple(t.shape)} {t.dtype}")
+    for name, t, shape in (("A", A, (D, N)), ("Dskip", Dskip, (D,)), ("delta_bias", delta_bias, (D,)),
+                           ("h0", h0, (Bsz, D, N)), ("hT", hT, (Bsz, D, N))):
+        if t is not None and (t.shape != shape or t.dtype != torch.float32):
+            raise LbscanError(EINVAL, f"{name}: expected {shape} float32")
+    tensors = (x, delta, A, Bm, Cm, Dskip, z, delta_bias, y, workspace, saved_state, h0, hT)
+    for i, t in enumerate(tensors):
+        if t is not None and not (t.is_cuda and t.is_contiguous()):
+            name = ("x", "delta", "A", "Bm", "Cm", "Dskip", "z", "delta_bias", "y", "workspace", "saved_state", "h0", "hT")[i]
+            raise LbscanError(EINVAL, f"{name} must be a contiguous device tensor")
 
 
 def make_args(x, delta, A, Bm, Cm, Dskip=None, z=None, delta_bias=None, *, window,
@@ -143,34 +184,17 @@ def make_args(x, delta, A, Bm, Cm, Dskip=None, z=None, delta_bias=None, *, windo
     (B,D,L); Bm, Cm (B,N,L); A (D,N) fp32; Dskip, delta_bias (D) fp32; h0, hT
     (B,D,N) fp32.  grid = (H, W) or (H, W, prefix): scan the H x W token grid that
     starts at token `prefix` column by column (see include/lbscan.h)."""
-    import torch
     Bsz, D, L = x.shape
     N = A.shape[1]
     code = _dtype_code(x)
-    for name, t, shape in (("delta", delta, (Bsz, D, L)), ("Bm", Bm, (Bsz, N, L)),
-                           ("Cm", Cm, (Bsz, N, L)), ("z", z, (Bsz, D, L)), ("y", y, (Bsz, D, L))):
-        if t is None:
-            continue
-        if tuple(t.shape) != shape or t.dtype != x.dtype:
-            raise LbscanError(EINVAL, f"{name}: expected {shape} {x.dtype}, got {tuple(t.shape)} {t.dtype}")
-    for name, t, shape in (("A", A, (D, N)), ("Dskip", Dskip, (D,)), ("delta_bias", delta_bias, (D,)),
-                           ("h0", h0, (Bsz, D, N)), ("hT", hT, (Bsz, D, N))):
-        if t is None:
-            continue
-        if tuple(t.shape) != shape or t.dtype != torch.float32:
-            raise LbscanError(EINVAL, f"{name}: expected {shape} float32")
-    for name, t in (("x", x), ("delta", delta), ("A", A), ("Bm", Bm), ("Cm", Cm), ("Dskip", Dskip),
-                    ("z", z), ("delta_bias", delta_bias), ("y", y), ("workspace", workspace),
-                    ("saved_state", saved_state), ("h0", h0), ("hT", hT)):
-        if t is not None and (not t.is_cuda or not t.is_contiguous()):
-            raise LbscanError(EINVAL, f"{name} must be a contiguous device tensor")
-    a = LbscanArgs(Bsz, D, N, L, int(window), code, int(bool(delta_softplus)), int(bool(reverse)),
-                   _ptr(x), _ptr(delta), _ptr(Bm), _ptr(Cm), _ptr(z), _ptr(A), _ptr(Dskip),
-                   _ptr(delta_bias), _ptr(y), _ptr(workspace),
-                   0 if workspace is None else workspace.numel() * workspace.element_size(),
-                   _ptr(saved_state),
-                   0 if saved_state is None else saved_state.numel() * saved_state.element_size(),
-                   _ptr(h0), _ptr(hT))
+    _check_tensors(x, delta, A, Bm, Cm, Dskip, z, delta_bias, y, workspace, saved_state, h0, hT)
+    a = LbscanArgs.from_buffer_copy(_ARGS_LAYOUT.pack(
+        Bsz, D, N, L, ctypes.c_int32(int(window)).value, code, int(bool(delta_softplus)), int(bool(reverse)),
+        x.data_ptr(), delta.data_ptr(), Bm.data_ptr(), Cm.data_ptr(), _address(z), A.data_ptr(), _address(Dskip),
+        _address(delta_bias), _address(y), _address(workspace),
+        0 if workspace is None else workspace.numel() * workspace.element_size(), _address(saved_state),
+        0 if saved_state is None else saved_state.numel() * saved_state.element_size(),
+        _address(h0), _address(hT), 0, 0, 0, 0))
     if grid is not None:
         a.scan_order = ORDER_COLUMNS
         a.grid_h, a.grid_w = int(grid[0]), int(grid[1])
