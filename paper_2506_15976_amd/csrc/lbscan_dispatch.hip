@@ -13,11 +13,6 @@ struct Shape { int nseg, seg_tiles; };
 // 8 x 384 x 1500 51.8 / 57.1.)
 constexpr int kFoldChainSegments = 16;
 
-// Blocks that the summary pass of a backward call is cut for (blocks of 32 rows, five
-// to a CU).  Training step, one summary segment to a segment / 2048 / 4096 blocks: 8 x 768 x
-// 4096 bf16 792 / 780 / 816 us, 1 x 256 x 65536 fp32 543 / 546 / 561 us.
-constexpr long kSummaryBlocks = 2048;
-
 // Cuts the rows into want_seg segments of whole forward tiles, at least 64 tokens each
 // (force_nseg: as many as asked for).
 Shape cut_rows(const FwdParams& p, long want_seg)
@@ -69,12 +64,21 @@ Shape in_block_shape(const FwdParams& p)
     return {(ntiles + st - 1) / st, st};
 }
 
-// The backward kernel runs one block per (64 rows, segment), two on a CU: one round of
-// 512 blocks where rows are cut.
+// The backward kernel runs one block per (64 rows, segment), two on a CU.  Where rows are
+// cut: three rounds of 512 blocks, so that a block's end leaves little idle, but not more than 64
+// segments unless one round needs them (long chains, more summaries to read).  Backward call on
+// MI355X, us, at 512 / 1536 blocks:
+//   8 x 768 x 4096 bf16    641 / 604      4 x 768 x 2048 bf16    189 / 180
+//   16 x 768 x 2048 bf16   754 / 607      2 x 768 x 4096 bf16    190 / 183
+//   16 x 768 x 1024 fp32   374 / 317      8 x 768 x 1100 fp32    193 / 207
+//   4 x 768 x 4096 bf16    331 / 316      6 x 768 x 2048 fp32    255 / 253
+//   1 x 256 x 65536 fp32   403 / 440      1 x 512 x 16384 fp32   207 / 230
 Shape pick_bwd_shape(const FwdParams& p)
 {
     const long nrb = (long)((p.dim + 63) / 64) * p.batch;
-    return cut_rows(p, nrb < 256 ? 512 / nrb : 1);
+    if (nrb >= 256) return cut_rows(p, 1);
+    const long fill = 512 / nrb, rounds = 1536 / nrb < 64 ? 1536 / nrb : 64;
+    return cut_rows(p, fill > rounds ? fill : rounds);
 }
 
 size_t carry_floats(const FwdParams& p, int nseg)
@@ -245,8 +249,7 @@ bool needs_gamma_checkpoints(const FwdParams& f)
 }
 
 struct BwdLayout {
-    Shape shape;            // segments of the backward kernel in forward tiles (32 tokens)
-    Shape sum;              // and of the summary pass: a whole number of them to one of those
+    Shape shape;            // segments in forward tiles (32 tokens)
     size_t ntiles16;        // backward tiles (16 tokens) per row
     size_t ckpt, cum, gck, carry, dsum, psi, part;   // float offsets into the workspace
     size_t total;           // floats
@@ -257,27 +260,16 @@ BwdLayout bwd_layout(const FwdParams& f)
     BwdLayout l;
     l.shape = pick_bwd_shape(f);
     const bool gamma = needs_gamma_checkpoints(f);
-    l.sum = l.shape;
-    if (l.shape.nseg > 1) {
+    if (gamma && l.shape.nseg > 1) {
+        // segments must start at window starts: whole windows per segment
+        long g = f.window, r = kFwdTileTokens;
+        while (r) { const long t = g % r; g = r; r = t; }          // gcd(window, 32)
+        const long unit = f.window / g;                            // forward tiles per window period
         const long ntiles = (f.seqlen + kFwdTileTokens - 1) / kFwdTileTokens;
-        const long nrb = (long)((f.dim + 31) / 32) * f.batch;
-        long fine = f.force_nseg >= 1 ? 1 : kSummaryBlocks / (nrb * l.shape.nseg);
-        if (fine < 1) fine = 1;
-        if (fine > l.shape.seg_tiles / 2) fine = l.shape.seg_tiles / 2 > 0 ? l.shape.seg_tiles / 2 : 1;
-        long st = (l.shape.seg_tiles + fine - 1) / fine;
-        if (gamma) {
-            // segments must start at window starts: whole windows per segment
-            long g = f.window, r = kFwdTileTokens;
-            while (r) { const long t = g % r; g = r; r = t; }      // gcd(window, 32)
-            const long unit = f.window / g;                        // forward tiles per window period
-            st = (st + unit - 1) / unit * unit;
-        }
-        if (st > ntiles) st = ntiles;
-        fine = (l.shape.seg_tiles + st - 1) / st;
-        l.sum.seg_tiles = (int)st;
-        l.sum.nseg = (int)((ntiles + st - 1) / st);
-        l.shape.seg_tiles = (int)(st * fine < ntiles ? st * fine : ntiles);
-        l.shape.nseg = (int)((ntiles + st * fine - 1) / (st * fine));
+        long st = ((l.shape.seg_tiles + unit - 1) / unit) * unit;
+        if (st >= ntiles) st = ntiles;
+        l.shape.seg_tiles = (int)st;
+        l.shape.nseg = (int)((ntiles + st - 1) / st);
     }
     const size_t rows = (size_t)f.batch * f.dim, N = f.dstate;
     l.ntiles16 = (f.seqlen + kTileTokens - 1) / kTileTokens;
@@ -285,7 +277,7 @@ BwdLayout bwd_layout(const FwdParams& f)
     l.ckpt = o; o += l.ntiles16 * rows * N;
     l.cum = o;  o += l.ntiles16 * rows;
     l.gck = o;  if (gamma) o += l.ntiles16 * rows * N;
-    const size_t ns = l.sum.nseg > 1 ? l.sum.nseg : 0;
+    const size_t ns = l.shape.nseg > 1 ? l.shape.nseg : 0;
     l.carry = o; o += ns * rows * N;
     l.dsum = o;  o += ns * rows;
     l.psi = o;   o += ns * rows * N;
@@ -319,12 +311,10 @@ hipError_t launch_bwd(const FwdParams& f, BwdParams p, void* dBm, void* dCm, voi
     p.gck = gamma ? ws + l.gck : nullptr;
     p.nseg = s.nseg;
     p.seg_tiles = s.seg_tiles * (kFwdTileTokens / kTileTokens);
-    p.nsum = l.sum.nseg;
-    p.sum_tiles = l.sum.seg_tiles * (kFwdTileTokens / kTileTokens);
     // uncut rows: the entering state and the gradient arriving at the leaving state
     // take the places of the chained values
-    p.carry = p.nsum > 1 ? ws + l.carry : f.h0;
-    p.psi_in = p.nsum > 1 ? ws + l.psi : dhT;
+    p.carry = s.nseg > 1 ? ws + l.carry : f.h0;
+    p.psi_in = s.nseg > 1 ? ws + l.psi : dhT;
 
     hipError_t e;
     const ZeroMany z{{p.dA, p.dDskip, p.dbias, nullptr, nullptr},
@@ -338,7 +328,7 @@ hipError_t launch_bwd(const FwdParams& f, BwdParams p, void* dBm, void* dCm, voi
                             : launch_reduce_bf16(p.dBpart, dBm, dCm, bnl, nbx, stream);
     };
 
-    if (saved && p.nsum == 1 && !gamma) {
+    if (saved && s.nseg == 1 && !gamma) {
         // the forward call left the checkpoints (entering state included): no summary pass
         p.ckpt = saved;
         p.cum = nullptr;
@@ -352,8 +342,8 @@ hipError_t launch_bwd(const FwdParams& f, BwdParams p, void* dBm, void* dCm, voi
     // forward and of the right-to-left recurrence; for windows that straddle tile
     // starts also the checkpoints of the adjoint of the local backward state
     FwdParams q = f;
-    q.nseg = l.sum.nseg;
-    q.seg_tiles = l.sum.seg_tiles;
+    q.nseg = s.nseg;
+    q.seg_tiles = s.seg_tiles;
     q.summary_only = 1;
     q.ckpt = ws + l.ckpt;
     q.cum = ws + l.cum;

@@ -89,13 +89,12 @@ struct BwdParams {
     float* dDskip;        // (D) zeroed, nullable
     float* dbias;         // (D) zeroed, nullable
     const float* ckpt;    // (ntiles, N, B*D): f at the first step of every tile, counted
-                          // from the start of the tile's summary segment
-    // rows cut into nseg segments of seg_tiles backward tiles (16 tokens each), a segment
-    // into whole summary segments of sum_tiles (nsum of them in a row):
-    int nseg, seg_tiles, nsum, sum_tiles;
-    const float* cum;     // (ntiles, B*D): time-step sum from the summary segment's start to the tile
-    const float* carry;   // (nsum, N, B*D): forward state entering each summary segment (null: zeros)
-    const float* psi_in;  // (nsum, N, B*D): psi entering each summary segment from the right
+                          // from the start of the tile's segment
+    // rows cut into nseg segments of seg_tiles backward tiles (16 tokens each):
+    int nseg, seg_tiles;
+    const float* cum;     // (ntiles, B*D): time-step sum from the segment start to the tile
+    const float* carry;   // (nseg, N, B*D): forward state entering each segment (null: zeros)
+    const float* psi_in;  // (nseg, N, B*D): psi entering each segment from the right
     const float* gck;     // (ntiles, N, B*D), nullable: abar_{t-1} gamma_{t-1} entering each tile
                           // (windows that straddle tile starts)
     float* dh0;           // (B*D, N), nullable: psi leaving the row on the left
