@@ -49,9 +49,9 @@ _PROFILE_LINES = {
 
 # The launches of one lbscan_fwd call (the library's own choice at these shapes).
 FWD_KERNELS = {
-    "vim_tiny": "rowlane_fwd_kernel", "vim_small": "rowlane_fwd_kernel",
+    "vim_tiny": "wave_fwd_kernel", "vim_small": "wave_fwd_kernel",
     "hires_4096": "chunk_fwd_kernel",
-    "wsi_bag": "rowlane_fwd_kernel summary pass + carry_chain_kernel + rowlane_fwd_kernel full pass",
+    "wsi_bag": "wave_fwd_kernel summary pass + carry_chain_kernel + wave_fwd_kernel full pass",
 }
 
 
@@ -198,7 +198,7 @@ def measure_workload(lb, lib, name, w, sets, steps, warmup, with_bwd, per_launch
         out["fwd_cache_hot_ms"] = time_calls(fwd_calls[:1], steps, warmup)
     else:
         out["fwd_ms"] = time_calls(fwd_calls, steps, warmup)
-    # the same call with the row-per-lane kernels forced (rows cut into segments), where
+    # the same call with the wave-tile kernels forced (rows cut into segments), where
     # the library itself picks the chunk-per-lane kernel
     out["fwd_row_per_lane_ms"] = None
     if w["seqlen"] >= 1024 and w["batch"] * w["dim"] >= 1536 and grid is None:
@@ -454,7 +454,7 @@ def main():
                    "input_sets_rotated": nsets},
         "roofline": {"bound": "hbm", "achieved": gbps, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": gbps / HBM_PEAK_GBPS, "traffic": profile_figure("traffic", a.workload),
-                     "kernel": FWD_KERNELS.get(a.workload, "rowlane_fwd_kernel"),
+                     "kernel": FWD_KERNELS.get(a.workload, "wave_fwd_kernel"),
                      "algorithmic_bytes_per_launch": fwd_bytes,
                      "launch_ms": ms_fwd, "launch_ms_event_pairs": fl["mean"],
                      "launch_ms_median": fl["median"], "launch_ms_min": fl["min"]},

@@ -198,55 +198,6 @@ __device__ __forceinline__ Quad<T> quad_raw_checked(const T* __restrict__ base, 
     return q;
 }
 
-// The same result as quad_raw_checked with ONE quad load, for rows of at least four
-// tokens that allow quad loads: the quad is loaded from the nearest position that
-// lies inside the row (ph clamped to [0, L-4]) and its elements are moved to where
-// they belong; elements whose token ph + e is outside [0, L) become zero.  Element
-// loads cost the texture-address unit one pass per element (a wave's 64 dwords sit
-// in up to 64 different sectors), which made the ragged last tile of a row as
-// expensive as a full one.
-// Two steps, so that the load can stay in flight: quad_raw_clamped issues it,
-// quad_rearrange (when the data is needed) moves the elements.
-template <typename T>
-__device__ __forceinline__ Quad<T> quad_raw_clamped(const T* __restrict__ base, long off, int ph, int L)
-{
-    const int phc = ph < 0 ? 0 : (ph > L - 4 ? L - 4 : ph);
-    return *reinterpret_cast<const Quad<T>*>(base + (off + (phc - ph)));
-}
-template <typename T>
-__device__ __forceinline__ Quad<T> quad_rearrange(const Quad<T>& q, int ph, int L)
-{
-    const int phc = ph < 0 ? 0 : (ph > L - 4 ? L - 4 : ph);
-    const int s = ph - phc;                       // wanted element e is loaded element e + s
-    Quad<T> r;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int k = e + s;
-        T v = zero_elem<T>();
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v = (k == j) ? q.v[j] : v;
-        r.v[e] = v;
-    }
-    return r;
-}
-template <typename T>
-__device__ __forceinline__ Quad<T> quad_raw_ragged(const T* __restrict__ base, long off, int ph, int L)
-{
-    const int phc = ph < 0 ? 0 : (ph > L - 4 ? L - 4 : ph);
-    const Quad<T> q = *reinterpret_cast<const Quad<T>*>(base + (off + (phc - ph)));
-    const int s = ph - phc;                       // wanted element e is loaded element e + s
-    Quad<T> r;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int k = e + s;
-        T v = zero_elem<T>();
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v = (k == j) ? q.v[j] : v;
-        r.v[e] = v;
-    }
-    return r;
-}
-
 template <typename T>
 __device__ __forceinline__ void quad_store(T* __restrict__ base, long off, bool fast,
                                            int ph, int L, const float in[4])
