@@ -15,6 +15,9 @@
 // written out token by token, 64 neighbouring tokens of a row per wave.  A lane keeps
 // its tokens' places in the LDS row in registers and walks the block's rows, so the
 // index arithmetic is paid once per block and not once per element.
+// The gate of a wave's next kReAhead rows is loaded while it writes the rows before (the first
+// ones with the block's quads): loaded where it is used, every row waited for its gate (69 us,
+// 3.4 TB/s for 128 x 768 x 197 in fp32; now 49).
 #include "lbscan_device.h"
 #include "lbscan_internal.h"
 
@@ -25,6 +28,8 @@ constexpr int kReThreads = 256;
 constexpr int kReFloats = 32 * kReThreads;            // elements of a block's rows
 constexpr int kReQuads = kReFloats / 4 / kReThreads;  // quads per thread
 constexpr int kReCols = 4;                            // tokens a lane holds at a time (256 of a row per wave)
+constexpr int kReWaves = kReThreads / 64;
+constexpr int kReAhead = 3;                           // rows whose gate a wave has in flight
 
 // one float of padding every 32: a column of a grid whose width is a multiple of 16
 // would otherwise sit in two banks
@@ -60,6 +65,20 @@ reorder_kernel(const ReorderMany m, const int L, const int rows_per_block, const
         const int k = ((int)threadIdx.x + i * kReThreads) * 4;
         if (k + 4 <= n) q[i] = quad_raw_fast<TS>(src, k);
     }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    TD g[GATE ? kReAhead : 1][kReCols];
+    auto load_gate = [&](int t0, int r0) {
+#pragma unroll
+        for (int u = 0; u < kReAhead; ++u) {
+            const int r = r0 + kReWaves * u;
+#pragma unroll
+            for (int j = 0; j < kReCols; ++j) {
+                const int t = t0 + 64 * j + lane;
+                g[u][j] = gate[(r < nrows ? r : nrows - 1) * dp + (t < L ? t : L - 1)];
+            }
+        }
+    };
+    if constexpr (GATE) load_gate(0, wave);
 #pragma unroll
     for (int i = 0; i < kReQuads; ++i) {
         const int k = ((int)threadIdx.x + i * kReThreads) * 4;
@@ -72,7 +91,6 @@ reorder_kernel(const ReorderMany m, const int L, const int rows_per_block, const
     }
     __syncthreads();
 
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int t0 = 0; t0 < dp; t0 += 64 * kReCols) {
         int from[kReCols];
 #pragma unroll
@@ -80,21 +98,27 @@ reorder_kernel(const ReorderMany m, const int L, const int rows_per_block, const
             const int t = t0 + 64 * j + lane;
             from[j] = map(t < L ? t : L - 1);
         }
-        for (int r = wave; r < nrows; r += kReThreads / 64) {
-            float g[kReCols];
-            if (GATE) {
+        if constexpr (GATE) { if (t0 > 0) load_gate(t0, wave); }
+        for (int r0 = wave; r0 < nrows; r0 += kReWaves * kReAhead) {
+            float f[kReAhead][kReCols];
+            if constexpr (GATE) {
+#pragma unroll
+                for (int u = 0; u < kReAhead; ++u)
+#pragma unroll
+                    for (int j = 0; j < kReCols; ++j) f[u][j] = to_f32(g[u][j]);
+                if (r0 + kReWaves * kReAhead < nrows) load_gate(t0, r0 + kReWaves * kReAhead);
+            }
+#pragma unroll
+            for (int u = 0; u < kReAhead; ++u) {
+                const int r = r0 + kReWaves * u;
+                if (r >= nrows) break;
 #pragma unroll
                 for (int j = 0; j < kReCols; ++j) {
                     const int t = t0 + 64 * j + lane;
-                    g[j] = to_f32(gate[r * dp + (t < L ? t : L - 1)]);
+                    float v = buf[pad_slot(r * sp + from[j])];
+                    if (GATE) v *= f[u][j] * sigmoid_f32(f[u][j]);
+                    if (t < dp) dst[r * dp + t] = from_f32<TD>(v);
                 }
-            }
-#pragma unroll
-            for (int j = 0; j < kReCols; ++j) {
-                const int t = t0 + 64 * j + lane;
-                float v = buf[pad_slot(r * sp + from[j])];
-                if (GATE) v *= g[j] * sigmoid_f32(g[j]);
-                if (t < dp) dst[r * dp + t] = from_f32<TD>(v);
             }
         }
     }
