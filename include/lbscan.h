@@ -128,7 +128,7 @@ typedef struct lbscan_args {
    stored one (0: these sizes gather faster, or have more than 4096 tokens).  Includes
    LBSCAN_WS_FWD / LBSCAN_WS_BWD; for the backward size, args->z says whether there is a
    gate.  It is large: two (forward; and one in fp32) or seven (backward, with a gate)
-   tensors of x's size and two or four of Bm's, 236 MB and 674 MB at 128 x 768 x 16 x 197
+   tensors of x's size and two or four of Bm's, 268 MB and 750 MB at 128 x 768 x 16 x 197
    in fp32. */
 #define LBSCAN_WS_FWD_ORDER 4
 #define LBSCAN_WS_BWD_ORDER 5
