@@ -375,36 +375,37 @@ hipError_t launch_bwd(const FwdParams& f, BwdParams p, void* dBm, void* dCm, voi
 // of the rows the caches hold between tiles: rows of few bytes, grids of few rows or few
 // columns and small calls gather well.  Measured on MI355X (us, gather / copies):
 //   rows x tokens (grid)            forward fp32   forward bf16   backward fp32  backward bf16
-//   128 x 384, 50 (7 x 7)           27 / 43        27 / 42        154 / 180      158 / 167
-//   1042 x 384, 50                  180 / 276      185 / 244      824 / 983      877 / 862
-//   88 x 384, 65 (8 x 8)            34 / 50        34 / 48        161 / 181      179 / 174
-//   127 x 384, 82 (9 x 9)           44 / 73        39 / 60        229 / 229      217 / 209
-//   103 x 384, 101 (10 x 10)        60 / 75        50 / 63        261 / 239      243 / 226
-//   72 x 384, 145 (12 x 12)         66 / 72        52 / 61        277 / 202      214 / 197
-//   90 x 384, 145                   96 / 84        65 / 72        414 / 289      346 / 283
-//   29 x 384, 197 (14 x 14)         82 / 59        56 / 58        233 / 164      195 / 158
-//   106 x 384, 197                  162 / 119      99 / 108       708 / 397      526 / 367
-//   132 x 384, 197                  227 / 145      149 / 135      906 / 480      609 / 430
-//   128 x 768, 197                  351 / 226      207 / 194      1540 / 771     1017 / 677
-//   30 x 384, 257 (16 x 16)         92 / 71        62 / 67        358 / 196      272 / 189
-//   35 x 384, 257                   117 / 76       80 / 71        404 / 207      298 / 201
-//   32 x 384, 325 (18 x 18)         148 / 84       86 / 73        513 / 233      328 / 225
-//   4 x 768, 1025 (32 x 32)         141 / 77       112 / 78       359 / 209      273 / 212
-//   768, 4096 (64 x 64)             120 / 97       119 / 91       321 / 220      278 / 220
-//   119 x 384, 197 (2 x 98)         96 / 125       92 / 112       413 / 422      470 / 375
-//   119 x 384, 197 (65 x 3)         130 / 125      93 / 112       442 / 420      464 / 383
-//   8 x 384, 1025 (4 x 256)         65 / 82        64 / 78        219 / 214      223 / 216
-//   30 x 384, 1025 (4 x 256)        240 / 193      227 / 189      689 / 632      758 / 592
-//   6 x 384, 1025 (8 x 128)         77 / 76        65 / 77        245 / 180      210 / 174
-//   8 x 384, 1025 (8 x 128)         73 / 80        69 / 78        271 / 213      241 / 216
-//   11 x 384, 1025 (8 x 128)        149 / 95       132 / 87       442 / 256      414 / 249
-//   3 x 384, 2049 (8 x 256)         97 / 80        76 / 80        257 / 187      232 / 184
-//   4 x 384, 2049 (8 x 256)         72 / 90        68 / 86        261 / 222      229 / 229
-// (How fast a gather of few long rows is goes up and down with how their blocks fill the
-// chip: fp32 at 8 x 384 and 4 x 384 is on the wrong side of the line.)
+//   128 x 384, 50 (7 x 7)           29 / 46        34 / 48        116 / 125      118 / 121
+//   1042 x 384, 50 (7 x 7)          185 / 250      214 / 231      725 / 742      678 / 654
+//   88 x 384, 65 (8 x 8)            31 / 46        37 / 49        128 / 132      135 / 131
+//   127 x 384, 82 (9 x 9)           44 / 59        45 / 60        188 / 165      166 / 154
+//   103 x 384, 101 (10 x 10)        53 / 58        51 / 60        223 / 177      198 / 169
+//   72 x 384, 145 (12 x 12)         67 / 58        51 / 58        256 / 159      183 / 155
+//   90 x 384, 145 (12 x 12)         86 / 67        67 / 68        359 / 224      279 / 213
+//   29 x 384, 197 (14 x 14)         70 / 51        52 / 55        237 / 129      169 / 133
+//   106 x 384, 197 (14 x 14)        164 / 89       103 / 89       662 / 317      431 / 284
+//   132 x 384, 197 (14 x 14)        215 / 114      125 / 104      874 / 395      518 / 343
+//   128 x 768, 197 (14 x 14)        385 / 200      202 / 171      1517 / 651     904 / 563
+//   30 x 384, 257 (16 x 16)         76 / 62        59 / 63        309 / 146      220 / 145
+//   35 x 384, 257 (16 x 16)         82 / 60        61 / 61        396 / 167      271 / 162
+//   32 x 384, 325 (18 x 18)         124 / 66       82 / 66        438 / 177      268 / 166
+//   4 x 768, 1025 (32 x 32)         138 / 75       97 / 77        255 / 153      215 / 153
+//   768, 4096 (64 x 64)             105 / 88       105 / 90       219 / 172      234 / 176
+//   119 x 384, 197 (2 x 98)         92 / 103       101 / 94       359 / 341      360 / 295
+//   119 x 384, 197 (65 x 3)         122 / 102      102 / 94       395 / 338      354 / 294
+//   8 x 384, 1025 (4 x 256)         52 / 75        58 / 77        157 / 154      151 / 154
+//   30 x 384, 1025 (4 x 256)        242 / 181      191 / 171      642 / 460      618 / 431
+//   6 x 384, 1025 (8 x 128)         50 / 66        54 / 69        191 / 138      167 / 138
+//   8 x 384, 1025 (8 x 128)         60 / 76        61 / 78        178 / 154      168 / 152
+//   11 x 384, 1025 (8 x 128)        130 / 86       104 / 89       395 / 205      373 / 200
+//   3 x 384, 2049 (8 x 256)         58 / 71        57 / 75        216 / 150      197 / 155
+//   4 x 384, 2049 (8 x 256)         58 / 81        61 / 83        170 / 169      165 / 175
+// (The lines stand where the kernels before put them; on the wrong side are now, forward: fp32
+// at 8 x 128 and 8 x 256 below 4 million elements, at 72 x 384 x 145, bf16 at 106 x 384 x 197;
+// backward: fp32 at 2 x 98, by 5%.)
 // The copies ask for an fp32 result, which the chunk-per-lane kernel gives for bf16 only
 // with window 1: bf16 images of 4096 tokens run the wave-tile kernels here (8 x 768:
-// 2023 / 379).
+// 2396 / 405).
 namespace {
 
 // Elements of a (B,D,L) tensor from which the forward pass copies.  Never below 2^21:
