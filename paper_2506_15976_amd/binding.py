@@ -188,13 +188,17 @@ def make_args(x, delta, A, Bm, Cm, Dskip=None, z=None, delta_bias=None, *, windo
     N = A.shape[1]
     code = _dtype_code(x)
     _check_tensors(x, delta, A, Bm, Cm, Dskip, z, delta_bias, y, workspace, saved_state, h0, hT)
-    a = LbscanArgs.from_buffer_copy(_ARGS_LAYOUT.pack(
-        Bsz, D, N, L, ctypes.c_int32(int(window)).value, code, int(bool(delta_softplus)), int(bool(reverse)),
-        x.data_ptr(), _address(delta), _address(Bm), _address(Cm), _address(z), A.data_ptr(), _address(Dskip),
-        _address(delta_bias), _address(y), _address(workspace),
-        0 if workspace is None else workspace.numel() * workspace.element_size(), _address(saved_state),
-        0 if saved_state is None else saved_state.numel() * saved_state.element_size(),
-        _address(h0), _address(hT), 0, 0, 0, 0))
+    try:
+        packed = _ARGS_LAYOUT.pack(
+            Bsz, D, N, L, ctypes.c_int32(int(window)).value, code, int(bool(delta_softplus)), int(bool(reverse)),
+            x.data_ptr(), _address(delta), _address(Bm), _address(Cm), _address(z), A.data_ptr(), _address(Dskip),
+            _address(delta_bias), _address(y), _address(workspace),
+            0 if workspace is None else workspace.numel() * workspace.element_size(), _address(saved_state),
+            0 if saved_state is None else saved_state.numel() * saved_state.element_size(),
+            _address(h0), _address(hT), 0, 0, 0, 0)
+    except struct.error:
+        raise LbscanError(EINVAL, f"sizes {Bsz} x {D} x {N} x {L} do not fit 32 bits") from None
+    a = LbscanArgs.from_buffer_copy(packed)
     if grid is not None:
         a.scan_order = ORDER_COLUMNS
         a.grid_h, a.grid_w = int(grid[0]), int(grid[1])

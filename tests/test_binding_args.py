@@ -36,3 +36,12 @@ def test_a_required_tensor_left_out(name):
     with pytest.raises(binding.LbscanError) as e:
         binding.lbscan_fwd(**s, window=4, out=s["x"], stream=Stream())
     assert e.value.code == binding.EINVAL
+
+
+@pytest.mark.parametrize("sizes", [dict(B=1 << 31, D=0), dict(D=0, L=1 << 31), dict(D=0, N=1 << 31)])
+def test_sizes_beyond_32_bits(sizes):
+    """Empty tensors with an edge that the struct cannot hold."""
+    with pytest.raises(binding.LbscanError) as e:
+        s = _inputs(**sizes)
+        binding.lbscan_fwd(**s, window=4, out=s["x"], stream=Stream())
+    assert e.value.code == binding.EINVAL
