@@ -102,6 +102,7 @@ lbscan::FwdParams to_params(const lbscan_args* a, int window)
     p.A = a->A; p.Dskip = a->Dskip; p.bias = a->delta_bias;
     p.yprev = nullptr; p.y = a->y; p.y_is_f32 = 0;
     p.force_nseg = tuning_nseg();
+    p.beside = 0;
     p.force_mapping = g_mapping.load(std::memory_order_relaxed);
     p.nseg = 1; p.seg_tiles = 0; p.in_block = 0; p.summary_only = 0; p.fold_chain = 0; p.carry = nullptr; p.dsum = nullptr;
     p.ckpt = nullptr; p.cum = nullptr; p.dout = nullptr; p.psi = nullptr; p.gck = nullptr;

@@ -1,4 +1,5 @@
 // Launch-shape heuristics of the forward path.
+#include "../../include/lbscan.h"
 #include "lbscan_internal.h"
 
 #include <limits.h>
@@ -30,6 +31,17 @@ Shape cut_rows(const FwdParams& p, long want_seg)
     return s;
 }
 
+size_t carry_floats(const FwdParams& p, int nseg)
+{
+    return (size_t)nseg * p.batch * p.dim * (size_t)p.dstate;
+}
+
+// Scratch of rows cut into nseg segments: the states and the sums of time steps.
+size_t summary_bytes(const FwdParams& p, int nseg)
+{
+    return nseg <= 1 ? 0 : (carry_floats(p, nseg) + (size_t)nseg * p.batch * p.dim) * sizeof(float);
+}
+
 // The forward kernels run one block per (32 rows, segment), six of them on a CU.  Rows that
 // cannot fill the chip are cut into segments scanned in parallel: a summary launch, the
 // carry chain, then the full pass started from the carried-in states.  That costs a second
@@ -38,10 +50,19 @@ Shape cut_rows(const FwdParams& p, long want_seg)
 // 62.4 / 61.6, 784 tokens 84.7 / 81.2; 192 blocks: 197 tokens 22.6 / 23.3, 576 tokens
 // 54.1 / 39.8; 768 blocks: 197 tokens 35.4 / 48.5.  Number of blocks aimed at (1 x 256 x
 // 65536): 1024: 156, 1536: 154, 2048: 149, 2560: 164; 1 x 512 x 16384: 768: 93, 1024: 88, 2048: 88.
+// The summaries alone take 5.3 MB at most.  Beside a first pass's result they may not fit what
+// lbscan_fwd_static holds: the rows are then cut into as many segments as do, but into no fewer
+// than 768 blocks of 64 rows need (uncut from 256 such row blocks on).
 Shape pick_shape(const FwdParams& p)
 {
     const long nrb = (long)((p.dim + 31) / 32) * p.batch;
-    return cut_rows(p, nrb < 384 ? (2048 + nrb - 1) / nrb : 1);
+    const Shape s = cut_rows(p, nrb < 384 ? (2048 + nrb - 1) / nrb : 1);
+    if (p.beside + summary_bytes(p, s.nseg) <= LBSCAN_STATIC_SCRATCH_BYTES || p.beside > LBSCAN_STATIC_SCRATCH_BYTES) return s;
+    const long nrb64 = (long)((p.dim + 63) / 64) * p.batch;
+    const long coarse = nrb64 < 256 ? (768 + nrb64 - 1) / nrb64 : 1;
+    const long fitting = (long)((LBSCAN_STATIC_SCRATCH_BYTES - p.beside) / (summary_bytes(p, 2) / 2));
+    const Shape t = cut_rows(p, fitting > coarse ? fitting : coarse);
+    return p.beside + summary_bytes(p, t.nseg) <= LBSCAN_STATIC_SCRATCH_BYTES ? t : s;
 }
 
 // Few short rows: the segments of a row as waves of one block of 8 rows, one launch instead of two;
@@ -79,11 +100,6 @@ Shape pick_bwd_shape(const FwdParams& p)
     if (nrb >= 256) return cut_rows(p, 1);
     const long fill = 512 / nrb, rounds = 1536 / nrb < 64 ? 1536 / nrb : 64;
     return cut_rows(p, fill > rounds ? fill : rounds);
-}
-
-size_t carry_floats(const FwdParams& p, int nseg)
-{
-    return (size_t)nseg * p.batch * p.dim * (size_t)p.dstate;
 }
 
 // The chunk-per-lane kernel (one wave per row, 1024-token chunks, one launch) against the
@@ -127,9 +143,7 @@ bool use_chunk_mapping(const FwdParams& p, const float* saved)
 size_t fwd_workspace_bytes(const FwdParams& p)
 {
     if (p.batch == 0 || p.dim == 0 || p.seqlen == 0) return 0;
-    const Shape s = pick_shape(p);
-    if (s.nseg <= 1 || in_block_shape(p).nseg) return 0;
-    return (carry_floats(p, s.nseg) + (size_t)s.nseg * p.batch * p.dim) * sizeof(float);
+    return in_block_shape(p).nseg ? 0 : summary_bytes(p, pick_shape(p).nseg);
 }
 
 size_t saved_state_bytes(const FwdParams& p)
@@ -194,13 +208,18 @@ hipError_t launch_fwd(FwdParams p, void* workspace, float* saved, hipStream_t st
 // first in fp32 (in y itself when y is fp32, else at the start of the
 // workspace); pass 2 adds the second for any window length, gates and writes y.
 
+static size_t generic_partial_bytes(const FwdParams& p)
+{
+    return p.dtype == 0 ? 0 : (size_t)p.batch * p.dim * p.seqlen * sizeof(float);
+}
+
 size_t fwd_generic_workspace_bytes(const FwdParams& p)
 {
     if (p.batch == 0 || p.dim == 0 || p.seqlen == 0) return 0;
     FwdParams p1 = p;
     p1.window = 1;
-    const size_t partial = p.dtype == 0 ? 0 : (size_t)p.batch * p.dim * p.seqlen * sizeof(float);
-    return partial + fwd_workspace_bytes(p1);
+    p1.beside = generic_partial_bytes(p);
+    return p1.beside + fwd_workspace_bytes(p1);
 }
 
 hipError_t launch_fwd_generic(FwdParams p, void* workspace, hipStream_t stream)
@@ -211,9 +230,10 @@ hipError_t launch_fwd_generic(FwdParams p, void* workspace, hipStream_t stream)
     if (p.dtype != 0) {
         if (!workspace) return hipErrorInvalidValue;
         partial = static_cast<float*>(workspace);
-        scratch += (size_t)p.batch * p.dim * p.seqlen * sizeof(float);
+        scratch += generic_partial_bytes(p);
     }
     FwdParams p1 = p;
+    p1.beside = generic_partial_bytes(p);
     p1.window = 1; p1.z = nullptr; p1.y = partial; p1.y_is_f32 = 1;
     hipError_t e = launch_fwd(p1, scratch, nullptr, stream);
     if (e != hipSuccess) return e;

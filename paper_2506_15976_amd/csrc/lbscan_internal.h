@@ -29,6 +29,7 @@ struct FwdParams {
     void* y;              // element type = dtype, or fp32 when y_is_f32
     int y_is_f32;         // write y as fp32 whatever dtype says (first pass of the two-pass scan)
     int force_nseg;       // >= 1: override the number of segments a row is cut into
+    size_t beside;        // bytes of a first pass's result that share the scratch with the cut's summaries (0: none)
     int force_mapping;    // 0: heuristic; 1: wave-tile kernels; 2: chunk-per-lane kernel where it applies
     // Long rows are cut into nseg segments of seg_tiles forward tiles (kFwdTileTokens tokens each), one
     // block per (64 rows, segment).  carry: (nseg, N, B*D) states entering each
