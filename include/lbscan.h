@@ -230,8 +230,9 @@ int lbscan_default_window(int32_t seqlen);
  *                 stay inside one wave, and there is one way of spreading them.
  *   "segments":   0 (default) lets the library choose into how many segments a
  *                 row is cut for parallel scanning (long rows, few channels);
- *                 k >= 1 asks for k (rounded so that segments are whole 32-token tiles).  It
- *                 changes lbscan_workspace_bytes: query after setting it.
+ *                 k >= 1 asks for k (rounded so that segments are whole 32-token tiles), and
+ *                 lbscan_fwd then takes the first of the families below unless "mapping" is 2.
+ *                 It changes lbscan_workspace_bytes: query after setting it.
  *   "mapping":    0 (default) lets lbscan_fwd choose between its two kernel
  *                 families: waves of eight rows (walked in tiles; cut into
  *                 segments when rows are few) and one wave per row with 16 tokens

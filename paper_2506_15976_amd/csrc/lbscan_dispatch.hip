@@ -131,6 +131,7 @@ bool use_chunk_mapping(const FwdParams& p, const float* saved)
     if (!fwd_chunk_supported(q)) return false;
     if (saved) return false;
     if (p.force_mapping == 2) return true;
+    if (p.force_nseg >= 1) return false;                              // (it takes its rows whole)
     const long rows = (long)p.batch * p.dim;
     const long chunk = 1024, nchunks = (p.seqlen + chunk - 1) / chunk;
     if (p.seqlen * 5 < nchunks * chunk * 4) return false;             // chunks less than 80% full

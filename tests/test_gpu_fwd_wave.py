@@ -60,3 +60,33 @@ def test_rows_of_one_chunk(oracle, shape, dtype):
                 _check(lb, oracle, s, dtype, window, reverse, h0)
         finally:
             lb.lbscan_set_option("mapping", 0)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("tokens, segments", [(1024, 3), (1024, 32)])
+def test_a_forced_cut_is_made(oracle, tokens, segments, dtype):
+    """Option "segments" at sizes that the library itself hands to the chunk-per-lane kernel, which
+    takes rows whole: the summaries are written to the scratch, and the result is right."""
+    import ctypes
+    import torch
+    import paper_2506_15976_amd as lb
+    from gpu_util import assert_close, fwd_inputs, to_device, to_numpy
+    from paper_2506_15976_amd.inputs import make_inputs
+    s = make_inputs(1, 64, 16, tokens, seed=9450 + tokens, dtype=dtype)
+    dev = to_device(s, dtype)
+    y = torch.empty_like(dev["x"])
+    a = lb.make_args(**fwd_inputs(dev), window=4, y=y)
+    lb.lbscan_set_option("segments", segments)
+    try:
+        need = lb.lbscan_workspace_bytes(a, 0)
+        assert need == segments * 64 * (16 + 1) * 4
+        ws = torch.full((need // 4,), float("nan"), device="cuda:0")
+        a.workspace, a.workspace_bytes = ws.data_ptr(), need
+        rc = lb.load().lbscan_fwd(ctypes.byref(a), torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+    finally:
+        lb.lbscan_set_option("segments", 0)
+    assert rc == 0
+    written = torch.isfinite(ws).sum().item()
+    assert written >= (segments - 1) * 64 * (16 + 1)        # nobody reads the last segment's
+    assert_close(to_numpy(y), oracle.fwd(**fwd_inputs(s), window=4), dtype)

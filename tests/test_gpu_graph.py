@@ -32,6 +32,7 @@ def _workspace(lb, args, which, device):
 
 @pytest.mark.parametrize("shape,window,segments,mapping", [
     ((2, 70, 16, 197), 4, 0, 0), ((1, 64, 16, 900), 8, 3, 0), ((2, 64, 16, 100), 5, 0, 0),
+    ((1, 64, 16, 900), 8, 29, 0),       # a chain too long for the full pass to fold: a launch of its own
     ((2, 9, 16, 2500), 8, 0, 2),        # the chunk-per-lane kernel
 ])
 def test_forward_call_replays_from_a_graph(lb, shape, window, segments, mapping):
