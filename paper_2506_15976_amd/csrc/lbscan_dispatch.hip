@@ -102,27 +102,30 @@ Shape pick_bwd_shape(const FwdParams& p)
     return cut_rows(p, fill > rounds ? fill : rounds);
 }
 
-// The chunk-per-lane kernel (one wave per row, 1024-token chunks, one launch) against the
-// wave-tile kernels (rows cut where that is faster), measured on MI355X (us, wave tiles /
-// chunk; fp32 with window 4, bf16 with window 8):
-//   rows x tokens      fp32           bf16
-//   192 x 1024         22.1 / 18.2    22.4 / 16.6
-//   768 x 1024         21.2 / 17.6    22.7 / 17.5
-//   6144 x 1024        58.8 / 47.5    64.7 / 42.9
-//   12288 x 1024       97.6 / 84.6    108 / 75.8
-//   24576 x 1024       138 / 181      147 / 142
-//   1536 x 2048        42.5 / 38.8    42.9 / 34.3
-//   12288 x 2048       189 / 181      200 / 145
-//   768 x 4096         45.3 / 59.0    46.1 / 53.7
-//   1536 x 4096        70.7 / 72.1    74.2 / 65.0
-//   3072 x 4096        109 / 87.9     121 / 81.9
-//   6144 x 4096        196 / 187      211 / 152
-//   3072 x 1500 (73%)  52.0 / 52.9    55.3 / 52.8
-//   6144 x 784 (77%)   48.5 / 67.3    51.8 / 69.0
-// It needs chunks that are mostly full, and rows enough for a wave each unless a row is a
-// single chunk; with fp32 storage (four rows share a staged Bm / Cm chunk, so those reads are
-// twice the row reads) it loses where the wave tiles fill the chip without cutting rows.  It leaves no
-// checkpoints for a backward call.
+// The chunk-per-lane kernel (one wave per row, 1024-token chunks, one launch; 768 blocks of four rows
+// in flight) against the wave-tile kernels (rows cut where that is faster), measured on MI355X
+// (us, wave tiles / chunk; fp32 with window 4, bf16 with window 8).  Whole chunks:
+//   rows x tokens      fp32           bf16           rows x tokens      fp32           bf16
+//   192 x 1024         20.7 / 16.6    21.6 / 14.6    1536 x 4096        65.5 / 72.5    68.3 / 63.9
+//   3072 x 1024        36.7 / 26.2    40.2 / 22.6    3072 x 4096        109 / 88.1     118 / 80.7
+//   12288 x 1024       105 / 87.3     119 / 75.8     6144 x 4096        214 / 183      218 / 150
+//   24576 x 1024       145 / 188      148 / 143      12288 x 4096       425 / 366      508 / 313
+//   1536 x 2048        39.2 / 38.7    40.3 / 33.1    16128 x 2048       213 / 240      251 / 193
+// A chunk that the row does not fill takes its loads element by element, in every state:
+//   192 x 900          19.9 / 22.4    20.8 / 24.1    3072 x 2000        64.8 / 58.2    67.5 / 57.5
+//   768 x 1020         21.0 / 23.2    21.1 / 24.1    6144 x 1700        95.6 / 103     105 / 104
+//   1920 x 1020        32.2 / 30.8    32.3 / 27.3    6144 x 5000        264 / 265      268 / 217
+//   2688 x 900         34.4 / 36.1    40.0 / 32.7    9216 x 2000        148 / 181      160 / 158
+//   3072 x 960         35.9 / 36.0    37.8 / 34.3    12288 x 1700       175 / 217      205 / 202
+//   3456 x 960         41.3 / 58.4    44.0 / 57.2    12288 x 4000       398 / 412      513 / 388
+//   6144 x 1000        62.4 / 71.1    67.6 / 73.0    16128 x 2000       209 / 327      252 / 290
+//   16128 x 960        100 / 185      115 / 190      2688 x 2700        78.4 / 73.1    77.4 / 74.2
+// It needs chunks that are mostly full, and rows enough for a wave each unless a row is one whole
+// chunk; a row of one ragged chunk pays where the rows about fill one round of blocks (3072).  With fp32
+// storage (four rows share a staged Bm / Cm chunk, so those reads are twice the row reads) it loses
+// where the wave tiles fill the chip without cutting rows, with ragged chunks beyond two rounds.
+// (On the wrong side: bf16 rows of two ragged chunks around 1536 and 3456 rows and from 14592 rows on.)
+// It leaves no checkpoints for a backward call.
 bool use_chunk_mapping(const FwdParams& p, const float* saved)
 {
     if (p.force_mapping == 1) return false;
@@ -134,8 +137,11 @@ bool use_chunk_mapping(const FwdParams& p, const float* saved)
     if (p.force_nseg >= 1) return false;                              // (it takes its rows whole)
     const long rows = (long)p.batch * p.dim;
     const long chunk = 1024, nchunks = (p.seqlen + chunk - 1) / chunk;
+    const bool ragged = p.seqlen % chunk != 0;
     if (p.seqlen * 5 < nchunks * chunk * 4) return false;             // chunks less than 80% full
+    if (ragged && nchunks == 1) return rows > 1536 && rows <= 3072;
     if (p.dtype != 0) return nchunks == 1 || rows >= 1536;
+    if (ragged) return rows <= 6144 && (rows >= 3072 || (nchunks == 2 && rows > 1536));
     return rows <= 16384 && (nchunks == 1 || rows >= 3072 || (nchunks == 2 && rows >= 1536));
 }
 

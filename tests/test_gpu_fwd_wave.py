@@ -1,5 +1,6 @@
-"""Forward kernel at the edges of its tiles (8 rows a wave, 32 a block, 32 tokens), and the
-calls that its rule hands to the chunk-per-lane kernel; fp64 oracle as the reference."""
+"""Forward kernel at the edges of its tiles (8 rows a wave, 32 a block, 32 tokens), and rows of
+one chunk, which a rule shares out between it and the chunk-per-lane kernel; fp64 oracle as the
+reference."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -43,17 +44,17 @@ def test_outputs_at_the_edges_of_a_tile(oracle, shape, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
-@pytest.mark.parametrize("shape", [(1, 5, 16, 1024), (2, 3, 7, 820), (1, 200, 16, 1000)])
+@pytest.mark.parametrize("shape", [(1, 5, 16, 1024), (2, 3, 7, 820), (1, 200, 16, 1000), (1, 1537, 5, 822)])
 def test_rows_of_one_chunk(oracle, shape, dtype):
-    """Few rows of 820 to 1024 tokens: one launch of the chunk-per-lane kernel; the wave tiles
-    (option "mapping") give the same within the same bounds."""
+    """Rows of 820 to 1024 tokens, which the library hands to one family or the other: its own
+    choice (the chunk-per-lane kernel for the first and the last), and each family asked for."""
     import numpy as np
     import paper_2506_15976_amd as lb
     from paper_2506_15976_amd.inputs import make_inputs
     B, D, N, L = shape
     s = make_inputs(B, D, N, L, seed=9400 + D + L, dtype=dtype, random_A=True)
     h0 = np.random.default_rng(D).standard_normal((B, D, N)).astype(np.float32)
-    for mapping in (0, 1):
+    for mapping in (0, 1, 2):
         lb.lbscan_set_option("mapping", mapping)
         try:
             for window, reverse in ((4, False), (16, True)):
