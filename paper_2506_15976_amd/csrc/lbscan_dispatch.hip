@@ -45,18 +45,42 @@ size_t summary_bytes(const FwdParams& p, int nseg)
 // The forward kernels run one block per (32 rows, segment), six of them on a CU.  Rows that
 // cannot fill the chip are cut into segments scanned in parallel: a summary launch, the
 // carry chain, then the full pass started from the carried-in states.  That costs a second
-// read of x, delta, Bm and ~60% more arithmetic, so only when rows are scarce.  Measured on
-// MI355X (us, fp32, window 4, uncut / cut): 384 blocks: 197 tokens 26.9 / 30.5, 576 tokens
-// 62.4 / 61.6, 784 tokens 84.7 / 81.2; 192 blocks: 197 tokens 22.6 / 23.3, 576 tokens
-// 54.1 / 39.8; 768 blocks: 197 tokens 35.4 / 48.5.  Number of blocks aimed at (1 x 256 x
-// 65536): 1024: 156, 1536: 154, 2048: 149, 2560: 164; 1 x 512 x 16384: 768: 93, 1024: 88, 2048: 88.
-// The summaries alone take 5.3 MB at most.  Beside a first pass's result they may not fit what
+// read of x, delta, Bm and ~60% more arithmetic, so only when rows are scarce.  Number of blocks
+// aimed at (us, 1 x 256 x 65536): 1024: 156, 1536: 154, 2048: 149, 2560: 164; 1 x 512 x 16384:
+// 768: 93, 1024: 88, 2048: 88.  Up to 256 row blocks a CU has one block of uncut rows at most, and
+// all rows that one block cannot take whole (in_block_shape) are cut; beyond, the longer the rows
+// the more a cut can pay for its launches.  Measured on MI355X (us, uncut / cut; fp32 with window
+// 4, bf16 with window 8):
+//   tokens  blocks  fp32          bf16             tokens  blocks  fp32          bf16
+//   160     264     18.7 / 20.4   20.3 / 21.2      700     348     73.6 / 76.2   86.0 / 76.8
+//   197     324     25.4 / 27.3   28.8 / 30.2      700     372     73.8 / 81.2   86.1 / 80.5
+//   197     348     25.4 / 30.1   28.7 / 33.7      700     396     74.0 / 82.1   86.3 / 84.8
+//   256     324     28.8 / 30.1   31.1 / 32.5      1100    372     113 / 113     134 / 120
+//   256     348     28.8 / 31.5   30.8 / 33.9      1600    384     161 / 159     184 / 162
+//   300     348     34.9 / 39.4   39.6 / 40.7      1600    396     161 / 158     184 / 169
+//   300     372     35.0 / 40.7   40.0 / 42.9      1600    420     161 / 169     185 / 183
+//   400     348     44.6 / 46.7   51.7 / 50.0      3001    384     325 / 334     380 / 323
+//   400     372     44.8 / 47.6   51.8 / 50.3      3001    396     320 / 349     381 / 344
+//   400     396     44.9 / 53.5   52.0 / 55.3      3001    420     322 / 370     383 / 366
+// (The lines stand where neither direction and no window loses by them: reversed rows and window 1
+// gain from a cut a little further on.  At 384 blocks reversed fp32 rows off whole lines would gain 5 to 8% from a cut,
+// forward ones lose as much; the size of the scratch does not depend on the direction.)
+long cut_below(const FwdParams& p)
+{
+    const int L = p.seqlen;
+    if (L <= 192) return 257;
+    if (L <= 256) return 336;
+    if (p.dtype == 0 || L <= 320) return L <= 1024 ? 360 : 384;
+    return L <= 1024 ? 390 : 410;
+}
+
+// The summaries alone take 5.4 MB at most.  Beside a first pass's result they may not fit what
 // lbscan_fwd_static holds: the rows are then cut into as many segments as do, but into no fewer
 // than 768 blocks of 64 rows need (uncut from 256 such row blocks on).
 Shape pick_shape(const FwdParams& p)
 {
     const long nrb = (long)((p.dim + 31) / 32) * p.batch;
-    const Shape s = cut_rows(p, nrb < 384 ? (2048 + nrb - 1) / nrb : 1);
+    const Shape s = cut_rows(p, nrb < cut_below(p) ? (2048 + nrb - 1) / nrb : 1);
     if (p.beside + summary_bytes(p, s.nseg) <= LBSCAN_STATIC_SCRATCH_BYTES || p.beside > LBSCAN_STATIC_SCRATCH_BYTES) return s;
     const long nrb64 = (long)((p.dim + 63) / 64) * p.batch;
     const long coarse = nrb64 < 256 ? (768 + nrb64 - 1) / nrb64 : 1;
