@@ -32,10 +32,11 @@ def test_gradients_at_the_edges_of_a_tile(oracle, shape, dtype):
             assert_close(to_numpy(got[k]), r, dtype, f"{k} window {window} reverse {reverse}")
 
 
-@pytest.mark.parametrize("tokens, segments", [(97, 2), (1100, 17), (9000, 282)])
+@pytest.mark.parametrize("tokens, segments", [(97, 2), (1100, 18), (1100, 35), (9000, 282)])
 def test_carry_chains_of_any_length(oracle, tokens, segments):
-    """Chains folded in the pass, of more segments than a wave takes, and of more than a block
-    takes (256): forward states and the right-to-left recurrence."""
+    """Chains folded in the pass, of more segments than a wave takes (16) with a second and a
+    third wave partly filled, and of more than a block takes (256): forward states and the
+    right-to-left recurrence."""
     import numpy as np
     import torch
     import paper_2506_15976_amd as lb
@@ -47,6 +48,8 @@ def test_carry_chains_of_any_length(oracle, tokens, segments):
     h0, dhT = (rng.standard_normal((1, 35, 5)).astype(np.float32) for _ in range(2))
     lb.lbscan_set_option("segments", segments)
     try:
+        # (a count that the rounding to whole tiles leaves as it is)
+        assert lb.lbscan_workspace_bytes(lb.make_args(**fwd_inputs(dev), window=4), 0) == segments * 35 * (5 + 1) * 4
         out, hT = lb.lbscan_fwd(**fwd_inputs(dev), window=4, h0=torch.from_numpy(h0).cuda(), return_state=True)
         got = lb.lbscan_bwd(**fwd_inputs(dev), dout=dev["dout"], window=4, h0=torch.from_numpy(h0).cuda(),
                             dhT=torch.from_numpy(dhT).cuda())

@@ -51,20 +51,23 @@ def test_ragged_shapes(lb, oracle, shape, window):
     _run_fwd(lb, oracle, s, window=window, reverse=True)
 
 
-@pytest.mark.parametrize("waves_log2", [0, 1, 2, 3])
-def test_every_state_split_variant(lb, oracle, waves_log2):
-    """The states of a row can be split over 1, 2, 4 or 8 waves; force each."""
+@pytest.mark.parametrize("N", [1, 7, 8, 9, 16])
+@pytest.mark.parametrize("segments", [0, 1, 3])
+def test_every_spread_of_the_states(lb, oracle, N, segments):
+    """A lane holds one state of a row up to N = 8 and two beyond, with lanes that hold fewer or
+    none: rows whose segments are the waves of a block (the library's choice for the long
+    ones here), whole rows and rows cut by the launch."""
     from paper_2506_15976_amd.inputs import make_inputs
-    lb.lbscan_set_option("waves_log2", waves_log2)
+    lb.lbscan_set_option("segments", segments)
     try:
-        for (B, D, N, L, M) in [(2, 70, 16, 37, 4), (1, 130, 8, 50, 8), (1, 64, 5, 33, 2), (2, 64, 16, 197, 16)]:
+        for (B, D, L, M) in [(2, 70, 37, 4), (1, 130, 100, 8), (1, 64, 33, 2), (2, 64, 197, 16)]:
             s = make_inputs(B, D, N, L, seed=4000 + D + L, random_A=True)
             _run_fwd(lb, oracle, s, window=M)
             _run_fwd(lb, oracle, s, window=M, reverse=True)
-        s = make_inputs(1, 96, 16, 64, seed=4100, dtype="bf16")
+        s = make_inputs(1, 96, N, 64, seed=4100, dtype="bf16")
         _run_fwd(lb, oracle, s, window=4, dtype="bf16")
     finally:
-        lb.lbscan_set_option("waves_log2", -1)
+        lb.lbscan_set_option("segments", 0)
 
 
 @pytest.mark.parametrize("segments", [2, 3, 7])

@@ -270,19 +270,22 @@ def test_copies_replay_from_a_graph(lb, dtype):
         assert torch.equal(again["out"], eager["out"])
 
 
-@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
-@pytest.mark.parametrize("grid", [(14, 14, 0), (13, 16, 1), (16, 16, 0), (9, 25, 3)])
-def test_copies_with_room_behind_their_rows(lb, oracle, grid, dtype):
-    """The copies' rows start at multiples of 32 tokens: ragged rows and whole ones, both
-    directions, at sizes that copy in both passes."""
+@pytest.mark.parametrize("dtype, B, grid", [
+    ("fp32", 20, (14, 14, 0)), ("fp32", 20, (13, 16, 1)), ("fp32", 20, (16, 16, 0)), ("fp32", 20, (9, 25, 3)),
+    # bf16 rows copy in the forward call from 208 tokens on, smaller calls from 320
+    ("bf16", 12, (18, 18, 0)), ("bf16", 32, (13, 16, 1)), ("bf16", 32, (16, 16, 0)), ("bf16", 32, (9, 25, 3)),
+])
+def test_copies_with_room_behind_their_rows(lb, oracle, dtype, B, grid):
+    """The copies' rows start at multiples of 32 tokens: ragged rows (of odd length among them) and
+    whole ones, both directions, at sizes that copy in both passes."""
     from paper_2506_15976_amd import binding
     from paper_2506_15976_amd.inputs import make_inputs
     h, w, prefix = grid
-    L = prefix + h * w + (1 if h == 14 else 0)
-    B, D, N = 20, 560, 16
+    L = prefix + h * w + (1 if h in (14, 18) else 0)
+    D, N = 560, 16
     a = binding.LbscanArgs(B, D, N, L, 4, 0 if dtype == "fp32" else 1)
     a.scan_order, a.grid_h, a.grid_w, a.grid_prefix = binding.ORDER_COLUMNS, h, w, prefix
-    assert binding.lbscan_workspace_bytes(a, binding.WS_BWD_ORDER) > 0
+    assert all(binding.lbscan_workspace_bytes(a, which) > 0 for which in (binding.WS_FWD_ORDER, binding.WS_BWD_ORDER))
     s = make_inputs(B, D, N, L, seed=9700 + L, dtype=dtype, with_dout=True)
     for reverse in (False, True):
         _check(lb, oracle, s, grid, window=4, dtype=dtype, reverse=reverse)
