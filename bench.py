@@ -196,15 +196,18 @@ def measure_workload(lb, lib, name, w, sets, steps, warmup, with_bwd, per_launch
     if per_launch:
         out["fwd_ms"], out["fwd_launch"] = time_calls(fwd_calls, steps, warmup, per_launch=True)
         out["fwd_cache_hot_ms"] = time_calls(fwd_calls[:1], steps, warmup)
+        # the GPU runs slower for about 20 ms after an idle spell: a few steps after a few warmup
+        # steps lie inside them, 200 calls after 300 do not
+        out["fwd_settled_ms"] = time_calls(fwd_calls, 200, 300)
     else:
         out["fwd_ms"] = time_calls(fwd_calls, steps, warmup)
     # the same call with the wave-tile kernels forced (rows cut into segments), where
     # the library itself picks the chunk-per-lane kernel
-    out["fwd_row_per_lane_ms"] = None
+    out["fwd_wave_tiles_ms"] = None
     if w["seqlen"] >= 1024 and w["batch"] * w["dim"] >= 1536 and grid is None:
         lb.lbscan_set_option("mapping", 1)
         try:
-            out["fwd_row_per_lane_ms"] = time_calls(fwd_calls, max(steps // 2, 1), max(warmup // 2, 1))
+            out["fwd_wave_tiles_ms"] = time_calls(fwd_calls, max(steps // 2, 1), max(warmup // 2, 1))
         finally:
             lb.lbscan_set_option("mapping", 0)
 
@@ -287,8 +290,8 @@ def summarize(name, w, r):
         "two_pass_bidir_ms": r["bidir_ms"],
         "speedup_vs_two_pass_bidir": None if r["bidir_ms"] is None else r["bidir_ms"] / r["fwd_ms"],
     }
-    if r.get("fwd_row_per_lane_ms") is not None:
-        rec["fwd_row_per_lane_ms"] = r["fwd_row_per_lane_ms"]
+    if r.get("fwd_wave_tiles_ms") is not None:
+        rec["fwd_wave_tiles_ms"] = r["fwd_wave_tiles_ms"]
     if r.get("bwd_ms") is not None:
         rec.update({
             "bwd_ms": r["bwd_ms"], "bwd_algorithmic_bytes": bb,
@@ -312,7 +315,6 @@ def main():
     ap.add_argument("--no-others", action="store_true", help="only the headline workload (profiling runs)")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="also run a plain 1 GiB elementwise copy kernel, for scaling rocprofv3 FETCH_SIZE / WRITE_SIZE")
-    ap.add_argument("--waves-log2", type=int, default=-1, help="force the state-split launch shape (tuning)")
     ap.add_argument("--segments", type=int, default=0, help="force the number of row segments (tuning)")
     ap.add_argument("--sets", type=int, default=0, help="independent input sets to rotate over (0: enough for 640 MB)")
     a = ap.parse_args()
@@ -335,7 +337,6 @@ def main():
         torch.cuda.synchronize()
         del src, dst
     lib = lb.load()
-    lb.lbscan_set_option("waves_log2", a.waves_log2)
     lb.lbscan_set_option("segments", a.segments)
     if a.shape:
         f = a.shape.split(",")
@@ -463,6 +464,9 @@ def main():
         "speedup_vs_two_pass_bidir": head["bidir_ms"] / ms_fwd,
         "two_pass_bidir_ms": head["bidir_ms"],
         "cache_hot_ms_per_step": head["fwd_cache_hot_ms"],
+        "settled_ms_per_step": head["fwd_settled_ms"],
+        "settled_note": "the same calls timed after 300 others: the first 150 or so after an idle spell take "
+                        "up to 1.3 times as long (value and ms_per_step are of the steps asked for)",
         "bwd_ms": head["bwd_ms"],
         "fwd_plus_bwd_ms": head["fwd_plus_bwd_ms"],
         "fwd_plus_bwd_window1_ms": head.get("fwd_plus_bwd_window1_ms"),
