@@ -47,7 +47,7 @@ int check_args_sizes(const lbscan_args* a, bool* empty)
     if (a->dtype != LBSCAN_FP32 && a->dtype != LBSCAN_BF16) return LBSCAN_EUNSUPPORTED;
     if (a->dstate > LBSCAN_MAX_DSTATE) return LBSCAN_EUNSUPPORTED;
     if (a->reverse != 0 && a->reverse != 1) return LBSCAN_EINVAL;
-    if (a->seqlen > (1 << 24)) return LBSCAN_EUNSUPPORTED;   // 64 rows * L is indexed in 32 bits
+    if (a->seqlen > (1 << 24)) return LBSCAN_EUNSUPPORTED;   // the 16 rows of a wave are addressed in 32 bits of bytes
     if (a->scan_order != LBSCAN_ORDER_SEQUENCE && a->scan_order != LBSCAN_ORDER_COLUMNS) return LBSCAN_EINVAL;
     if (a->scan_order == LBSCAN_ORDER_COLUMNS) {
         if (a->grid_h < 1 || a->grid_w < 1 || a->grid_prefix < 0) return LBSCAN_EINVAL;
@@ -314,8 +314,8 @@ int lbscan_bwd_state(const lbscan_args* a, const void* dout, const float* dhT,
     const void* ptrs[] = {dout, dx, ddelta, dz, dBm, dCm, dA, dDskip, ddelta_bias, dhT, dh0};
     for (const void* q : ptrs)
         if (q && !aligned4(q)) return LBSCAN_EINVAL;
-    // one backward kernel covers every window length (1, 2, 4 with a compiled window
-    // structure, all others with run-time window masks); a window that covers the
+    // one backward kernel covers every window length (1, 2, 4, 8, 16 with a compiled
+    // window structure, all others with run-time window masks); a window that covers the
     // whole row is the same as any longer one
     const int fwdM = effective_window(a->window, a->seqlen);
     const int M = fwdM ? fwdM : (a->window < a->seqlen ? a->window : a->seqlen);

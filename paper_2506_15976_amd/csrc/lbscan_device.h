@@ -90,8 +90,9 @@ template <> __device__ __forceinline__ bf16_t from_f32<bf16_t>(float v)
 // Four consecutive elements.  Global memory on gfx950 serves multi-dword
 // accesses at dword alignment, so the fp32 quad only promises 4-byte alignment
 // (rows of odd length start at any dword); the bf16 quad promises 4 bytes too:
-// where a row can start at an odd element callers use quad_raw_unaligned /
-// quad_store_unaligned inside the row and element accesses at its ragged end.
+// where a row can start at an odd element callers load the words around a quad
+// (Words3) and use quad_store_unaligned inside the row, and element accesses at its
+// ragged end.
 template <typename T> struct Quad;
 template <> struct __attribute__((packed, aligned(4))) Quad<float> { float v[4]; };
 template <> struct __attribute__((packed, aligned(4))) Quad<bf16_t> { bf16_t v[4]; };
@@ -127,16 +128,6 @@ __device__ __forceinline__ Quad<bf16_t> quad_of_words(const Words3& w, const bf1
     q.v[0].bits = (uint16_t)lo; q.v[1].bits = (uint16_t)(lo >> 16);
     q.v[2].bits = (uint16_t)hi; q.v[3].bits = (uint16_t)(hi >> 16);
     return q;
-}
-__device__ __forceinline__ Quad<bf16_t> quad_raw_unaligned(const bf16_t* __restrict__ p)
-{
-    const uintptr_t u = reinterpret_cast<uintptr_t>(p);
-    return quad_of_words(*reinterpret_cast<const Words3*>(u & ~static_cast<uintptr_t>(3)), p);
-}
-// (fp32 rows need no such path; the overload keeps templates uniform)
-__device__ __forceinline__ Quad<float> quad_raw_unaligned(const float* __restrict__ p)
-{
-    return *reinterpret_cast<const Quad<float>*>(p);
 }
 // The matching store: 2 + 4 + 2 bytes at an odd element address, 8 bytes at an even one.
 __device__ __forceinline__ void quad_store_unaligned(bf16_t* __restrict__ p, const float in[4])

@@ -118,6 +118,9 @@ Shape in_block_shape(const FwdParams& p)
 //   16 x 768 x 1024 fp32   374 / 317      8 x 768 x 1100 fp32    193 / 207
 //   4 x 768 x 4096 bf16    331 / 316      6 x 768 x 2048 fp32    255 / 253
 //   1 x 256 x 65536 fp32   403 / 440      1 x 512 x 16384 fp32   207 / 230
+// (On the wrong side: rows that three rounds cut into segments of two or three tiles, as 8 x 768 x
+// 1100 above; 32 x 384 x 197 106 us in four segments, 98 in two; 4 x 768 x 1100 125 and 119.  The next
+// lengths go the other way, 8 x 768 x 1300 239 / 227.)
 Shape pick_bwd_shape(const FwdParams& p)
 {
     const long nrb = (long)((p.dim + 63) / 64) * p.batch;
@@ -221,7 +224,7 @@ hipError_t launch_fwd(FwdParams p, void* workspace, float* saved, hipStream_t st
         hipError_t e = launch(q);
         if (e != hipSuccess) return e;
         // few segments: the full pass folds the chain itself (one launch less);
-        // many: the chain kernel, a shuffle scan over the segments
+        // many: the chain kernel, which shares them out to the waves of a block
         p.fold_chain = s.nseg <= kFoldChainSegments;
         if (!p.fold_chain) {
             e = launch_carry_chain(p, stream);

@@ -32,7 +32,7 @@ struct FwdParams {
     size_t beside;        // bytes of a first pass's result that share the scratch with the cut's summaries (0: none)
     int force_mapping;    // 0: heuristic; 1: wave-tile kernels; 2: chunk-per-lane kernel where it applies
     // Long rows are cut into nseg segments of seg_tiles forward tiles (kFwdTileTokens tokens each), one
-    // block per (64 rows, segment).  carry: (nseg, N, B*D) states entering each
+    // block per (32 rows, segment); in_block: one per 8 rows.  carry: (nseg, N, B*D) states entering each
     // segment (read by the full pass; written by the summary pass as the states a
     // segment reaches from zero); dsum: (nseg, B*D) sum of time steps per segment.
     int nseg, seg_tiles;
@@ -47,7 +47,7 @@ struct FwdParams {
     float* ckpt;
     float* cum;
     // summary pass for a segmented backward pass (nullable): dout (B,D,L) in, and
-    // psi (nseg, B*D, N) out: the segment's summary of the right-to-left recurrence
+    // psi (nseg, N, B*D) out: the segment's summary of the right-to-left recurrence
     const void* dout;
     float* psi;
     // summary pass for window lengths that 16 is not a multiple of (nullable):
@@ -58,7 +58,7 @@ struct FwdParams {
     float* hT;
     // second pass of the path for window lengths without a compiled kernel: only
     // the local backward part, added to yprev; window is then the run-time window
-    // length and the grid has one block per (64 rows, seg_tokens logical steps)
+    // length and the grid has one block per (32 rows, seg_tokens logical steps)
     int generic_window;
     int seg_tokens;
 };
@@ -95,7 +95,8 @@ struct BwdParams {
     int nseg, seg_tiles;
     const float* cum;     // (ntiles, B*D): time-step sum from the segment start to the tile
     const float* carry;   // (nseg, N, B*D): forward state entering each segment (null: zeros)
-    const float* psi_in;  // (nseg, N, B*D): psi entering each segment from the right
+    const float* psi_in;  // (nseg, N, B*D): psi entering each segment from the right (null: zeros)
+                          // (rows not cut: both (B*D, N), as the caller holds them)
     const float* gck;     // (ntiles, N, B*D), nullable: abar_{t-1} gamma_{t-1} entering each tile
                           // (windows that straddle tile starts)
     float* dh0;           // (B*D, N), nullable: psi leaving the row on the left
@@ -173,8 +174,8 @@ hipError_t launch_zero_many(ZeroMany z, hipStream_t stream);
 // Whole backward pass: zero the accumulators, checkpoint pass, backward kernel,
 // conversion of dBm / dCm when the storage type is not fp32.  dBm / dCm are the
 // caller's outputs; workspace must hold bwd_workspace_bytes(f) bytes.  f.window is
-// any window length >= 1 (1, 2, 4 run with a compiled window structure, all others
-// with run-time window masks).
+// any window length >= 1 (1, 2, 4, 8, 16 run with a compiled window structure, all
+// others with run-time window masks).
 // saved (nullable): checkpoints left by launch_fwd on the same inputs.
 // dhT (nullable): gradient arriving at the state that leaves the row.
 hipError_t launch_bwd(const FwdParams& f, BwdParams p, void* dBm, void* dCm, void* workspace,

@@ -1,10 +1,10 @@
-// What the wave-tile kernels share: a wave owns 16 rows (channels of one batch entry) and
-// keeps a tile of them in LDS that no other wave reads, so that nothing but the shared
-// Bm / Cm tile needs a block barrier.
+// What the wave-tile kernels share: a wave owns R rows (channels of one batch entry: 8 in the
+// forward kernel, 16 in the backward one) and keeps a tile of them in LDS that no other wave
+// reads, so that nothing but the shared Bm / Cm tile needs a block barrier.
 //
 // Two layouts of the 64 lanes meet in a tile:
-//   staging:  lane = 4 * row + quad     four tokens of one row, as memory holds them
-//   scan:     lane = 16 * group + row   a quarter of the row's states, all its tokens
+//   staging:  lane = 64 / R * row + quad   four tokens of one row, as memory holds them
+//   scan:     lane = R * group + row       a share (1 in 64 / R) of the row's states, all its tokens
 #pragma once
 #include <type_traits>
 
@@ -12,8 +12,8 @@
 
 namespace lbscan {
 
-constexpr int kWaveRows = 16;                     // rows of a wave
 constexpr int kBlockWaves = 4;                    // waves of a block (they share Bm / Cm)
+constexpr int kWaveRows = 16;                     // backward kernel: rows of a wave
 constexpr int kBlockRows = kWaveRows * kBlockWaves;
 
 // LDS traffic between the lanes of one wave: the hardware keeps a wave's accesses in

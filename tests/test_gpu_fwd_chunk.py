@@ -69,7 +69,7 @@ def test_bf16_storage(lb, oracle, chunk_mapping):
 
 
 def test_bf16_rows_of_odd_length_fall_back(lb, oracle, chunk_mapping):
-    """Rows that start at odd bf16 elements allow no quad accesses: the row-per-lane
+    """Rows that start at odd bf16 elements allow no quad accesses: the wave-tile
     kernels take the call, with the same result."""
     from paper_2506_15976_amd.inputs import make_inputs
     s = make_inputs(1, 9, 16, 1501, seed=7310, dtype="bf16")
@@ -143,7 +143,7 @@ def test_two_pass_comparison_and_any_window_through_this_kernel(lb, oracle, chun
 
 def test_matches_row_per_lane_kernels_at_full_size(lb, oracle):
     """The 4096-token workload in the launch the library picks by itself (this kernel)
-    against the oracle, and against the row-per-lane path forced on the same inputs."""
+    against the oracle, and against the wave-tile path forced on the same inputs."""
     import torch
     from gpu_util import assert_close, fwd_inputs, to_device, to_numpy
     from paper_2506_15976_amd.inputs import WORKLOADS, make_workload
@@ -159,4 +159,4 @@ def test_matches_row_per_lane_kernels_at_full_size(lb, oracle):
     torch.cuda.synchronize()
     ref = oracle.fwd(**fwd_inputs(s), window=w["window"])
     assert_close(to_numpy(got), ref, w["dtype"], "chunk per lane")
-    assert_close(to_numpy(other), ref, w["dtype"], "row per lane")
+    assert_close(to_numpy(other), ref, w["dtype"], "wave tiles")
