@@ -42,6 +42,28 @@ size_t summary_bytes(const FwdParams& p, int nseg)
     return nseg <= 1 ? 0 : (carry_floats(p, nseg) + (size_t)nseg * p.batch * p.dim) * sizeof(float);
 }
 
+// Rows that the kernels gather token by token (a scan order without copies).  The summary launch
+// gathers x, delta and Bm a second time, which costs the more the less of the rows the caches
+// hold.  Measured on MI355X (us, uncut / cut; rows x tokens, MB of x):
+//   blocks  fp32                                     bf16
+//   96      2305, 28 MB  609 / 511                   4097, 25 MB  1222 / 822
+//   120     1601, 25 MB  480 / 405                   4097, 31 MB  1351 / 1135
+//   120     2305, 35 MB  693 / 755                   5185, 40 MB  1668 / 1917
+//   144     1025, 19 MB  364 / 334                   2305, 21 MB  722 / 647
+//   144     4097, 76 MB  1416 / 1941                 4097, 38 MB  1520 / 1819
+//   192     1025, 25 MB  470 / 525                   1601, 20 MB  564 / 547
+//   192     4097, 101 MB 1871 / 2553                 2305, 28 MB  882 / 997
+//   240     577, 18 MB   202 / 211                   1601, 25 MB  663 / 767
+//   336     401, 17 MB   150 / 162                   1025, 22 MB  525 / 595
+//   288     145          -                           145          32 / 36
+//   288     257          64 / 56                     401          93 / 77
+bool gather_cut_pays(const FwdParams& p, long nrb)
+{
+    if (p.seqlen <= 192) return nrb < 208;
+    const double bytes = (double)p.batch * p.dim * p.seqlen * (p.dtype == 0 ? 4 : 2);
+    return nrb < 120 || (nrb < 384 && nrb * bytes < 4.4e9);
+}
+
 // The forward kernels run one block per (32 rows, segment), six of them on a CU.  Rows that
 // cannot fill the chip are cut into segments scanned in parallel: a summary launch, the
 // carry chain, then the full pass started from the carried-in states.  That costs a second
@@ -65,13 +87,14 @@ size_t summary_bytes(const FwdParams& p, int nseg)
 // (The lines stand where neither direction and no window loses by them: reversed rows and window 1
 // gain from a cut a little further on.  At 384 blocks reversed fp32 rows off whole lines would gain 5 to 8% from a cut,
 // forward ones lose as much; the size of the scratch does not depend on the direction.)
-long cut_below(const FwdParams& p)
+bool cut_pays(const FwdParams& p, long nrb)
 {
     const int L = p.seqlen;
-    if (L <= 192) return 257;
-    if (L <= 256) return 336;
-    if (p.dtype == 0 || L <= 320) return L <= 1024 ? 360 : 384;
-    return L <= 1024 ? 390 : 410;
+    if (p.order.kind != 0) return gather_cut_pays(p, nrb);
+    if (L <= 192) return nrb < 257;
+    if (L <= 256) return nrb < 336;
+    if (p.dtype == 0 || L <= 320) return nrb < (L <= 1024 ? 360 : 384);
+    return nrb < (L <= 1024 ? 390 : 410);
 }
 
 // The summaries alone take 5.4 MB at most.  Beside a first pass's result they may not fit what
@@ -80,7 +103,7 @@ long cut_below(const FwdParams& p)
 Shape pick_shape(const FwdParams& p)
 {
     const long nrb = (long)((p.dim + 31) / 32) * p.batch;
-    const Shape s = cut_rows(p, nrb < cut_below(p) ? (2048 + nrb - 1) / nrb : 1);
+    const Shape s = cut_rows(p, cut_pays(p, nrb) ? (2048 + nrb - 1) / nrb : 1);
     if (p.beside + summary_bytes(p, s.nseg) <= LBSCAN_STATIC_SCRATCH_BYTES || p.beside > LBSCAN_STATIC_SCRATCH_BYTES) return s;
     const long nrb64 = (long)((p.dim + 63) / 64) * p.batch;
     const long coarse = nrb64 < 256 ? (768 + nrb64 - 1) / nrb64 : 1;
@@ -99,12 +122,15 @@ Shape pick_shape(const FwdParams& p)
 //   9216 rows, 197 tokens  27.7 / 29.3 -> 27.1 / 29.8    1536 rows, 576 tokens   21.9 / 21.7 -> 24.4 / 26.0
 //   12288 rows, 197 tokens 27.5 / 30.5 -> 33.9 / 36.9    64 rows, 50 tokens      15.7 / 15.7 -> 16.3 / 15.5
 //   1536 rows, 401 tokens  21.8 / 21.8 -> 17.9 / 20.6
+// Gathered rows pay more for the eightfold Bm and Cm (bf16, 145 tokens: 6144 rows 28.3 -> 23.9, 7680
+// rows 28.6 -> 33.3; 197 tokens, 7680 rows: 38.8 -> 33.2).
 Shape in_block_shape(const FwdParams& p)
 {
     const int ntiles = (p.seqlen + kFwdTileTokens - 1) / kFwdTileTokens;
     const long blocks = (long)((p.dim + 7) / 8) * p.batch;
     if (p.force_nseg >= 1 || ntiles < 3) return {0, 0};
-    if (blocks > (ntiles <= kInBlockSegments ? 1024 : ntiles <= 2 * kInBlockSegments ? 256 : 0)) return {0, 0};
+    const long most = p.order.kind != 0 && ntiles <= 5 ? 832 : 1024;
+    if (blocks > (ntiles <= kInBlockSegments ? most : ntiles <= 2 * kInBlockSegments ? 256 : 0)) return {0, 0};
     const int st = (ntiles + kInBlockSegments - 1) / kInBlockSegments;
     return {(ntiles + st - 1) / st, st};
 }

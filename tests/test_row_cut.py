@@ -20,3 +20,16 @@ def test_rows_are_cut_where_that_is_faster(B, D, L, fp32, bf16):
         assert (binding.lbscan_workspace_bytes(a, binding.WS_FWD) > 0) == cut
         a.reverse = 1                                       # one size for both directions
         assert (binding.lbscan_workspace_bytes(a, binding.WS_FWD) > 0) == cut
+
+
+@pytest.mark.parametrize("B, D, grid, fp32, bf16", [
+    (24, 384, (12, 12), False, False),                      # 288 row blocks, 145 tokens
+    (24, 384, (16, 16), True, True), (32, 384, (16, 16), False, False),
+    (12, 384, (32, 32), True, True), (16, 384, (32, 32), False, True), (18, 384, (32, 32), False, True),
+    (8, 384, (64, 64), True, True), (12, 384, (64, 64), False, False), (10, 384, (64, 64), False, True),
+])
+def test_gathered_rows_are_cut_where_that_is_faster(B, D, grid, fp32, bf16):
+    for dtype, cut in ((binding.LBSCAN_FP32, fp32), (binding.LBSCAN_BF16, bf16)):
+        a = binding.LbscanArgs(B, D, 16, grid[0] * grid[1] + 1, 4, dtype)
+        a.scan_order, (a.grid_h, a.grid_w) = binding.ORDER_COLUMNS, grid
+        assert (binding.lbscan_workspace_bytes(a, binding.WS_FWD) > 0) == cut
