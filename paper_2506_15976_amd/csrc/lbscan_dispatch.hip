@@ -57,11 +57,14 @@ size_t summary_bytes(const FwdParams& p, int nseg)
 //   336     401, 17 MB   150 / 162                   1025, 22 MB  525 / 595
 //   288     145          -                           145          32 / 36
 //   288     257          64 / 56                     401          93 / 77
+// (square grids; few rows or few columns keep more of the lines: 360 blocks of 4 x 256 tokens in bf16
+// 238 / 191)
 bool gather_cut_pays(const FwdParams& p, long nrb)
 {
     if (p.seqlen <= 192) return nrb < 208;
     const double bytes = (double)p.batch * p.dim * p.seqlen * (p.dtype == 0 ? 4 : 2);
-    return nrb < 120 || (nrb < 384 && nrb * bytes < 4.4e9);
+    const int side = p.order.H < p.order.W ? p.order.H : p.order.W;
+    return nrb < 120 || (nrb < 384 && (side < 16 || nrb * bytes < 4.4e9));
 }
 
 // The forward kernels run one block per (32 rows, segment), six of them on a CU.  Rows that
@@ -455,37 +458,37 @@ hipError_t launch_bwd(const FwdParams& f, BwdParams p, void* dBm, void* dCm, voi
 // of the rows the caches hold between tiles: rows of few bytes, grids of few rows or few
 // columns and small calls gather well.  Measured on MI355X (us, gather / copies):
 //   rows x tokens (grid)            forward fp32   forward bf16   backward fp32  backward bf16
-//   128 x 384, 50 (7 x 7)           29 / 46        34 / 48        116 / 125      118 / 121
-//   1042 x 384, 50 (7 x 7)          185 / 250      214 / 231      725 / 742      678 / 654
-//   88 x 384, 65 (8 x 8)            31 / 46        37 / 49        128 / 132      135 / 131
-//   127 x 384, 82 (9 x 9)           44 / 59        45 / 60        188 / 165      166 / 154
-//   103 x 384, 101 (10 x 10)        53 / 58        51 / 60        223 / 177      198 / 169
-//   72 x 384, 145 (12 x 12)         67 / 58        51 / 58        256 / 159      183 / 155
-//   90 x 384, 145 (12 x 12)         86 / 67        67 / 68        359 / 224      279 / 213
-//   29 x 384, 197 (14 x 14)         70 / 51        52 / 55        237 / 129      169 / 133
-//   106 x 384, 197 (14 x 14)        164 / 89       103 / 89       662 / 317      431 / 284
-//   132 x 384, 197 (14 x 14)        215 / 114      125 / 104      874 / 395      518 / 343
-//   128 x 768, 197 (14 x 14)        385 / 200      202 / 171      1517 / 651     904 / 563
-//   30 x 384, 257 (16 x 16)         76 / 62        59 / 63        309 / 146      220 / 145
-//   35 x 384, 257 (16 x 16)         82 / 60        61 / 61        396 / 167      271 / 162
-//   32 x 384, 325 (18 x 18)         124 / 66       82 / 66        438 / 177      268 / 166
-//   4 x 768, 1025 (32 x 32)         138 / 75       97 / 77        255 / 153      215 / 153
-//   768, 4096 (64 x 64)             105 / 88       105 / 90       219 / 172      234 / 176
-//   119 x 384, 197 (2 x 98)         92 / 103       101 / 94       359 / 341      360 / 295
-//   119 x 384, 197 (65 x 3)         122 / 102      102 / 94       395 / 338      354 / 294
-//   8 x 384, 1025 (4 x 256)         52 / 75        58 / 77        157 / 154      151 / 154
-//   30 x 384, 1025 (4 x 256)        242 / 181      191 / 171      642 / 460      618 / 431
-//   6 x 384, 1025 (8 x 128)         50 / 66        54 / 69        191 / 138      167 / 138
-//   8 x 384, 1025 (8 x 128)         60 / 76        61 / 78        178 / 154      168 / 152
-//   11 x 384, 1025 (8 x 128)        130 / 86       104 / 89       395 / 205      373 / 200
-//   3 x 384, 2049 (8 x 256)         58 / 71        57 / 75        216 / 150      197 / 155
-//   4 x 384, 2049 (8 x 256)         58 / 81        61 / 83        170 / 169      165 / 175
-// (The lines stand where the kernels before put them; on the wrong side are now, forward: fp32
-// at 8 x 128 and 8 x 256 below 4 million elements, at 72 x 384 x 145, bf16 at 106 x 384 x 197;
-// backward: fp32 at 2 x 98, by 5%.)
+//   128 x 384, 50 (7 x 7)           26 / 42        29 / 42        107 / 115      109 / 111
+//   1042 x 384, 50 (7 x 7)          172 / 236      193 / 219      703 / 731      669 / 648
+//   88 x 384, 65 (8 x 8)            28 / 44        34 / 46        124 / 127      129 / 125
+//   127 x 384, 82 (9 x 9)           42 / 56        43 / 57        181 / 162      162 / 150
+//   103 x 384, 101 (10 x 10)        51 / 56        49 / 57        220 / 175      194 / 164
+//   72 x 384, 145 (12 x 12)         65 / 57        48 / 56        253 / 161      179 / 151
+//   90 x 384, 145 (12 x 12)         85 / 66        65 / 66        355 / 222      274 / 210
+//   29 x 384, 197 (14 x 14)         68 / 46        50 / 46        234 / 129      161 / 128
+//   106 x 384, 197 (14 x 14)        160 / 90       100 / 85       657 / 317      427 / 283
+//   132 x 384, 197 (14 x 14)        212 / 114      121 / 102      869 / 394      517 / 341
+//   128 x 768, 197 (14 x 14)        387 / 196      197 / 169      1506 / 653     897 / 561
+//   30 x 384, 257 (16 x 16)         74 / 56        58 / 57        309 / 145      214 / 141
+//   35 x 384, 257 (16 x 16)         81 / 59        60 / 60        399 / 167      268 / 158
+//   32 x 384, 325 (18 x 18)         122 / 65       79 / 72        433 / 176      260 / 164
+//   4 x 768, 1025 (32 x 32)         160 / 73       96 / 72        264 / 151      211 / 150
+//   1 x 768, 4096 (64 x 64)         104 / 84       104 / 85       239 / 168      229 / 172
+//   119 x 384, 197 (2 x 98)         91 / 102       99 / 92        354 / 335      357 / 291
+//   119 x 384, 197 (65 x 3)         121 / 100      99 / 92        395 / 336      349 / 293
+//   8 x 384, 1025 (4 x 256)         50 / 72        56 / 72        148 / 150      148 / 148
+//   30 x 384, 1025 (4 x 256)        241 / 176      190 / 166      634 / 456      617 / 423
+//   6 x 384, 1025 (8 x 128)         48 / 62        54 / 64        188 / 133      169 / 134
+//   8 x 384, 1025 (8 x 128)         57 / 72        60 / 72        175 / 149      165 / 147
+//   11 x 384, 1025 (8 x 128)        130 / 83       103 / 85       394 / 206      371 / 196
+//   3 x 384, 2049 (8 x 256)         57 / 68        55 / 70        212 / 148      191 / 150
+//   4 x 384, 2049 (8 x 256)         55 / 77        59 / 77        169 / 165      158 / 168
+//   8 x 768, 4096 (64 x 64)         1872 / 378     1913 / 416     4210 / 945     3798 / 931
+// (The lines stand where the kernels before the wave tiles put them.  On the wrong side are now,
+// forward: fp32 at 8 x 128 and 8 x 256 below 4 million elements (they copy) and at 72 x 384 x 145,
+// bf16 at 106 x 384 x 197 (they gather); backward: fp32 at 2 x 98, by 5%.)
 // The copies ask for an fp32 result, which the chunk-per-lane kernel gives for bf16 only
-// with window 1: bf16 images of 4096 tokens run the wave-tile kernels here (8 x 768:
-// 2396 / 405).
+// with window 1: bf16 images of 4096 tokens run the wave-tile kernels here.
 namespace {
 
 // Elements of a (B,D,L) tensor from which the forward pass copies.  Never below 2^21:

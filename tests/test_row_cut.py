@@ -26,6 +26,7 @@ def test_rows_are_cut_where_that_is_faster(B, D, L, fp32, bf16):
     (24, 384, (12, 12), False, False),                      # 288 row blocks, 145 tokens
     (24, 384, (16, 16), True, True), (32, 384, (16, 16), False, False),
     (12, 384, (32, 32), True, True), (16, 384, (32, 32), False, True), (18, 384, (32, 32), False, True),
+    (30, 384, (4, 256), True, True),                        # few rows of the grid
     (8, 384, (64, 64), True, True), (12, 384, (64, 64), False, False), (10, 384, (64, 64), False, True),
 ])
 def test_gathered_rows_are_cut_where_that_is_faster(B, D, grid, fp32, bf16):
