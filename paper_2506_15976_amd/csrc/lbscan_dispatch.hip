@@ -61,7 +61,7 @@ size_t summary_bytes(const FwdParams& p, int nseg)
 // 238 / 191)
 bool gather_cut_pays(const FwdParams& p, long nrb)
 {
-    if (p.seqlen <= 192) return nrb < 208;
+    if (p.seqlen <= 160) return nrb < 208;
     const double bytes = (double)p.batch * p.dim * p.seqlen * (p.dtype == 0 ? 4 : 2);
     const int side = p.order.H < p.order.W ? p.order.H : p.order.W;
     return nrb < 120 || (nrb < 384 && (side < 16 || nrb * bytes < 4.4e9));
@@ -95,9 +95,25 @@ bool cut_pays(const FwdParams& p, long nrb)
     const int L = p.seqlen;
     if (p.order.kind != 0) return gather_cut_pays(p, nrb);
     if (L <= 192) return nrb < 257;
-    if (L <= 256) return nrb < 336;
+    if (L <= 256) return nrb < 348;
     if (p.dtype == 0 || L <= 320) return nrb < (L <= 1024 ? 360 : 384);
     return nrb < (L <= 1024 ? 390 : 410);
+}
+
+// Segments aimed at where rows are cut.  With at most eight states a lane has half the work for the
+// same launches, and long rows of few channels notice how the blocks fill the chip: whole rounds of
+// 1536 blocks, and no chain of more segments than one block of the chain kernel takes (256).
+// Measured on MI355X (us, fp32, N = 8, window 2; kernels before the wave tiles / 2048 blocks / this):
+//   4 blocks x 30000    45.5 / 47.4 / 41.2      12 blocks x 30000   85.3 / 90.5 / 82.7
+//   6 blocks x 20000    42.0 / 45.2 / 38.2      12 blocks x 65536   151 / 163 / 149
+//   8 blocks x 30000    63.2 / 67.0 / 60.3      16 blocks x 41432   146 / 165 / 148
+//   8 blocks x 65536    106 / 112 / 111         24 blocks x 30000   150 / 162 / 146
+// (Shorter rows, 16 x 14000 55.6 / 58.2 us, and 16 states gain at some lengths and lose at others.)
+long segments_wanted(const FwdParams& p, long nrb)
+{
+    if (p.dstate > 8 || nrb > 32 || p.seqlen < 20000) return (2048 + nrb - 1) / nrb;
+    const long want = (nrb <= 8 ? 1536 : 3072) / nrb;
+    return want < 256 ? want : 256;
 }
 
 // The summaries alone take 5.4 MB at most.  Beside a first pass's result they may not fit what
@@ -106,7 +122,7 @@ bool cut_pays(const FwdParams& p, long nrb)
 Shape pick_shape(const FwdParams& p)
 {
     const long nrb = (long)((p.dim + 31) / 32) * p.batch;
-    const Shape s = cut_rows(p, cut_pays(p, nrb) ? (2048 + nrb - 1) / nrb : 1);
+    const Shape s = cut_rows(p, cut_pays(p, nrb) ? segments_wanted(p, nrb) : 1);
     if (p.beside + summary_bytes(p, s.nseg) <= LBSCAN_STATIC_SCRATCH_BYTES || p.beside > LBSCAN_STATIC_SCRATCH_BYTES) return s;
     const long nrb64 = (long)((p.dim + 63) / 64) * p.batch;
     const long coarse = nrb64 < 256 ? (768 + nrb64 - 1) / nrb64 : 1;
@@ -160,14 +176,14 @@ Shape pick_bwd_shape(const FwdParams& p)
 
 // The chunk-per-lane kernel (one wave per row, 1024-token chunks, one launch; 768 blocks of four rows
 // in flight) against the wave-tile kernels (rows cut where that is faster), measured on MI355X
-// (us, wave tiles / chunk; fp32 with window 4, bf16 with window 8).  Whole chunks:
+// (us, wave tiles / chunk; fp32 with window 4, bf16 with window 8; 16 states).  Whole chunks:
 //   rows x tokens      fp32           bf16           rows x tokens      fp32           bf16
 //   192 x 1024         20.7 / 16.6    21.6 / 14.6    1536 x 4096        65.5 / 72.5    68.3 / 63.9
 //   3072 x 1024        36.7 / 26.2    40.2 / 22.6    3072 x 4096        109 / 88.1     118 / 80.7
 //   12288 x 1024       105 / 87.3     119 / 75.8     6144 x 4096        214 / 183      218 / 150
 //   24576 x 1024       145 / 188      148 / 143      12288 x 4096       425 / 366      508 / 313
 //   1536 x 2048        39.2 / 38.7    40.3 / 33.1    16128 x 2048       213 / 240      251 / 193
-// A chunk that the row does not fill takes its loads element by element, in every state:
+// A chunk that the row does not fill takes its loads element by element, in every state,
 //   192 x 900          19.9 / 22.4    20.8 / 24.1    3072 x 2000        64.8 / 58.2    67.5 / 57.5
 //   768 x 1020         21.0 / 23.2    21.1 / 24.1    6144 x 1700        95.6 / 103     105 / 104
 //   1920 x 1020        32.2 / 30.8    32.3 / 27.3    6144 x 5000        264 / 265      268 / 217
@@ -176,8 +192,12 @@ Shape pick_bwd_shape(const FwdParams& p)
 //   3456 x 960         41.3 / 58.4    44.0 / 57.2    12288 x 4000       398 / 412      513 / 388
 //   6144 x 1000        62.4 / 71.1    67.6 / 73.0    16128 x 2000       209 / 327      252 / 290
 //   16128 x 960        100 / 185      115 / 190      2688 x 2700        78.4 / 73.1    77.4 / 74.2
+// and less so with fewer states, while a wave tile has lanes for 8 or 16 of them (rows x tokens x N):
+//   192 x 1000 x 12    20.1 / 19.2    21.2 / 20.0    192 x 1000 x 5     16.3 / 12.7    17.2 / 12.8
+//   6144 x 1000 x 12   61.1 / 60.8    66.7 / 61.0    768 x 1000 x 8     15.4 / 16.0    16.4 / 16.1
+//   14592 x 1700 x 8   145 / 191      167 / 157      14592 x 1000 x 8   85.8 / 117     101 / 115
 // It needs chunks that are mostly full, and rows enough for a wave each unless a row is one whole
-// chunk; a row of one ragged chunk pays where the rows about fill one round of blocks (3072).  With fp32
+// chunk; of 13 to 16 states a row of one ragged chunk pays where the rows about fill one round of blocks (3072).  With fp32
 // storage (four rows share a staged Bm / Cm chunk, so those reads are twice the row reads) it loses
 // where the wave tiles fill the chip without cutting rows, with ragged chunks beyond two rounds.
 // (On the wrong side: bf16 rows of two ragged chunks around 1536 and 3456 rows and from 14592 rows on.)
@@ -195,10 +215,12 @@ bool use_chunk_mapping(const FwdParams& p, const float* saved)
     const long chunk = 1024, nchunks = (p.seqlen + chunk - 1) / chunk;
     const bool ragged = p.seqlen % chunk != 0;
     if (p.seqlen * 5 < nchunks * chunk * 4) return false;             // chunks less than 80% full
-    if (ragged && nchunks == 1) return rows > 1536 && rows <= 3072;
+    if (ragged && p.dstate > 12) {
+        if (nchunks == 1) return rows > 1536 && rows <= 3072;
+        if (p.dtype == 0) return rows <= 6144 && (rows >= 3072 || (nchunks == 2 && rows > 1536));
+    }
     if (p.dtype != 0) return nchunks == 1 || rows >= 1536;
-    if (ragged) return rows <= 6144 && (rows >= 3072 || (nchunks == 2 && rows > 1536));
-    return rows <= 16384 && (nchunks == 1 || rows >= 3072 || (nchunks == 2 && rows >= 1536));
+    return rows <= (ragged && p.dstate > 4 ? 12288 : 16384) && (nchunks == 1 || rows >= 3072 || (nchunks == 2 && rows >= 1536));
 }
 
 }  // namespace

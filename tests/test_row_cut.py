@@ -7,7 +7,7 @@ from paper_2506_15976_amd import binding
 
 @pytest.mark.parametrize("B, D, L, fp32, bf16", [
     (24, 384, 160, False, False),                           # 288 row blocks of 32
-    (27, 384, 197, True, True), (28, 384, 197, False, False), (336, 32, 256, False, False),
+    (28, 384, 197, True, True), (29, 384, 197, False, False), (348, 32, 256, False, False),
     (29, 384, 300, True, True), (30, 384, 300, False, False),
     (29, 384, 400, True, True), (30, 384, 400, False, True), (32, 384, 700, False, True), (33, 384, 700, False, False),
     (31, 384, 1601, True, True), (32, 384, 1601, False, True), (64, 176, 1601, False, True),
