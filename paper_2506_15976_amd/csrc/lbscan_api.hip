@@ -104,7 +104,7 @@ lbscan::FwdParams to_params(const lbscan_args* a, int window)
     p.force_nseg = tuning_nseg();
     p.beside = 0;
     p.force_mapping = g_mapping.load(std::memory_order_relaxed);
-    p.nseg = 1; p.seg_tiles = 0; p.in_block = 0; p.summary_only = 0; p.fold_chain = 0; p.carry = nullptr; p.dsum = nullptr;
+    p.nseg = 1; p.seg_tiles = 0; p.seg_step = 0; p.in_block = 0; p.summary_only = 0; p.fold_chain = 0; p.carry = nullptr; p.dsum = nullptr;
     p.ckpt = nullptr; p.cum = nullptr; p.dout = nullptr; p.psi = nullptr; p.gck = nullptr;
     p.h0 = a->h0; p.hT = a->hT;
     p.generic_window = 0; p.seg_tokens = 0;

@@ -36,6 +36,7 @@ struct FwdParams {
     // segment (read by the full pass; written by the summary pass as the states a
     // segment reaches from zero); dsum: (nseg, B*D) sum of time steps per segment.
     int nseg, seg_tiles;
+    int seg_step;         // blocks from one segment to the next in the grid (set by the launcher)
     int in_block;         // full pass, at most kInBlockSegments segments: they are the waves of a block
     int summary_only;
     int fold_chain;       // full pass: fold the chain over the summaries in the kernel

@@ -289,3 +289,18 @@ def test_copies_with_room_behind_their_rows(lb, oracle, dtype, B, grid):
     s = make_inputs(B, D, N, L, seed=9700 + L, dtype=dtype, with_dout=True)
     for reverse in (False, True):
         _check(lb, oracle, s, grid, window=4, dtype=dtype, reverse=reverse)
+
+
+@pytest.mark.parametrize("dim", [220, 400, 480, 560])
+@pytest.mark.parametrize("batch, segments", [(1, 3), (3, 2)])
+def test_gathered_rows_in_segments(lb, oracle, route, batch, segments, dim):
+    """Row blocks that are padded to whole rounds of the XCDs, or not (7 to 54 of them), without
+    copies: the forward call, and the summary pass of the backward one."""
+    from paper_2506_15976_amd.inputs import make_inputs
+    route(False)
+    s = make_inputs(batch, dim, 5, 91, seed=9800 + dim, with_dout=True, random_A=True)
+    lb.lbscan_set_option("segments", segments)
+    try:
+        _check(lb, oracle, s, (9, 10, 1), window=4, reverse=bool(batch & 2))
+    finally:
+        lb.lbscan_set_option("segments", 0)
