@@ -191,7 +191,8 @@ def make_args(x, delta, A, Bm, Cm, Dskip=None, z=None, delta_bias=None, *, windo
     try:
         packed = _ARGS_LAYOUT.pack(
             Bsz, D, N, L, ctypes.c_int32(int(window)).value, code, int(bool(delta_softplus)), int(bool(reverse)),
-            x.data_ptr(), _address(delta), _address(Bm), _address(Cm), _address(z), A.data_ptr(), _address(Dskip),
+            x.data_ptr(), 0 if delta is None else delta.data_ptr(), 0 if Bm is None else Bm.data_ptr(),
+            0 if Cm is None else Cm.data_ptr(), _address(z), A.data_ptr(), _address(Dskip),
             _address(delta_bias), _address(y), _address(workspace),
             0 if workspace is None else workspace.numel() * workspace.element_size(), _address(saved_state),
             0 if saved_state is None else saved_state.numel() * saved_state.element_size(),
