@@ -43,7 +43,7 @@ struct FwdParams {
     float* carry;         // nullable when nseg == 1
     float* dsum;
     // summary pass only: per-tile checkpoints for the backward pass (nullable):
-    // ckpt (ntiles, N, B*D) state at the start of each tile, cum (ntiles, B*D)
+    // ckpt (ntiles, B*D, N, see kCkptRows) state at the start of each tile, cum (ntiles, B*D)
     // time-step sum up to there, both counted from the start of the segment
     float* ckpt;
     float* cum;
@@ -90,7 +90,7 @@ struct BwdParams {
     float* dA;            // (D,N) zeroed
     float* dDskip;        // (D) zeroed, nullable
     float* dbias;         // (D) zeroed, nullable
-    const float* ckpt;    // (ntiles, N, B*D): f at the first step of every tile, counted
+    const float* ckpt;    // (ntiles, B*D, N, see kCkptRows): f at the first step of every tile, counted
                           // from the start of the tile's segment
     // rows cut into nseg segments of seg_tiles backward tiles (16 tokens each):
     int nseg, seg_tiles;
@@ -126,6 +126,10 @@ constexpr int kTileTokens = LBSCAN_BWD_TILE;      // tokens per tile of the back
 #define LBSCAN_FWD_TILE 32
 #endif
 constexpr int kFwdTileTokens = LBSCAN_FWD_TILE;   // tokens per tile of the forward kernel (32: 128 bytes of an fp32 row)
+
+// Checkpoints of f are kept by groups of rows of a batch entry, (tile, group, n, row of the group); the
+// last group of an entry holds the rows that are left.
+constexpr int kCkptRows = 8;
 
 // Segments of a row that one block takes (FwdParams::in_block).
 constexpr int kInBlockSegments = 8;

@@ -30,6 +30,14 @@ __device__ __forceinline__ void lds_get4(const float* a, int o, float (&v)[4])
     const float4 q = *reinterpret_cast<const float4*>(a + o);
     v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
 }
+__device__ __forceinline__ void lds_get8(const float* a, int o, float (&v)[8])
+{
+    float lo[4], hi[4];
+    lds_get4(a, o, lo);
+    lds_get4(a, o + 4, hi);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { v[e] = lo[e]; v[4 + e] = hi[e]; }
+}
 __device__ __forceinline__ void lds_put4(float* a, int o, const float (&v)[4])
 {
     *reinterpret_cast<float4*>(a + o) = make_float4(v[0], v[1], v[2], v[3]);
@@ -40,14 +48,20 @@ __device__ __forceinline__ void lds_put4(float* a, int o, const float (&v)[4])
 //   unaligned: the same for 2-byte rows that start at odd elements: the three aligned
 //              words around a quad
 //   clamped:   the ragged last tile: whole quads from the nearest position inside the row
+//   tail:      a short last tile of the forward kernel: one token a lane
 //   elements:  element by element (scan orders that gather, short and odd ragged rows)
-enum class TileLoads { quads, unaligned, clamped, elements };
+enum class TileLoads { quads, unaligned, clamped, tail, elements };
 
 // A quad as loaded.  Nothing touches it before it is needed: a conversion, or the shift of
 // unaligned words, at the load would make the wave wait for it there.
+// (Vectors: of single elements the compiler makes copies where ways of loading meet, and waits
+// for the load to make them.)
+typedef float Float4 __attribute__((ext_vector_type(4)));
+typedef uint32_t Word3 __attribute__((ext_vector_type(3)));
+typedef Float4 Float4At4 __attribute__((aligned(4)));        // at any 4-byte address
 template <typename T> struct HeldQuad;
-template <> struct HeldQuad<float> { Quad<float> q; };
-template <> struct HeldQuad<bf16_t> { Words3 w; };
+template <> struct HeldQuad<float> { Float4 q; };
+template <> struct HeldQuad<bf16_t> { Word3 w; };
 
 struct __attribute__((packed, aligned(4))) Words2 { uint32_t v[2]; };
 
@@ -64,24 +78,34 @@ __device__ __forceinline__ T* at_bytes(T* base, unsigned bytes)
     return reinterpret_cast<T*>(reinterpret_cast<char*>(base) + bytes);
 }
 
-__device__ __forceinline__ void hold_quad(HeldQuad<float>& h, const float* p) { h.q = *reinterpret_cast<const Quad<float>*>(p); }
+__device__ __forceinline__ void hold_quad(HeldQuad<float>& h, const float* p) { h.q = *reinterpret_cast<const Float4At4*>(p); }
 __device__ __forceinline__ void hold_quad(HeldQuad<bf16_t>& h, const bf16_t* p)
 {
     const Words2 w = *reinterpret_cast<const Words2*>(p);
-    h.w.v[0] = w.v[0]; h.w.v[1] = w.v[1]; h.w.v[2] = 0u;
+    Word3 v;                                          // (the third word is not looked at: shift 0)
+    v[0] = w.v[0]; v[1] = w.v[1];
+    h.w = v;
 }
 __device__ __forceinline__ void hold_unaligned(HeldQuad<float>& h, const float* p) { hold_quad(h, p); }
 __device__ __forceinline__ void hold_unaligned(HeldQuad<bf16_t>& h, const bf16_t* p)
 {
-    h.w = *reinterpret_cast<const Words3*>(p - ((reinterpret_cast<uintptr_t>(p) >> 1) & 1));
+    const Words3 w = *reinterpret_cast<const Words3*>(p - ((reinterpret_cast<uintptr_t>(p) >> 1) & 1));
+    h.w = Word3{w.v[0], w.v[1], w.v[2]};
 }
-__device__ __forceinline__ void hold_elements(HeldQuad<float>& h, const Quad<float>& q) { h.q = q; }
+__device__ __forceinline__ void hold_elements(HeldQuad<float>& h, const Quad<float>& q) { h.q = Float4{q.v[0], q.v[1], q.v[2], q.v[3]}; }
 __device__ __forceinline__ void hold_elements(HeldQuad<bf16_t>& h, const Quad<bf16_t>& q)
 {
-    h.w.v[0] = (uint32_t)q.v[0].bits | ((uint32_t)q.v[1].bits << 16);
-    h.w.v[1] = (uint32_t)q.v[2].bits | ((uint32_t)q.v[3].bits << 16);
-    h.w.v[2] = 0u;
+    h.w = Word3{(uint32_t)q.v[0].bits | ((uint32_t)q.v[1].bits << 16), (uint32_t)q.v[2].bits | ((uint32_t)q.v[3].bits << 16), 0u};
 }
+// The quad is waited for here, on every path that may have loaded it.
+__device__ __forceinline__ void arrived(const HeldQuad<float>& h) { asm volatile("" : : "v"(h.q)); }
+__device__ __forceinline__ void arrived(const HeldQuad<bf16_t>& h) { asm volatile("" : : "v"(h.w)); }
+
+// One element, first in the quad (tail).
+__device__ __forceinline__ void hold_element(HeldQuad<float>& h, const float* p) { Float4 v; v[0] = *p; h.q = v; }
+__device__ __forceinline__ void hold_element(HeldQuad<bf16_t>& h, const bf16_t* p) { Word3 v; v[0] = p->bits; h.w = v; }
+__device__ __forceinline__ float open_element(const HeldQuad<float>& h) { return h.q[0]; }
+__device__ __forceinline__ float open_element(const HeldQuad<bf16_t>& h) { return __uint_as_float(h.w[0] << 16); }
 
 // The four elements in 32 bits, in logical order (REV: the stored order mirrored).  shift:
 // 16 where the quad was held unaligned at an odd element, else 0 (2-byte types).
@@ -89,13 +113,13 @@ template <bool REV>
 __device__ __forceinline__ void open_quad(const HeldQuad<float>& h, unsigned, float (&v)[4])
 {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[REV ? 3 - e : e] = h.q.v[e];
+    for (int e = 0; e < 4; ++e) v[REV ? 3 - e : e] = h.q[e];
 }
 template <bool REV>
 __device__ __forceinline__ void open_quad(const HeldQuad<bf16_t>& h, unsigned shift, float (&v)[4])
 {
-    const uint32_t lo = __builtin_amdgcn_alignbit(h.w.v[1], h.w.v[0], shift);
-    const uint32_t hi = __builtin_amdgcn_alignbit(h.w.v[2], h.w.v[1], shift);
+    const uint32_t lo = __builtin_amdgcn_alignbit(h.w[1], h.w[0], shift);
+    const uint32_t hi = __builtin_amdgcn_alignbit(h.w[2], h.w[1], shift);
     v[REV ? 3 : 0] = __uint_as_float(lo << 16);
     v[REV ? 2 : 1] = __uint_as_float(lo & 0xffff0000u);
     v[REV ? 1 : 2] = __uint_as_float(hi << 16);

@@ -44,6 +44,35 @@ def test_outputs_at_the_edges_of_a_tile(oracle, shape, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("tokens", [39, 40, 41, 69, 72, 104, 105])
+def test_a_short_last_tile(oracle, tokens, dtype):
+    """Rows whose last tile holds seven to nine tokens (up to eight are staged one a lane, beyond
+    that a quad a lane), whole, cut and in the summary of a cut backward pass."""
+    import numpy as np
+    import torch
+    import paper_2506_15976_amd as lb
+    from gpu_util import assert_close, fwd_inputs, to_device, to_numpy
+    from paper_2506_15976_amd.inputs import make_inputs
+    for D, N in ((13, 16), (40, 7)):
+        s = make_inputs(2, D, N, tokens, seed=9700 + D + tokens, dtype=dtype, random_A=True, with_dout=True)
+        h0 = np.random.default_rng(D).standard_normal((2, D, N)).astype(np.float32)
+        dev = to_device(s, dtype)
+        for segments in (1, 2):
+            lb.lbscan_set_option("segments", segments)
+            try:
+                for window, reverse in ((4, False), (8, True), (16, False), (16, True), (6, True)):
+                    _check(lb, oracle, s, dtype, window, reverse, h0)
+                for window in (4, 6):
+                    got = lb.lbscan_bwd(**fwd_inputs(dev), dout=dev["dout"], window=window)
+                    torch.cuda.synchronize()
+                    ref = oracle.bwd(**fwd_inputs(s), dout=s["dout"], window=window)
+                    for k in ("dx", "ddelta", "dz", "dBm", "dCm", "dA"):
+                        assert_close(to_numpy(got[k]), ref[k], dtype, f"{k} window {window} segments {segments}")
+            finally:
+                lb.lbscan_set_option("segments", 0)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("shape", [(1, 5, 16, 1024), (2, 3, 7, 820), (1, 200, 16, 1000), (1, 1537, 5, 822)])
 def test_rows_of_one_chunk(oracle, shape, dtype):
     """Rows of 820 to 1024 tokens, which the library hands to one family or the other: its own
