@@ -210,4 +210,26 @@ __device__ __forceinline__ float groups_sum4(const float (&v)[4])
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// Sums over eight state groups (bits 1 to 3 of the lane) of four values per lane: the lanes with
+// s in bits 2 and 3 end with the sum of value s.  Halving steps as in row16_sum8, within a row
+// of lanes throughout: a DPP add takes half the time of a swap between rows (4 and 8 clocks a
+// wave; a plain add 2).
+__device__ __forceinline__ float groups8_sum4(float (&v)[4])
+{
+    asm volatile(
+        "s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %1, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %0, %2, %2 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %1, %3, %3 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "s_nop 0\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_ror:12 row_mask:0xf bank_mask:0x5\n\t"
+        "v_add_f32_dpp %0, %1, %1 row_ror:4 row_mask:0xf bank_mask:0xa\n\t"
+        "s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf"
+        : "+&v"(v[0]), "+&v"(v[1])
+        : "v"(v[2]), "v"(v[3]));
+    return v[0];
+}
+
 }  // namespace lbscan
