@@ -27,8 +27,8 @@
 // lane ends up with its own 16 tokens; y goes back the same way.
 #include <type_traits>
 
-#include "lbscan_device.h"
 #include "lbscan_internal.h"
+#include "lbscan_wave_tile.h"
 
 namespace lbscan {
 namespace {
@@ -44,19 +44,6 @@ constexpr int kChunk = 64 * kP;        // tokens per wave and chunk
 constexpr int kR = LBSCAN_CHUNK_ROWS;  // rows (waves) per block
 constexpr int kPitch = kP + 4;         // LDS pitch of a lane's tokens (16-byte reads, see lbscan_bwd_wave.inc)
 constexpr int kBuf = 64 * kPitch;      // floats of one staged chunk
-
-__device__ __forceinline__ void lds_get4(const float* a, int o, float (&v)[4])
-{
-    const float4 q = *reinterpret_cast<const float4*>(a + o);
-    v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-}
-
-__device__ __forceinline__ void wave_sync_lds()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // v of the lane that the DPP control names; `old` in lanes that have no such lane or
 // that the row mask leaves out.
@@ -93,8 +80,9 @@ __device__ __forceinline__ void wave_scan_affine(float& P, float& e)
 // Quad q (tokens 4q .. 4q+3 of the chunk) lands where lane q / 4 reads its tokens from.
 __device__ __forceinline__ int quad_slot(int q) { return (q >> 2) * kPitch + 4 * (q & 3); }
 
-// Four quads of a row tensor of element type U, as loaded (lane l: quads l, l+64, ...).
-template <typename U> struct RowQuads { Quad<U> q[4]; };
+// Four quads of a row tensor of element type U, as loaded (lane l: quads l, l+64, ...).  Nothing
+// unpacks or mirrors them before they are needed.
+template <typename U> struct RowQuads { HeldQuad<U> q[4]; };
 
 // TY: element type of y (the storage type, or float for the first pass of the two-pass
 // global bi-directional scan, which leaves its ungated result in fp32).
@@ -141,37 +129,36 @@ chunk_fwd_kernel(const FwdParams p)
     // Bm / Cm staging: the 256 quads of each are spread over the block's threads
     constexpr int kBCQ = 256 / (64 * kR) > 0 ? 256 / (64 * kR) : 1;   // quads per thread and tensor
     static_assert(64 * kR * kBCQ == 256, "one block stages a chunk of Bm and Cm");
-    struct BCQuads { Quad<T> q[2][kBCQ]; };
-    // (whether a chunk lies inside the row is decided once per chunk, for all lanes:
-    // per-quad checks would put every load behind a branch of its own)
+    struct BCQuads { HeldQuad<T> q[2][kBCQ]; };
+    // (whether a chunk lies inside the row is decided once for all loads that go out together: a
+    // check for every quad puts every load behind a branch of its own.  That, quads held as vectors
+    // until they are used, and x fetched earlier, us: 8 x 768 x 16 x 4096 bf16 window 8 156.3 -> 153.6, reversed
+    // 164 -> 152, fp32 window 4 182 -> 168, 5000 tokens 256 -> 234)
     auto chunk_is_whole = [&](int chunk) { return (chunk + 1) * kChunk <= L; };
     // The quad of logical tokens t0 .. t0+3 of a row tensor.  REV: logical token t is the
     // stored token L-1-t (the scan runs over the reversed sequence), i.e. the stored
     // quad that ends at L-t0, its elements in opposite order.
-    auto fetch_quad = [&](const auto* src, int t0, bool whole) {
+    auto fetch_quad = [&](const auto* src, int t0, bool whole, auto& h) __attribute__((always_inline)) {
         using U = std::remove_cv_t<std::remove_pointer_t<decltype(src)>>;
         const int ph = REV ? L - 4 - t0 : t0;
-        Quad<U> q;
-        if (whole) q = quad_raw_fast<U>(src, ph);
-        else q = quad_raw_checked<U>(src, ph, ph, L);
-        if (REV) {
-            const U a = q.v[0], b2 = q.v[1];
-            q.v[0] = q.v[3]; q.v[1] = q.v[2]; q.v[2] = b2; q.v[3] = a;
-        }
-        return q;
+        if (whole) hold_quad(h, src + ph);
+        else hold_elements(h, quad_raw_checked<U>(src, ph, ph, L));
     };
     auto load_bc = [&](int chunk, int n) {
         BCQuads r;
-        const bool whole = chunk_is_whole(chunk);
+        auto fetch = [&](bool whole) __attribute__((always_inline)) {
 #pragma unroll
-        for (int w = 0; w < 2; ++w) {
-            const T* src = (w ? Cg : Bg) + (long)n * LP;
+            for (int w = 0; w < 2; ++w) {
+                const T* src = (w ? Cg : Bg) + (long)n * LP;
 #pragma unroll
-            for (int j = 0; j < kBCQ; ++j) {
-                const int t0 = chunk * kChunk + 4 * (tid + 64 * kR * j);
-                r.q[w][j] = fetch_quad(src, t0, whole);
+                for (int j = 0; j < kBCQ; ++j) {
+                    const int t0 = chunk * kChunk + 4 * (tid + 64 * kR * j);
+                    fetch_quad(src, t0, whole, r.q[w][j]);
+                }
             }
-        }
+        };
+        if (chunk_is_whole(chunk)) fetch(true);
+        else fetch(false);
         return r;
     };
     auto put_bc = [&](int buf, const BCQuads& r) {
@@ -179,9 +166,9 @@ chunk_fwd_kernel(const FwdParams p)
         for (int w = 0; w < 2; ++w)
 #pragma unroll
             for (int j = 0; j < kBCQ; ++j) {
-                const Quad<T>& q = r.q[w][j];
-                *reinterpret_cast<float4*>(&sBC[buf][w][quad_slot(tid + 64 * kR * j)]) =
-                    make_float4(to_f32(q.v[0]), to_f32(q.v[1]), to_f32(q.v[2]), to_f32(q.v[3]));
+                float v[4];
+                open_quad<REV>(r.q[w][j], 0u, v);
+                lds_put4(sBC[buf][w], quad_slot(tid + 64 * kR * j), v);
             }
     };
     // one row tensor of the chunk: coalesced quads (issue_row), turned through the
@@ -189,21 +176,26 @@ chunk_fwd_kernel(const FwdParams p)
     auto issue_row = [&](const auto* src, int chunk) {
         using U = std::remove_cv_t<std::remove_pointer_t<decltype(src)>>;
         RowQuads<U> r;
-        const bool whole = chunk_is_whole(chunk);
+        auto fetch = [&](bool whole) __attribute__((always_inline)) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int t0 = chunk * kChunk + 4 * (lane + 64 * j);
-            r.q[j] = fetch_quad(src, t0, whole);
-        }
+            for (int j = 0; j < 4; ++j) {
+                const int t0 = chunk * kChunk + 4 * (lane + 64 * j);
+                fetch_quad(src, t0, whole, r.q[j]);
+            }
+        };
+        if (chunk_is_whole(chunk)) fetch(true);
+        else fetch(false);
         return r;
     };
     auto turn_row = [&](const auto& r, float (&out)[kP]) {
-        wave_sync_lds();                              // earlier readers of wbuf are done
+        wave_lds_fence();                              // earlier readers of wbuf are done
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            *reinterpret_cast<float4*>(&wbuf[quad_slot(lane + 64 * j)]) =
-                make_float4(to_f32(r.q[j].v[0]), to_f32(r.q[j].v[1]), to_f32(r.q[j].v[2]), to_f32(r.q[j].v[3]));
-        wave_sync_lds();
+        for (int j = 0; j < 4; ++j) {
+            float v[4];
+            open_quad<REV>(r.q[j], 0u, v);
+            lds_put4(wbuf, quad_slot(lane + 64 * j), v);
+        }
+        wave_lds_fence();
 #pragma unroll
         for (int g = 0; g < kP / 4; ++g) {
             float v[4];
@@ -217,10 +209,10 @@ chunk_fwd_kernel(const FwdParams p)
     put_bc(0, load_bc(0, 0));
     __syncthreads();
 
-    // the time steps of a chunk are fetched during the last state of the chunk before
-    // and its x while that chunk's result is stored; z during the chunk's own last state
-    // (fp32 quads are twice the registers: there the time steps wait for the store phase too)
-    constexpr bool kEarlyDt = sizeof(T) == 2;
+    // the time steps and x of a chunk are fetched during the last state of the chunk before, z
+    // during the chunk's own last state (fp32 quads are twice the registers: there the first two wait
+    // for the store phase)
+    constexpr bool kEarly = sizeof(T) == 2;
     RowQuads<T> qd = issue_row(dg, 0), qx = issue_row(xg, 0), qz;
     for (int chunk = 0; chunk < nchunks; ++chunk) {
         const int t_lane = chunk * kChunk + lane * kP;          // this lane's first token
@@ -257,7 +249,9 @@ chunk_fwd_kernel(const FwdParams p)
             if (more) nxt = n + 1 < N ? load_bc(chunk, n + 1) : load_bc(chunk + 1, 0);
             if constexpr (LAST) {
                 if (zg) qz = issue_row(zg, chunk);
-                if constexpr (kEarlyDt) { if (chunk + 1 < nchunks) qd = issue_row(dg, chunk + 1); }
+                if constexpr (kEarly) {
+                    if (chunk + 1 < nchunks) { qd = issue_row(dg, chunk + 1); qx = issue_row(xg, chunk + 1); }
+                }
             }
 
             if (row_ok) {
@@ -339,15 +333,14 @@ chunk_fwd_kernel(const FwdParams p)
 #pragma unroll
             for (int k = 0; k < kP; ++k) y[k] *= zv[k] * sigmoid_f32(zv[k]);
         }
-        wave_sync_lds();
+        wave_lds_fence();
 #pragma unroll
         for (int g = 0; g < kP / 4; ++g)
             *reinterpret_cast<float4*>(&wbuf[lane * kPitch + 4 * g]) =
                 make_float4(y[4 * g], y[4 * g + 1], y[4 * g + 2], y[4 * g + 3]);
-        wave_sync_lds();
-        if (chunk + 1 < nchunks) {
-            if constexpr (!kEarlyDt) qd = issue_row(dg, chunk + 1);
-            qx = issue_row(xg, chunk + 1);
+        wave_lds_fence();
+        if constexpr (!kEarly) {
+            if (chunk + 1 < nchunks) { qd = issue_row(dg, chunk + 1); qx = issue_row(xg, chunk + 1); }
         }
         if (row_ok) {
             const bool whole = chunk_is_whole(chunk);
@@ -367,7 +360,7 @@ chunk_fwd_kernel(const FwdParams p)
         }
     }
     if (p.hT && row_ok) {
-        wave_sync_lds();
+        wave_lds_fence();
         if (lane < N) p.hT[((long)b * D + d) * N + lane] = scar[wv][lane];
     }
 }
