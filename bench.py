@@ -26,10 +26,11 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBPS = 8000.0          # MI355X HBM3E, published
-# Plain (unpacked) fp32 VALU issue: 256 CUs x 64 lanes x 2.4 GHz; packed FP32 is off by
-# build rule, so the 157.3 TFLOP/s figure (packed FMA) does not apply.  v_exp_f32 issues
-# at half rate on this chip (measured: 19.2 T/s against 38.6 T/s for fma, and the two do
-# not overlap), i.e. it takes two issue slots.
+# fp32 VALU slots of four clocks a wave instruction: 256 CUs x 64 lanes x 2.4 GHz.  That is what
+# compares, selects, shifts and DPP take (measured 4.2 clocks; v_exp_f32 8.2, two slots) and
+# about what a plain add, mul or fma takes of a wave alone (4.9); plain ones of several waves overlap down to
+# 2.3 clocks.  So the slots compare kernels of one kind with each other, and a kernel of
+# plain instructions only could pass this peak.
 VALU_PEAK_LANE_OPS = 256 * 64 * 2.4e9
 FWD_KEYS = ("x", "delta", "A", "Bm", "Cm", "Dskip", "z", "delta_bias")
 
@@ -88,9 +89,9 @@ def alu_bound(su_per_s, window, workload=None):
             "peak_lane_ops_per_s": VALU_PEAK_LANE_OPS,
             "slots_per_state_update_measured": measured,
             "frac_at_measured_slots": None if measured is None else su_per_s * measured / VALU_PEAK_LANE_OPS,
-            "note": "fp32 VALU issue bound (unpacked, 256 CUs x 64 lanes x 2.4 GHz) at the "
-                    "algorithmic slots per state update; the measured-slots figure is how busy "
-                    "the kernel as built keeps the VALUs"}
+            "note": "fp32 VALU slots of four clocks (256 CUs x 64 lanes x 2.4 GHz) at the "
+                    "algorithmic slots per state update; plain instructions of several waves can "
+                    "overlap, so both fractions compare kernels and are no end"}
 
 
 def algorithmic_bytes(w, which="fwd"):

@@ -67,7 +67,7 @@ bool gather_cut_pays(const FwdParams& p, long nrb)
     return nrb < 120 || (nrb < 384 && (side < 16 || nrb * bytes < 4.4e9));
 }
 
-// The forward kernels run one block per (32 rows, segment), six of them on a CU.  Rows that
+// The forward kernels run one block per (32 rows, segment), five to seven of them on a CU.  Rows that
 // cannot fill the chip are cut into segments scanned in parallel: a summary launch, the
 // carry chain, then the full pass started from the carried-in states.  That costs a second
 // read of x, delta, Bm and ~60% more arithmetic, so only when rows are scarce.  Number of blocks

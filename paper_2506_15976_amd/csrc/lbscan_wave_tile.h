@@ -5,6 +5,7 @@
 // Two layouts of the 64 lanes meet in a tile:
 //   staging:  lane = 64 / R * row + quad   four tokens of one row, as memory holds them
 //   scan:     lane = R * group + row       a share (1 in 64 / R) of the row's states, all its tokens
+//             (forward kernel, where Eq. 8 is summed: the eight lanes of a row within sixteen)
 #pragma once
 #include <type_traits>
 
