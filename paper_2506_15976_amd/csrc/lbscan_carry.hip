@@ -15,9 +15,13 @@
 // carried state passed along.  The backward pass's right-to-left recurrence
 // psi_t = abar_t (e_t + psi_{t+1}) chains the same way with the segments walked from the
 // last to the first, in the same launch (blockIdx.y).
-// Bound by the latency of two trips to memory.  MI355X, with a lane per segment before (every lane
+// Bound by the latency of a trip to memory and of its stores.  MI355X, with a lane per segment before (every lane
 // touched a line of its own) against now: forward call, 1 x 256 x 65536 (234 segments) 152 -> 146 us, 1 x 256 x
-// 8192 35 -> 31; training step, which chains twice more, 563 -> 543.
+// 8192 35 -> 31; training step, which chains twice more, 563 -> 543.  A and the entering state in
+// flight with the first segments' loads instead of waited for one by one before them, and the
+// segments' addresses as scalar steps (3.9 instead of 5.6 KB of code, fetched anew by every launch
+// between larger kernels): 1 x 192 x 8624, 5.7 -> 4.9, the forward call of 1 x 256 x 8192 30.3 -> 29.8.
+// Reading several waves' compositions from LDS at once made it slower (more code).
 #include "lbscan_device.h"
 #include "lbscan_internal.h"
 
@@ -42,24 +46,41 @@ carry_chain_kernel(const Chains chains, const float* __restrict__ dsum, const fl
 {
     __shared__ float sP[kChainWaves][64], sE[kChainWaves][64];
     const Chain ch = chains.c[blockIdx.y];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    const int n = blockIdx.x % N;
-    const long r0 = (long)(blockIdx.x / N) * 64 + lane;
+    // (wv uniform: a segment's address is scalar work)
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+    const int n = blockIdx.z;
+    const long r0 = (long)blockIdx.x * 64 + lane;
     const bool valid = r0 < rows;
-    const long row = valid ? r0 : rows - 1;
-    const float a2 = A[(row % D) * N + n] * kLog2e;
-    float cin = ch.init ? ch.init[row * N + n] : 0.0f;          // state entering the block's segments
+    const unsigned row = valid ? (unsigned)r0 : (unsigned)rows - 1;
+    // A and the state entering the walk are loaded on every path and used behind the first
+    // segments' loads, so that all of them are one trip to memory
+    const float* aa = A + (long)(row % (unsigned)D) * N + n;
+    float a = *aa;
+    float init = *(ch.init ? ch.init + (long)row * N + n : aa);
+    float cin = 0.0f;                                           // state entering the block's segments
+    // from one segment of the walk to the next
+    const long dstep = ch.reverse ? -(long)rows : rows, step = dstep * N;
+    auto at_segment = [&](float* buf, int ss) __attribute__((always_inline)) {
+        return buf + ((long)(ch.reverse ? nseg - 1 - ss : ss) * N + n) * rows;
+    };
     for (int base = 0; base < nseg; base += nw * kPerWave) {
         const int first = base + wv * kPerWave;
         float P[kPerWave], e[kPerWave];
+        // (segments without a summary: the last one that has one is loaded and not used)
+        const int from = first < ch.nsum ? first : ch.nsum > 0 ? ch.nsum - 1 : 0;
+        const float* es = at_segment(ch.buf, from);
+        const float* ds = dsum + (long)(ch.reverse ? nseg - 1 - from : from) * rows;
 #pragma unroll
         for (int k = 0; k < kPerWave; ++k) {
-            const int ss = first + k;
-            const bool have = ss < ch.nsum;
-            const long s = have ? (ch.reverse ? nseg - 1 - ss : ss) : 0;
-            e[k] = ch.buf[(s * N + n) * rows + row];
-            P[k] = dsum[s * rows + row];
+            e[k] = es[row];
+            P[k] = ds[row];
+            const bool more = first + k + 1 < ch.nsum;
+            es += more ? step : 0;
+            ds += more ? dstep : 0;
         }
+        asm volatile("" : "+v"(a), "+v"(init));
+        const float a2 = a * kLog2e;
+        if (base == 0) cin = ch.init ? init : 0.0f;
         float Pw = 1.0f, ew = 0.0f;
 #pragma unroll
         for (int k = 0; k < kPerWave; ++k) {
@@ -76,12 +97,14 @@ carry_chain_kernel(const Chains chains, const float* __restrict__ dsum, const fl
         for (int w = 0; w < nw; ++w) {
             if (w == wv) {
                 float v = c;
+                float* out = at_segment(ch.buf, first);
+                if (valid) {
 #pragma unroll
-                for (int k = 0; k < kPerWave; ++k) {
-                    const int ss = first + k;
-                    const long s = ch.reverse ? nseg - 1 - ss : ss;
-                    if (ss < nseg && valid) ch.buf[(s * N + n) * rows + row] = v;
-                    v = fmaf(P[k], v, e[k]);
+                    for (int k = 0; k < kPerWave; ++k) {
+                        if (first + k < nseg) out[row] = v;
+                        out += step;
+                        v = fmaf(P[k], v, e[k]);
+                    }
                 }
             }
             c = fmaf(sP[w][lane], c, sE[w][lane]);
@@ -128,7 +151,7 @@ hipError_t launch_chains(const FwdParams& p, const Chains& chains, int count, hi
     if (blocks == 0) return hipSuccess;
     if (blocks > 0x7fffffffL) return hipErrorInvalidConfiguration;
     const int waves = (p.nseg + kPerWave - 1) / kPerWave;
-    hipLaunchKernelGGL(carry_chain_kernel, dim3((unsigned)blocks, count), dim3(64 * (waves < kChainWaves ? waves : kChainWaves)),
+    hipLaunchKernelGGL(carry_chain_kernel, dim3((unsigned)(blocks / p.dstate), count, p.dstate), dim3(64 * (waves < kChainWaves ? waves : kChainWaves)),
                        0, stream, chains, p.dsum, p.A, (int)rows, p.dim, p.dstate, p.nseg);
     return hipGetLastError();
 }

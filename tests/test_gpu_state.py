@@ -127,6 +127,20 @@ def test_backward_with_only_the_arriving_gradient(lb, oracle):
     _check_bwd(lb, oracle, s, None, dhT, window=4)
 
 
+@pytest.mark.parametrize("nseg", [17, 18, 33, 256, 257, 258, 300])
+def test_chains_of_many_segments(lb, oracle, segments, nseg):
+    """The chain kernel at the edges of a wave's share (16 segments) and of a block's (256): rows of
+    two batch entries in two blocks of rows, with and without an entering state, both chains."""
+    from paper_2506_15976_amd.inputs import make_inputs
+    s = make_inputs(2, 35, 3, 32 * nseg - 5, seed=5140 + nseg, with_dout=True, random_A=True)
+    h0, dhT = _states(2, 35, 3, 5141 + nseg)
+    segments(nseg)
+    _check_fwd(lb, oracle, s, h0, window=4)
+    _check_fwd(lb, oracle, s, None, window=4, reverse=True)
+    _check_bwd(lb, oracle, s, h0, dhT, window=4)
+    _check_bwd(lb, oracle, s, None, dhT, window=4, reverse=True)
+
+
 @pytest.mark.parametrize("nseg", [2, 5])
 def test_backward_with_states_rows_cut_into_segments(lb, oracle, segments, nseg):
     from paper_2506_15976_amd.inputs import make_inputs
