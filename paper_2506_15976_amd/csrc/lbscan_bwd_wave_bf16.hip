@@ -6,7 +6,7 @@
 namespace lbscan {
 hipError_t launch_bwd_wave_bf16(const BwdParams& p, hipStream_t stream)
 {
-    return launch_bwd_t<bf16_t>(p, stream);
+    return launch_bwd_t<bf16_t, Rows::aligned>(p, stream);
 }
 hipError_t launch_reduce_bf16(const float* part, void* dB, void* dC, long bnl, int nbx, hipStream_t stream)
 {

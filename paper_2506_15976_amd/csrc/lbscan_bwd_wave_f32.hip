@@ -6,7 +6,7 @@
 namespace lbscan {
 hipError_t launch_bwd_wave_f32(const BwdParams& p, hipStream_t stream)
 {
-    return launch_bwd_t<float>(p, stream);
+    return launch_bwd_t<float, Rows::aligned>(p, stream);
 }
 hipError_t launch_reduce_f32(const float* part, void* dB, void* dC, long bnl, int nbx, hipStream_t stream)
 {

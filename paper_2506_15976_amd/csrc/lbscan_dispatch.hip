@@ -223,6 +223,27 @@ bool use_chunk_mapping(const FwdParams& p, const float* saved)
     return rows <= (ragged && p.dstate > 4 ? 12288 : 16384) && (nchunks == 1 || rows >= 3072 || (nchunks == 2 && rows >= 1536));
 }
 
+hipError_t launch_fwd_wave(const FwdParams& p, hipStream_t stream)
+{
+    // (the second pass of the any-window path starts segments anywhere and tells them apart itself)
+    switch (p.generic_window ? Rows::aligned : rows_of(p.order, p.dtype, p.pitch, p.seqlen, p.reverse)) {
+        case Rows::gathered: return p.dtype == 0 ? launch_fwd_gather_f32(p, stream) : launch_fwd_gather_bf16(p, stream);
+        case Rows::odd: return launch_fwd_odd_bf16(p, stream);
+        case Rows::aligned: break;
+    }
+    return p.dtype == 0 ? launch_fwd_wave_f32(p, stream) : launch_fwd_wave_bf16(p, stream);
+}
+
+hipError_t launch_bwd_wave(const BwdParams& p, hipStream_t stream)
+{
+    switch (rows_of(p.order, p.dtype, p.pitch, p.seqlen, p.reverse)) {
+        case Rows::gathered: return p.dtype == 0 ? launch_bwd_gather_f32(p, stream) : launch_bwd_gather_bf16(p, stream);
+        case Rows::odd: return launch_bwd_odd_bf16(p, stream);
+        case Rows::aligned: break;
+    }
+    return p.dtype == 0 ? launch_bwd_wave_f32(p, stream) : launch_bwd_wave_bf16(p, stream);
+}
+
 }  // namespace
 
 size_t fwd_workspace_bytes(const FwdParams& p)
@@ -247,10 +268,7 @@ hipError_t launch_fwd(FwdParams p, void* workspace, float* saved, hipStream_t st
     if (use_chunk_mapping(p, saved)) return launch_fwd_chunk(p, stream);
     p.ckpt = saved;
     p.cum = nullptr;
-    auto launch = [&](const FwdParams& q) {
-        return q.dtype == 0 ? launch_fwd_wave_f32(q, stream)
-                            : launch_fwd_wave_bf16(q, stream);
-    };
+    auto launch = [&](const FwdParams& q) { return launch_fwd_wave(q, stream); };
     p.nseg = s.nseg;
     p.seg_tiles = s.seg_tiles;
     p.in_block = 0;
@@ -338,8 +356,7 @@ hipError_t launch_fwd_generic(FwdParams p, void* workspace, hipStream_t stream)
     if (wps < 1) wps = 1;
     p2.seg_tokens = (int)(wps * M);
     p2.nseg = (int)((L + p2.seg_tokens - 1) / p2.seg_tokens);
-    return p2.dtype == 0 ? launch_fwd_wave_f32(p2, stream)
-                         : launch_fwd_wave_bf16(p2, stream);
+    return launch_fwd_wave(p2, stream);
 }
 
 // ---- backward ----------------------------------------------------------------
@@ -438,7 +455,7 @@ hipError_t launch_bwd(const FwdParams& f, BwdParams p, void* dBm, void* dCm, voi
         p.ckpt = saved;
         p.cum = nullptr;
         p.carry = nullptr;
-        e = f.dtype == 0 ? launch_bwd_wave_f32(p, stream) : launch_bwd_wave_bf16(p, stream);
+        e = launch_bwd_wave(p, stream);
         return e != hipSuccess ? e : finish();
     }
 
@@ -457,14 +474,13 @@ hipError_t launch_bwd(const FwdParams& f, BwdParams p, void* dBm, void* dCm, voi
     q.dsum = q.nseg > 1 ? ws + l.dsum : nullptr;
     q.psi = q.nseg > 1 ? ws + l.psi : nullptr;
     q.dout = p.dout;
-    e = q.dtype == 0 ? launch_fwd_wave_f32(q, stream)
-                     : launch_fwd_wave_bf16(q, stream);
+    e = launch_fwd_wave(q, stream);
     if (e != hipSuccess) return e;
     if (q.nseg > 1) {
         if ((e = launch_carry_chains(q, q.psi, dhT, stream)) != hipSuccess) return e;
     }
 
-    e = f.dtype == 0 ? launch_bwd_wave_f32(p, stream) : launch_bwd_wave_bf16(p, stream);
+    e = launch_bwd_wave(p, stream);
     return e != hipSuccess ? e : finish();
 }
 

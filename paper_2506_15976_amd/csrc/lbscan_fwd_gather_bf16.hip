@@ -1,0 +1,11 @@
+// Forward kernels (wave tiles) that gather the tokens of a scan order, bf16 storage.
+#include "lbscan_device.h"
+#include "lbscan_internal.h"
+#include "lbscan_fwd_wave.inc"
+
+namespace lbscan {
+hipError_t launch_fwd_gather_bf16(const FwdParams& p, hipStream_t stream)
+{
+    return launch_fwd_t<bf16_t, Rows::gathered>(p, stream);
+}
+}  // namespace lbscan

@@ -6,6 +6,6 @@
 namespace lbscan {
 hipError_t launch_fwd_wave_bf16(const FwdParams& p, hipStream_t stream)
 {
-    return launch_fwd_t<bf16_t>(p, stream);
+    return launch_fwd_t<bf16_t, Rows::aligned>(p, stream);
 }
 }  // namespace lbscan

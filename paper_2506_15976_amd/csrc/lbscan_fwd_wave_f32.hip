@@ -6,6 +6,6 @@
 namespace lbscan {
 hipError_t launch_fwd_wave_f32(const FwdParams& p, hipStream_t stream)
 {
-    return launch_fwd_t<float>(p, stream);
+    return launch_fwd_t<float, Rows::aligned>(p, stream);
 }
 }  // namespace lbscan

@@ -137,9 +137,29 @@ constexpr int kInBlockSegments = 8;
 // Window lengths with a compiled kernel.
 inline bool window_supported(int M) { return M == 1 || M == 2 || M == 4 || M == 8 || M == 16; }
 
-// Forward kernels (lbscan_fwd_wave.inc), one translation unit per storage type.
+// How the wave-tile kernels load the rows of a launch.  The kernels are compiled for one way each:
+// with all of them in every kernel (and the pairs of ways that meet at a row's end written out) the forward
+// kernels held twice the code and up to 68 spilled scalars, and lost in every
+// tile what they did not use.  MI355X, us, one kernel for all ways / one for each: 128 x 768 x 197 fp32 108.6 / 107.0,
+// 64 x 384 x 197 bf16, window 8, reversed 32.0 / 30.2, 1 x 256 x 8192 29.7 / 27.9, 128 x 384 x (7 x 7) by columns
+// 25.7 / 22.8.
+//   aligned:  whole quads (4 bytes an element, or rows that start at even ones)
+//   odd:      2-byte rows that start at odd elements every other row or, walked from their end, have an
+//             odd length: the aligned words around a quad
+//   gathered: token by token, in a scan order
+enum class Rows { aligned, odd, gathered };
+inline Rows rows_of(const TokenOrder& order, int dtype, int pitch, int seqlen, int reverse)
+{
+    if (order.kind != 0) return Rows::gathered;
+    return dtype != 0 && (pitch % 2 != 0 || (reverse && seqlen % 2 != 0)) ? Rows::odd : Rows::aligned;
+}
+
+// Forward kernels (lbscan_fwd_wave.inc), one translation unit per storage type and way.
 hipError_t launch_fwd_wave_f32(const FwdParams& p, hipStream_t stream);
 hipError_t launch_fwd_wave_bf16(const FwdParams& p, hipStream_t stream);
+hipError_t launch_fwd_odd_bf16(const FwdParams& p, hipStream_t stream);
+hipError_t launch_fwd_gather_f32(const FwdParams& p, hipStream_t stream);
+hipError_t launch_fwd_gather_bf16(const FwdParams& p, hipStream_t stream);
 
 // Chunk-per-lane forward kernel (lbscan_fwd_chunk.hip): one wave per row, 16 tokens
 // per lane, no workspace.  fwd_chunk_supported: p is within what it implements.
@@ -161,9 +181,12 @@ size_t fwd_generic_workspace_bytes(const FwdParams& p);
 // pass then needs its own summary pass anyway).
 size_t saved_state_bytes(const FwdParams& p);
 
-// Backward kernels (lbscan_bwd_wave.inc), one translation unit per storage type.
+// Backward kernels (lbscan_bwd_wave.inc), likewise.
 hipError_t launch_bwd_wave_f32(const BwdParams& p, hipStream_t stream);
 hipError_t launch_bwd_wave_bf16(const BwdParams& p, hipStream_t stream);
+hipError_t launch_bwd_odd_bf16(const BwdParams& p, hipStream_t stream);
+hipError_t launch_bwd_gather_f32(const BwdParams& p, hipStream_t stream);
+hipError_t launch_bwd_gather_bf16(const BwdParams& p, hipStream_t stream);
 // dBm, dCm (storage type) = the partial sums of BwdParams::dBpart added over the nbx
 // blocks of 64 channels; bnl = B * N * L.
 hipError_t launch_reduce_f32(const float* part, void* dB, void* dC, long bnl, int nbx, hipStream_t stream);

@@ -73,6 +73,42 @@ def test_a_short_last_tile(oracle, tokens, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("tokens", [1, 3, 9, 31, 32, 35, 41, 62, 64, 66, 95, 96, 129, 197, 230])
+def test_every_way_of_loading_rows_gives_the_same_bits(monkeypatch, tokens, dtype):
+    """A grid of one column is the stored order, and its rows are gathered token by token: the same
+    values as whole quads (even rows), unaligned ones (odd rows of a 2-byte type) and the
+    last tiles of either, and the same arithmetic behind them.  Rows whole, cut, and (few tiles, few
+    rows) in one block; forward call, and the gradients that no atomics are in."""
+    import torch
+    import paper_2506_15976_amd as lb
+    from gpu_util import fwd_inputs, to_device
+    from paper_2506_15976_amd import binding
+    from paper_2506_15976_amd.inputs import make_inputs
+    monkeypatch.setattr(binding, "_optional_block", lambda n, device: None)
+    for D, N, gate in ((13, 16, True), (40, 7, False)):
+        s = make_inputs(2, D, N, tokens, seed=9800 + D + tokens, dtype=dtype, random_A=True, with_dout=True)
+        if not gate:
+            s["z"] = None
+        dev = to_device(s, dtype)
+        for segments in (0, 1, 2):
+            lb.lbscan_set_option("segments", segments)
+            try:
+                for window in (1, 4, 8, 16):
+                    for reverse in (False, True):
+                        def both(**grid):
+                            out = lb.lbscan_fwd(**fwd_inputs(dev), window=window, reverse=reverse, **grid)
+                            g = lb.lbscan_bwd(**fwd_inputs(dev), dout=dev["dout"], window=window, reverse=reverse, **grid)
+                            torch.cuda.synchronize()
+                            return {"out": out, **g}
+                        stored, gathered = both(), both(grid=(tokens, 1))
+                        for k in ("out", "dx", "ddelta", "dz", "dBm", "dCm"):
+                            if gathered[k] is not None:
+                                assert torch.equal(stored[k], gathered[k]), (k, N, segments, window, reverse)
+            finally:
+                lb.lbscan_set_option("segments", 0)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("shape", [(1, 5, 16, 1024), (2, 3, 7, 820), (1, 200, 16, 1000), (1, 1537, 5, 822)])
 def test_rows_of_one_chunk(oracle, shape, dtype):
     """Rows of 820 to 1024 tokens, which the library hands to one family or the other: its own
