@@ -304,3 +304,44 @@ def test_gathered_rows_in_segments(lb, oracle, route, batch, segments, dim):
         _check(lb, oracle, s, (9, 10, 1), window=4, reverse=bool(batch & 2))
     finally:
         lb.lbscan_set_option("segments", 0)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("after", [0, 1, 2])
+@pytest.mark.parametrize("reverse", [False, True])
+def test_what_lies_behind_a_copied_row_is_not_scanned(lb, route, after, reverse, dtype):
+    """One to three tokens in the copies' last tile, and copies of the last scanned one behind them,
+    which are loaded with it.  That token is not finite: it reaches what it reaches in the gathered
+    rows, whose last tile holds zeros there."""
+    import torch
+    from gpu_util import fwd_inputs, to_device
+    from paper_2506_15976_amd import binding
+    from paper_2506_15976_amd.inputs import column_order, make_inputs
+    B, D, N, L, grid = 32, 560, 4, 257 + after, (16, 16, 1)
+    a = binding.LbscanArgs(B, D, N, L, 8, 0 if dtype == "fp32" else 1)
+    a.scan_order, a.grid_h, a.grid_w, a.grid_prefix = binding.ORDER_COLUMNS, *grid
+    assert all(binding.lbscan_workspace_bytes(a, which) > 0 for which in (binding.WS_FWD_ORDER, binding.WS_BWD_ORDER))
+    s = make_inputs(B, D, N, L, seed=9900 + after, dtype=dtype, with_dout=True)
+    last = column_order(L, *grid)[-1]
+    s["Bm"][0, 1, last] = np.inf
+    s["Cm"][1, 2, last] = -np.inf
+    s["x"][2, 3, last] = np.nan
+    s["delta"][3, 4, last] = np.inf
+    dev = to_device(s, dtype)
+    rel = 2e-5 if dtype == "fp32" else 2 ** -7          # as the finite values of copies and gathers differ
+
+    def both():
+        out = lb.lbscan_fwd(**fwd_inputs(dev), window=8, reverse=reverse, grid=grid)
+        g = lb.lbscan_bwd(**fwd_inputs(dev), dout=dev["dout"], window=8, reverse=reverse, grid=grid)
+        torch.cuda.synchronize()
+        return {"out": out, **g}
+    copied = both()
+    route(False)
+    for k, v in both().items():
+        c, v = copied[k].float(), v.float()
+        fine = torch.isfinite(v)
+        assert torch.equal(torch.isfinite(c), fine), k
+        assert torch.equal(torch.isnan(c), torch.isnan(v)), k
+        size = v[fine]
+        bound = rel * torch.maximum(size.abs(), size.square().mean().sqrt()) if size.numel() else size
+        assert bool(((c[fine] - size).abs() <= bound).all()), k
