@@ -60,13 +60,13 @@ struct TokenOrder {
     {
         if (kind == 0) return t;
         const int k = t - prefix;
-        if (k < 0 || k >= HW) return t;
         // column c = k / H: the float quotient is off by at most one for k < 2^24
         int c = (int)((float)k * rH);
         int r = k - c * H;
-        if (r < 0) { r += H; --c; }
-        if (r >= H) { r -= H; ++c; }
-        return prefix + r * W + c;
+        const int low = r < 0, high = r >= H, off = high - low;
+        const int in_grid = prefix + (r - off * H) * W + c + off;
+        // (values chosen between, not ways taken: a branch here would stand before every load)
+        return (unsigned)k < (unsigned)HW ? in_grid : t;
     }
 };
 
@@ -100,10 +100,13 @@ template <> struct __attribute__((packed, aligned(4))) Quad<bf16_t> { bf16_t v[4
 // One quad of a (rows, L) tensor in its storage type, for later conversion.  `base` is
 // uniform, `off` the element offset of quad element 0 and `ph` its token index.  The fast
 // form is one unconditional quad load.  The checked form (further down) zeroes elements
-// whose token index ph + e is outside [0, L); it loads from a clamped (always valid)
-// address and selects afterwards, so that no load sits behind a divergent branch: a load
-// that is conditionally re-issued into the same registers would force the compiler to wait
-// for the first one and serialise the prefetch.
+// whose token index ph + e is outside [0, L), loading from a clamped (always valid)
+// address.  Where the tokens of a scan order are gathered the loads are unconditional: a value
+// chosen between structs, or an index computed in a branch, becomes a branch that the
+// load is moved into, and the quad's loads wait for one another (4 x 384 x (37 x 37) by columns, bf16,
+// 72.6 -> 65.1 us).  In stored order such branches stand: the ragged chunks of the chunk kernel skip
+// what lies behind the row (unconditional, 1 x 192 x 900 fp32 22.4 -> 25.2 us; bf16 would gain, 8 x 384 x 960
+// 38.2 -> 30.8).
 template <typename T>
 __device__ __forceinline__ Quad<T> quad_raw_fast(const T* __restrict__ base, long off)
 {
@@ -157,6 +160,14 @@ __device__ __forceinline__ void quad_store_unaligned(float* __restrict__ p, cons
 template <typename T> __device__ __forceinline__ T zero_elem();
 template <> __device__ __forceinline__ float zero_elem<float>() { return 0.0f; }
 template <> __device__ __forceinline__ bf16_t zero_elem<bf16_t>() { bf16_t z; z.bits = 0; return z; }
+// v, or zero, chosen between as plain numbers (see quad_raw_checked).
+__device__ __forceinline__ float keep_if(bool keep, float v) { return keep ? v : 0.0f; }
+__device__ __forceinline__ bf16_t keep_if(bool keep, bf16_t v)
+{
+    const uint16_t zero = 0, bits = v.bits;
+    v.bits = keep ? bits : zero;
+    return v;
+}
 
 template <typename T>
 __device__ __forceinline__ Quad<T> quad_raw_checked(const T* __restrict__ base, long off, int ph, int L)
@@ -184,7 +195,7 @@ __device__ __forceinline__ Quad<T> quad_raw_checked(const T* __restrict__ base, 
         const int t = ph + e;
         const int tc = t < 0 ? 0 : (t >= L ? L - 1 : t);
         const T v = base[(off - ph) + ord(tc)];
-        q.v[e] = (t == tc) ? v : zero_elem<T>();
+        q.v[e] = keep_if(t == tc, v);
     }
     return q;
 }
