@@ -175,32 +175,40 @@ Shape pick_bwd_shape(const FwdParams& p)
 }
 
 // The chunk-per-lane kernel (one wave per row, 1024-token chunks, one launch; 768 blocks of four rows
-// in flight) against the wave-tile kernels (rows cut where that is faster), measured on MI355X
-// (us, wave tiles / chunk; fp32 with window 4, bf16 with window 8; 16 states).  Whole chunks:
+// in flight, so 3072 rows are a full round) against the wave-tile kernels (rows cut where that is
+// faster), measured on MI355X (us, wave tiles / chunk; fp32 with window 4, bf16 with window 8;
+// 16 states).  Whole chunks:
 //   rows x tokens      fp32           bf16           rows x tokens      fp32           bf16
-//   192 x 1024         20.7 / 16.6    21.6 / 14.6    1536 x 4096        65.5 / 72.5    68.3 / 63.9
-//   3072 x 1024        36.7 / 26.2    40.2 / 22.6    3072 x 4096        109 / 88.1     118 / 80.7
-//   12288 x 1024       105 / 87.3     119 / 75.8     6144 x 4096        214 / 183      218 / 150
-//   24576 x 1024       145 / 188      148 / 143      12288 x 4096       425 / 366      508 / 313
-//   1536 x 2048        39.2 / 38.7    40.3 / 33.1    16128 x 2048       213 / 240      251 / 193
+//   192 x 1024         17.9 / 14.3    18.2 / 14.2    1536 x 4096        57.1 / 65.3    59.3 / 62.1
+//   3072 x 1024        36.4 / 25.1    36.5 / 22.9    3072 x 4096        103 / 86.1     102 / 79.4
+//   12288 x 1024       91.0 / 85.6    95.3 / 73.2    6144 x 4096        192 / 164      188 / 152
+//   24576 x 1024       128 / 160      128 / 141      12288 x 4096       351 / 331      343 / 286
+//   1536 x 2048        35.6 / 34.2    35.7 / 32.5    16128 x 2048       179 / 210      192 / 188
 // A chunk that the row does not fill takes its loads element by element, in every state,
-//   192 x 900          19.9 / 22.4    20.8 / 24.1    3072 x 2000        64.8 / 58.2    67.5 / 57.5
-//   768 x 1020         21.0 / 23.2    21.1 / 24.1    6144 x 1700        95.6 / 103     105 / 104
-//   1920 x 1020        32.2 / 30.8    32.3 / 27.3    6144 x 5000        264 / 265      268 / 217
-//   2688 x 900         34.4 / 36.1    40.0 / 32.7    9216 x 2000        148 / 181      160 / 158
-//   3072 x 960         35.9 / 36.0    37.8 / 34.3    12288 x 1700       175 / 217      205 / 202
-//   3456 x 960         41.3 / 58.4    44.0 / 57.2    12288 x 4000       398 / 412      513 / 388
-//   6144 x 1000        62.4 / 71.1    67.6 / 73.0    16128 x 2000       209 / 327      252 / 290
-//   16128 x 960        100 / 185      115 / 190      2688 x 2700        78.4 / 73.1    77.4 / 74.2
+//   192 x 900          17.3 / 21.4    17.4 / 23.3    6144 x 1700        93.9 / 106     86.4 / 100
+//   1920 x 1020        30.3 / 29.8    30.5 / 33.5    6144 x 5000        254 / 234      235 / 227
+//   2688 x 900         32.0 / 34.4    31.7 / 36.9    9216 x 2000        144 / 168      141 / 175
+//   3072 x 960         34.6 / 35.5    35.1 / 37.9    12288 x 1700       154 / 206      160 / 219
+//   3456 x 960         36.7 / 56.3    38.7 / 61.4    12288 x 4000       341 / 372      342 / 368
+//   6144 x 1000        57.9 / 69.9    56.0 / 72.1    16128 x 2000       183 / 300      191 / 316
+//   3072 x 2000        58.0 / 55.2    57.2 / 55.4    1536 x 3000        49.0 / 58.7    47.9 / 61.7
 // and less so with fewer states, while a wave tile has lanes for 8 or 16 of them (rows x tokens x N):
-//   192 x 1000 x 12    20.1 / 19.2    21.2 / 20.0    192 x 1000 x 5     16.3 / 12.7    17.2 / 12.8
-//   6144 x 1000 x 12   61.1 / 60.8    66.7 / 61.0    768 x 1000 x 8     15.4 / 16.0    16.4 / 16.1
-//   14592 x 1700 x 8   145 / 191      167 / 157      14592 x 1000 x 8   85.8 / 117     101 / 115
+//   192 x 1000 x 12    17.6 / 18.3    17.5 / 19.5    14592 x 1700 x 8   118 / 172      122 / 172
+//   6144 x 1000 x 12   56.7 / 60.0    55.0 / 60.4    14592 x 1000 x 8   71.8 / 129     72.6 / 129
+//   192 x 1000 x 5     16.4 / 12.4    15.5 / 12.7    768 x 1000 x 8     15.2 / 16.9    15.5 / 16.8
 // It needs chunks that are mostly full, and rows enough for a wave each unless a row is one whole
-// chunk; of 13 to 16 states a row of one ragged chunk pays where the rows about fill one round of blocks (3072).  With fp32
-// storage (four rows share a staged Bm / Cm chunk, so those reads are twice the row reads) it loses
-// where the wave tiles fill the chip without cutting rows, with ragged chunks beyond two rounds.
-// (On the wrong side: bf16 rows of two ragged chunks around 1536 and 3456 rows and from 14592 rows on.)
+// chunk.  Ragged chunks of 15 and 16 states pay where the rows about fill one round of blocks, or two
+// with three chunks and more; of fewer states from two thirds of a round on (with two and three chunks not a little
+// over one), up to two rounds with two chunks or four with more; rows of one ragged chunk where they fill a round or
+// are few.  Where the wave tile's lanes are half idle (5, 6, 9, 10 states, and up to 4) fewer rows are
+// enough.  Whole chunks pay up to 13312 rows in fp32 (four rows share a staged Bm / Cm chunk, so those reads
+// are twice the row reads) and 20480 in bf16, and further with fewer states.  On 420 calls drawn over
+// 600 to 49000 rows, 820 to 12000 tokens, 5 to 16 states, both types and directions and windows 1 to
+// 16 the rule takes 1.6% more time than the faster side of each (the lines before the present kernels 3.8%; single
+// sizes of theirs up to 77%, 14592 x 1000 x 8).
+// (On the wrong side: rows of 2 to 8 states and two chunks or more below the lines, where the chunk
+// kernel would be up to a third faster; whole chunks of 13000 fp32 rows of 8 states, of a little over a
+// round.)
 // It leaves no checkpoints for a backward call.
 bool use_chunk_mapping(const FwdParams& p, const float* saved)
 {
@@ -213,14 +221,32 @@ bool use_chunk_mapping(const FwdParams& p, const float* saved)
     if (p.force_nseg >= 1) return false;                              // (it takes its rows whole)
     const long rows = (long)p.batch * p.dim;
     const long chunk = 1024, nchunks = (p.seqlen + chunk - 1) / chunk;
-    const bool ragged = p.seqlen % chunk != 0;
+    const long taken = (p.dim + 31) / 32 * 32L * p.batch;             // rows that wave tiles work on
+    const int N = p.dstate;
     if (p.seqlen * 5 < nchunks * chunk * 4) return false;             // chunks less than 80% full
-    if (ragged && p.dstate > 12) {
-        if (nchunks == 1) return rows > 1536 && rows <= 3072;
-        if (p.dtype == 0) return rows <= 6144 && (rows >= 3072 || (nchunks == 2 && rows > 1536));
+    if (p.seqlen % chunk == 0) {
+        if (p.dtype == 0)
+            return rows <= (N > 8 ? 13312 : N > 4 ? 14336 : 16384) && (nchunks == 1 || rows >= (nchunks == 2 ? 1536 : 3072));
+        if (N > 8 && rows > 20480) return false;
+        return nchunks == 1 || (N <= 8 || nchunks < 4 ? rows >= 1536 : taken >= (nchunks < 8 ? 1920 : 2048));
     }
-    if (p.dtype != 0) return nchunks == 1 || rows >= 1536;
-    return rows <= (ragged && p.dstate > 4 ? 12288 : 16384) && (nchunks == 1 || rows >= 3072 || (nchunks == 2 && rows >= 1536));
+    if (N <= 4) {
+        if (nchunks == 1) return rows <= 8192 || (p.dtype != 0 && N <= 2);
+        return p.dtype != 0 ? rows >= 1536 : rows <= 16384 && rows >= (nchunks == 2 ? 1536 : 3072);
+    }
+    const bool one_round = taken > 2720 && rows <= 3072;
+    const bool light = N <= 6 || (N > 8 && N <= 10);                  // few of the lanes that a wave tile has for states
+    if (nchunks == 1) {
+        if (light) return rows <= 6144;
+        return N <= 8 ? rows <= 768 || one_round : one_round && (N <= 14 || p.seqlen >= 1000);
+    }
+    if (N > 14) {
+        if (nchunks < 5) return one_round || (nchunks >= 3 && rows > 5632 && rows <= 6144);
+        return one_round || (rows > 4900 && rows <= 9216);
+    }
+    if (rows > (nchunks == 2 || (N > 12 && p.dtype == 0) ? 6144 : N > 6 && nchunks < 4 ? 12288 : 14336)) return false;
+    if (p.dtype == 0 && nchunks > 2 && rows < 2817) return false;
+    return light && (p.dtype != 0 || nchunks == 2) ? rows >= 1536 : taken >= 1920 && (N <= 6 || nchunks > 3 || rows <= 3072 || rows > 4096);
 }
 
 hipError_t launch_fwd_wave(const FwdParams& p, hipStream_t stream)

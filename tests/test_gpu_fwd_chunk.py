@@ -160,3 +160,38 @@ def test_matches_row_per_lane_kernels_at_full_size(lb, oracle):
     ref = oracle.fwd(**fwd_inputs(s), window=w["window"])
     assert_close(to_numpy(got), ref, w["dtype"], "chunk per lane")
     assert_close(to_numpy(other), ref, w["dtype"], "wave tiles")
+
+
+@pytest.mark.parametrize("rows, tokens, states, dtype, chunk", [
+    # ragged chunks: on both sides of the lines beside use_chunk_mapping
+    (1536, 1700, 16, "bf16", False), (2720, 1700, 16, "bf16", False), (2728, 1700, 16, "bf16", True),
+    (3072, 960, 16, "fp32", False), (3072, 1000, 16, "fp32", True), (3080, 2600, 16, "fp32", False),
+    (6144, 2600, 16, "bf16", True), (6152, 2600, 16, "bf16", False), (4904, 4600, 16, "bf16", True),
+    (1536, 900, 12, "fp32", False), (768, 900, 8, "fp32", True), (776, 900, 8, "fp32", False),
+    (6144, 900, 6, "bf16", True), (6152, 900, 6, "bf16", False), (1536, 2600, 10, "bf16", True), (1528, 2600, 10, "bf16", False),
+    (1856, 2600, 8, "bf16", False), (1920, 2600, 8, "bf16", True), (2816, 2600, 8, "fp32", False), (3080, 2600, 8, "fp32", False),
+    (4104, 2600, 8, "fp32", True),
+    # whole ones
+    (1536, 3072, 16, "bf16", True), (1536, 4096, 16, "bf16", False), (1920, 4096, 16, "bf16", True),
+    (3072, 4096, 16, "fp32", True), (2816, 4096, 16, "fp32", False),
+])
+def test_rows_go_to_the_faster_family(lb, rows, tokens, states, dtype, chunk):
+    """The chunk kernel takes no scratch; the wave tiles write theirs where rows are cut, as all of
+    these are (fewer than 257 blocks of 32 rows)."""
+    import ctypes
+    import torch
+    from paper_2506_15976_amd import binding
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x = torch.ones(1, rows, tokens, dtype=t, device="cuda:0")
+    b = torch.ones(1, states, tokens, dtype=t, device="cuda:0")
+    A = -torch.ones(rows, states, device="cuda:0")
+    y = torch.empty_like(x)
+    a = binding.make_args(x, x, A, b, b, window=4, y=y)
+    need = binding.lbscan_workspace_bytes(a, binding.WS_FWD)
+    assert need > 0
+    ws = torch.full((need // 4,), float("nan"), device="cuda:0")
+    a.workspace, a.workspace_bytes = ws.data_ptr(), need
+    assert lb.load().lbscan_fwd(ctypes.byref(a), torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(ws).all()) == chunk
+    assert bool(torch.isfinite(y.float()).all())

@@ -112,7 +112,7 @@ def test_every_way_of_loading_rows_gives_the_same_bits(monkeypatch, tokens, dtyp
 @pytest.mark.parametrize("shape", [(1, 5, 16, 1024), (2, 3, 7, 820), (1, 200, 16, 1000), (1, 1537, 5, 822)])
 def test_rows_of_one_chunk(oracle, shape, dtype):
     """Rows of 820 to 1024 tokens, which the library hands to one family or the other: its own
-    choice (the chunk-per-lane kernel for all but the third), and each family asked for."""
+    choice (the wave tiles for the third), and each family asked for."""
     import numpy as np
     import paper_2506_15976_amd as lb
     from paper_2506_15976_amd.inputs import make_inputs
