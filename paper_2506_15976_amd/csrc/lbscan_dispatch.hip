@@ -71,25 +71,29 @@ bool gather_cut_pays(const FwdParams& p, long nrb)
 // cannot fill the chip are cut into segments scanned in parallel: a summary launch, the
 // carry chain, then the full pass started from the carried-in states.  That costs a second
 // read of x, delta, Bm and ~60% more arithmetic, so only when rows are scarce.  Number of blocks
-// aimed at (us, 1 x 256 x 65536): 1024: 156, 1536: 154, 2048: 149, 2560: 164; 1 x 512 x 16384:
-// 768: 93, 1024: 88, 2048: 88.  Up to 256 row blocks a CU has one block of uncut rows at most, and
+// aimed at (us, 1 x 256 x 65536): 1024: 146, 1536: 142, 2048: 139, 2560: 150; 1 x 512 x 16384:
+// 768: 80, 1024: 77, 1536: 82, 2048: 79.  Up to 256 row blocks a CU has one block of uncut rows at most, and
 // all rows that one block cannot take whole (in_block_shape) are cut; beyond, the longer the rows
-// the more a cut can pay for its launches.  Measured on MI355X (us, uncut / cut; fp32 with window
-// 4, bf16 with window 8):
+// the more a cut can pay for its launches.  cut_pays says which calls take scratch for a cut: its lines
+// are those of the kernels before the ways of loading had kernels of their own, and callers
+// size their scratch by them.  whole_is_faster leaves rows whole within them where that is
+// faster now.  Measured on MI355X (us, uncut / cut; fp32 with window 4, bf16 with window 8):
 //   tokens  blocks  fp32          bf16             tokens  blocks  fp32          bf16
-//   160     264     18.7 / 20.4   20.3 / 21.2      700     348     73.6 / 76.2   86.0 / 76.8
-//   197     324     25.4 / 27.3   28.8 / 30.2      700     372     73.8 / 81.2   86.1 / 80.5
-//   197     348     25.4 / 30.1   28.7 / 33.7      700     396     74.0 / 82.1   86.3 / 84.8
-//   256     324     28.8 / 30.1   31.1 / 32.5      1100    372     113 / 113     134 / 120
-//   256     348     28.8 / 31.5   30.8 / 33.9      1600    384     161 / 159     184 / 162
-//   300     348     34.9 / 39.4   39.6 / 40.7      1600    396     161 / 158     184 / 169
-//   300     372     35.0 / 40.7   40.0 / 42.9      1600    420     161 / 169     185 / 183
-//   400     348     44.6 / 46.7   51.7 / 50.0      3001    384     325 / 334     380 / 323
-//   400     372     44.8 / 47.6   51.8 / 50.3      3001    396     320 / 349     381 / 344
-//   400     396     44.9 / 53.5   52.0 / 55.3      3001    420     322 / 370     383 / 366
-// (The lines stand where neither direction and no window loses by them: reversed rows and window 1
-// gain from a cut a little further on.  At 384 blocks reversed fp32 rows off whole lines would gain 5 to 8% from a cut,
-// forward ones lose as much; the size of the scratch does not depend on the direction.)
+//   197     300     21.6 / 25.5   22.3 / 25.8      700     300     65.2 / 63.1   66.5 / 61.0
+//   197     348     21.9 / 29.4   22.6 / 29.2      700     324     65.8 / 68.4   66.5 / 64.5
+//   256     324     25.3 / 27.4   26.0 / 28.4      700     348     66.2 / 75.2   66.6 / 68.2
+//   300     192     24.8 / 23.6   24.9 / 22.6      1100    300     101 / 98.4    102 / 92.7
+//   300     216     25.0 / 26.6   25.1 / 25.8      1100    324     102 / 106     103 / 94.7
+//   300     252     25.3 / 27.5   25.2 / 26.9      1100    372     103 / 116     105 / 107
+//   300     348     31.0 / 36.2   32.1 / 34.9      1600    324     140 / 138     149 / 131
+//   400     252     31.6 / 33.8   32.0 / 33.1      1600    348     139 / 144     150 / 143
+//   400     276     38.7 / 37.8   40.0 / 37.1      1600    372     140 / 153     151 / 153
+//   400     300     38.7 / 40.3   40.1 / 40.0      3001    300     273 / 264     278 / 244
+//   400     324     39.0 / 42.9   40.8 / 42.5      3001    348     279 / 297     281 / 271
+//   512     300     46.7 / 44.0   48.7 / 44.0      3001    372     270 / 310     281 / 283
+// With eight states 300 tokens cross at 300 blocks (24.2 / 24.6, 24.6 / 23.6) and not below 257 (240:
+// 21.6 / 21.1), and long bf16 rows beyond cut_pays' lines (64 x 168 x 3555, 384 blocks, 250 / 230); reversed
+// rows and windows 1 and 16 cross at the same lines within 3%.
 bool cut_pays(const FwdParams& p, long nrb)
 {
     const int L = p.seqlen;
@@ -98,6 +102,18 @@ bool cut_pays(const FwdParams& p, long nrb)
     if (L <= 256) return nrb < 348;
     if (p.dtype == 0 || L <= 320) return nrb < (L <= 1024 ? 360 : 384);
     return nrb < (L <= 1024 ? 390 : 410);
+}
+
+bool whole_is_faster(const FwdParams& p)
+{
+    const long nrb = (long)((p.dim + 31) / 32) * p.batch;
+    const int L = p.seqlen;
+    if (p.order.kind != 0) return false;
+    if (L <= 256) return nrb > 256;
+    if (L <= 320) return p.dstate > 8 ? nrb > 207 : nrb > 311;
+    if (p.dtype == 0) return nrb > (L <= 448 ? 287 : 317);
+    if (p.dstate <= 8 && L > 448) return false;
+    return nrb > (L <= 448 ? 311 : L <= 1024 ? 341 : 365);
 }
 
 // Segments aimed at where rows are cut.  With at most eight states a lane has half the work for the
@@ -290,7 +306,8 @@ hipError_t launch_fwd(FwdParams p, void* workspace, float* saved, hipStream_t st
 {
     if (p.batch == 0 || p.dim == 0 || p.seqlen == 0) return hipSuccess;
     // (a pass that leaves checkpoints takes its rows whole: its callers have rows enough)
-    const Shape s = saved ? Shape{1, (p.seqlen + kFwdTileTokens - 1) / kFwdTileTokens} : pick_shape(p);
+    const bool whole = saved || (p.force_nseg < 1 && whole_is_faster(p));
+    const Shape s = whole ? Shape{1, (p.seqlen + kFwdTileTokens - 1) / kFwdTileTokens} : pick_shape(p);
     if (use_chunk_mapping(p, saved)) return launch_fwd_chunk(p, stream);
     p.ckpt = saved;
     p.cum = nullptr;

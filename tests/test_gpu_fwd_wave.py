@@ -156,3 +156,36 @@ def test_a_forced_cut_is_made(oracle, tokens, segments, dtype):
     written = torch.isfinite(ws).sum().item()
     assert written >= (segments - 1) * 64 * (16 + 1)        # nobody reads the last segment's
     assert_close(to_numpy(y), oracle.fwd(**fwd_inputs(s), window=4), dtype)
+
+
+@pytest.mark.parametrize("blocks, tokens, states, dtype, cut", [
+    # on both sides of the lines beside whole_is_faster, within those that scratch is sized by
+    (324, 197, 16, "fp32", False), (336, 256, 16, "bf16", False), (207, 300, 16, "fp32", True), (208, 300, 16, "bf16", False),
+    (240, 300, 8, "bf16", True), (312, 300, 8, "fp32", False), (287, 448, 16, "fp32", True), (288, 448, 16, "fp32", False),
+    (311, 448, 16, "bf16", True), (312, 448, 16, "bf16", False), (317, 449, 16, "fp32", True), (318, 449, 16, "fp32", False),
+    (341, 700, 16, "bf16", True), (342, 700, 16, "bf16", False), (365, 1100, 16, "bf16", True), (366, 1100, 16, "bf16", False),
+    (366, 1100, 8, "bf16", True), (252, 700, 16, "fp32", True),
+])
+def test_rows_stay_whole_where_that_is_faster(blocks, tokens, states, dtype, cut):
+    """A call that takes scratch for a cut writes it only where it cuts its rows."""
+    import ctypes
+    import torch
+    import paper_2506_15976_amd as lb
+    from paper_2506_15976_amd import binding
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x = torch.ones(blocks, 32, tokens, dtype=t, device="cuda:0")
+    b = torch.ones(blocks, states, tokens, dtype=t, device="cuda:0")
+    A = -torch.ones(32, states, device="cuda:0")
+    y = torch.empty_like(x)
+    lb.lbscan_set_option("mapping", 1)
+    try:
+        a = binding.make_args(x, x, A, b, b, window=4, y=y)
+        need = binding.lbscan_workspace_bytes(a, binding.WS_FWD)
+        ws = torch.full((need // 4,), float("nan"), device="cuda:0")
+        a.workspace, a.workspace_bytes = ws.data_ptr(), need
+        assert need > 0 and lb.load().lbscan_fwd(ctypes.byref(a), torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+    finally:
+        lb.lbscan_set_option("mapping", 0)
+    assert bool(torch.isnan(ws).all()) != cut
+    assert bool(torch.isfinite(y.float()).all())

@@ -1,5 +1,6 @@
-"""Which forward calls cut their rows into segments (and so take scratch), on both sides of the
-lines that the rule in lbscan_dispatch.hip draws.  Host logic only."""
+"""Which forward calls take scratch for rows cut into segments, on both sides of the lines that
+cut_pays and gather_cut_pays in lbscan_dispatch.hip draw (within them whole_is_faster leaves some rows
+whole, which the launch decides: test_gpu_fwd_wave.py).  Host logic only."""
 import pytest
 
 from paper_2506_15976_amd import binding
