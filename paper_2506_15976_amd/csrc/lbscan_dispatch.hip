@@ -10,8 +10,8 @@ namespace {
 struct Shape { int nseg, seg_tiles; };
 
 // Up to this many segments the full forward pass folds the carry chain itself.
-// (Measured, up to 16 / up to 4, us: 4 x 384 x 576 22.6 / 25.1, 16 x 384 x 576 41.9 / 43.9,
-// 8 x 384 x 1500 51.8 / 57.1.)
+// (Measured, up to 16 / up to 4, us, fp32: 4 x 384 x 576 17.7 / 19.0, 16 x 384 x 576 34.6 / 37.7,
+// 8 x 384 x 1500 48.2 / 48.7.)
 constexpr int kFoldChainSegments = 16;
 
 // Cuts the rows into want_seg segments of whole forward tiles, at least 64 tokens each
@@ -46,19 +46,20 @@ size_t summary_bytes(const FwdParams& p, int nseg)
 // gathers x, delta and Bm a second time, which costs the more the less of the rows the caches
 // hold.  Measured on MI355X (us, uncut / cut; rows x tokens, MB of x):
 //   blocks  fp32                                     bf16
-//   96      2305, 28 MB  609 / 511                   4097, 25 MB  1222 / 822
-//   120     1601, 25 MB  480 / 405                   4097, 31 MB  1351 / 1135
-//   120     2305, 35 MB  693 / 755                   5185, 40 MB  1668 / 1917
-//   144     1025, 19 MB  364 / 334                   2305, 21 MB  722 / 647
-//   144     4097, 76 MB  1416 / 1941                 4097, 38 MB  1520 / 1819
-//   192     1025, 25 MB  470 / 525                   1601, 20 MB  564 / 547
-//   192     4097, 101 MB 1871 / 2553                 2305, 28 MB  882 / 997
-//   240     577, 18 MB   202 / 211                   1601, 25 MB  663 / 767
-//   336     401, 17 MB   150 / 162                   1025, 22 MB  525 / 595
-//   288     145          -                           145          32 / 36
-//   288     257          64 / 56                     401          93 / 77
+//   96      2305, 28 MB  650 / 509                   4097, 25 MB  1139 / 789
+//   120     1601, 25 MB  508 / 430                   4097, 31 MB  1365 / 1140
+//   120     2305, 35 MB  754 / 767                   5185, 40 MB  1661 / 1956
+//   144     1025, 19 MB  377 / 337                   2305, 21 MB  700 / 658
+//   144     4097, 76 MB  1534 / 1954                 4097, 38 MB  1537 / 1875
+//   192     1025, 25 MB  472 / 516                   1601, 20 MB  556 / 526
+//   192     4097, 101 MB 1903 / 2567                 2305, 28 MB  882 / 1007
+//   240     577, 18 MB   201 / 206                   1601, 25 MB  651 / 762
+//   336     401, 17 MB   150 / 157                   1025, 22 MB  513 / 572
+//   288     145          26 / 28                     145          23 / 25
+//   288     257          61 / 53                     401          72 / 62
 // (square grids; few rows or few columns keep more of the lines: 360 blocks of 4 x 256 tokens in bf16
-// 238 / 191)
+// 238 / 191 with kernels whose loads waited for one another.  On the wrong side: bf16 at 384 blocks of 401
+// tokens, 90 / 87.)
 bool gather_cut_pays(const FwdParams& p, long nrb)
 {
     if (p.seqlen <= 160) return nrb < 208;
@@ -119,12 +120,12 @@ bool whole_is_faster(const FwdParams& p)
 // Segments aimed at where rows are cut.  With at most eight states a lane has half the work for the
 // same launches, and long rows of few channels notice how the blocks fill the chip: whole rounds of
 // 1536 blocks, and no chain of more segments than one block of the chain kernel takes (256).
-// Measured on MI355X (us, fp32, N = 8, window 2; kernels before the wave tiles / 2048 blocks / this):
-//   4 blocks x 30000    45.5 / 47.4 / 41.2      12 blocks x 30000   85.3 / 90.5 / 82.7
-//   6 blocks x 20000    42.0 / 45.2 / 38.2      12 blocks x 65536   151 / 163 / 149
-//   8 blocks x 30000    63.2 / 67.0 / 60.3      16 blocks x 41432   146 / 165 / 148
-//   8 blocks x 65536    106 / 112 / 111         24 blocks x 30000   150 / 162 / 146
-// (Shorter rows, 16 x 14000 55.6 / 58.2 us, and 16 states gain at some lengths and lose at others.)
+// Measured on MI355X (us, fp32, N = 8, window 2; 2048 blocks / this):
+//   4 blocks x 30000    40.4 / 35.7      12 blocks x 30000   81.3 / 78.6
+//   6 blocks x 20000    38.2 / 33.6      12 blocks x 65536   150 / 148
+//   8 blocks x 30000    59.3 / 56.4      16 blocks x 41432   146 / 140
+//   8 blocks x 65536    101 / 104        24 blocks x 30000   145 / 143
+// (Shorter rows, 16 x 14000 51.4 / 53.1 us at 1536 blocks, and 16 states gain at some lengths and lose at others.)
 long segments_wanted(const FwdParams& p, long nrb)
 {
     if (p.dstate > 8 || nrb > 32 || p.seqlen < 20000) return (2048 + nrb - 1) / nrb;
@@ -151,14 +152,17 @@ Shape pick_shape(const FwdParams& p)
 // nseg 0 where it is not taken.  Every block stages all of Bm and Cm for its 8 rows, so it
 // wins only while the chip is not full.  Measured on MI355X (us, fp32 with window 4 / bf16 with window 8, separate launches
 // or uncut rows -> one launch):
-//   64 rows, 256 tokens    20.8 / 20.7 -> 15.4 / 15.8    3072 rows, 401 tokens   23.4 / 25.0 -> 23.7 / 28.4
-//   3072 rows, 197 tokens  20.5 / 21.2 -> 16.6 / 16.7    6144 rows, 401 tokens   32.9 / 35.7 -> 37.0 / 41.4
-//   6144 rows, 197 tokens  23.4 / 24.6 -> 18.9 / 20.7    384 rows, 576 tokens    20.7 / 21.1 -> 23.8 / 25.8
-//   9216 rows, 197 tokens  27.7 / 29.3 -> 27.1 / 29.8    1536 rows, 576 tokens   21.9 / 21.7 -> 24.4 / 26.0
-//   12288 rows, 197 tokens 27.5 / 30.5 -> 33.9 / 36.9    64 rows, 50 tokens      15.7 / 15.7 -> 16.3 / 15.5
-//   1536 rows, 401 tokens  21.8 / 21.8 -> 17.9 / 20.6
-// Gathered rows pay more for the eightfold Bm and Cm (bf16, 145 tokens: 6144 rows 28.3 -> 23.9, 7680
-// rows 28.6 -> 33.3; 197 tokens, 7680 rows: 38.8 -> 33.2).
+//   64 rows, 256 tokens    16.2 / 16.3 -> 11.2 / 11.2    1920 rows, 401 tokens   17.7 / 18.1 -> 13.3 / 14.0
+//   3072 rows, 197 tokens  15.7 / 16.3 -> 11.1 / 11.2    2304 rows, 401 tokens   17.6 / 17.6 -> 19.7 / 20.0
+//   6144 rows, 197 tokens  20.0 / 20.1 -> 15.1 / 15.8    3072 rows, 401 tokens   20.7 / 20.7 -> 20.1 / 20.4
+//   8064 rows, 197 tokens  21.4 / 22.1 -> 18.7 / 19.8    6144 rows, 401 tokens   28.8 / 29.4 -> 30.1 / 30.5
+//   8448 rows, 197 tokens  21.6 / 22.3 -> 21.8 / 23.6    384 rows, 576 tokens    16.3 / 16.0 -> 17.2 / 17.9
+//   12288 rows, 197 tokens 22.0 / 22.9 -> 28.0 / 30.8    1536 rows, 576 tokens   17.7 / 17.4 -> 17.8 / 18.3
+//   9216 rows, 100 tokens  12.5 / 12.5 -> 15.9 / 16.0    64 rows, 50 tokens      11.1 / 11.4 -> 11.1 / 11.2
+// (On the wrong side: 2304 and 3072 rows of 290 tokens, 15.9 / 15.8 -> 13.9 / 14.1 and 16.8 / 17.1 -> 14.5 / 14.2.)
+// Gathered rows pay more for the eightfold Bm and Cm (fp32 / bf16, 145 tokens: 6144 rows 21.3 / 19.4 -> 15.4 / 15.3,
+// 7680 rows 22.9 / 19.0 -> 24.5 / 23.1; 197 tokens, 7680 rows: 30.6 / 26.0 -> 24.1 / 23.2, and 9216 rows, beyond the
+// line, 38.4 / 30.6 -> 28.8 / 28.0).
 Shape in_block_shape(const FwdParams& p)
 {
     const int ntiles = (p.seqlen + kFwdTileTokens - 1) / kFwdTileTokens;
@@ -174,14 +178,14 @@ Shape in_block_shape(const FwdParams& p)
 // cut: three rounds of 512 blocks, so that a block's end leaves little idle, but not more than 64
 // segments unless one round needs them (long chains, more summaries to read).  Backward call on
 // MI355X, us, at 512 / 1536 blocks:
-//   8 x 768 x 4096 bf16    641 / 604      4 x 768 x 2048 bf16    189 / 180
-//   16 x 768 x 2048 bf16   754 / 607      2 x 768 x 4096 bf16    190 / 183
-//   16 x 768 x 1024 fp32   374 / 317      8 x 768 x 1100 fp32    193 / 207
-//   4 x 768 x 4096 bf16    331 / 316      6 x 768 x 2048 fp32    255 / 253
-//   1 x 256 x 65536 fp32   403 / 440      1 x 512 x 16384 fp32   207 / 230
+//   8 x 768 x 4096 bf16    575 / 539      4 x 768 x 2048 bf16    167 / 157
+//   16 x 768 x 2048 bf16   671 / 551      2 x 768 x 4096 bf16    167 / 159
+//   16 x 768 x 1024 fp32   332 / 298      8 x 768 x 1100 fp32    183 / 192
+//   4 x 768 x 4096 bf16    297 / 287      6 x 768 x 2048 fp32    229 / 231
+//   1 x 256 x 65536 fp32   373 / 401      1 x 512 x 16384 fp32   192 / 207
 // (On the wrong side: rows that three rounds cut into segments of two or three tiles, as 8 x 768 x
-// 1100 above; 32 x 384 x 197 106 us in four segments, 98 in two; 4 x 768 x 1100 125 and 119.  The next
-// lengths go the other way, 8 x 768 x 1300 239 / 227.)
+// 1100 above; 32 x 384 x 197 95.8 us in four segments, 85.2 in two; 4 x 768 x 1100 107.5 and 102.2.  The next
+// lengths go the other way, 8 x 768 x 1300 215 / 213.)
 Shape pick_bwd_shape(const FwdParams& p)
 {
     const long nrb = (long)((p.dim + 63) / 64) * p.batch;
@@ -539,35 +543,37 @@ hipError_t launch_bwd(const FwdParams& f, BwdParams p, void* dBm, void* dCm, voi
 // of the rows the caches hold between tiles: rows of few bytes, grids of few rows or few
 // columns and small calls gather well.  Measured on MI355X (us, gather / copies):
 //   rows x tokens (grid)            forward fp32   forward bf16   backward fp32  backward bf16
-//   128 x 384, 50 (7 x 7)           26 / 42        29 / 42        107 / 115      109 / 111
-//   1042 x 384, 50 (7 x 7)          172 / 236      193 / 219      703 / 731      669 / 648
-//   88 x 384, 65 (8 x 8)            28 / 44        34 / 46        124 / 127      129 / 125
-//   127 x 384, 82 (9 x 9)           42 / 56        43 / 57        181 / 162      162 / 150
-//   103 x 384, 101 (10 x 10)        51 / 56        49 / 57        220 / 175      194 / 164
-//   72 x 384, 145 (12 x 12)         65 / 57        48 / 56        253 / 161      179 / 151
-//   90 x 384, 145 (12 x 12)         85 / 66        65 / 66        355 / 222      274 / 210
-//   29 x 384, 197 (14 x 14)         68 / 46        50 / 46        234 / 129      161 / 128
-//   106 x 384, 197 (14 x 14)        160 / 90       100 / 85       657 / 317      427 / 283
-//   132 x 384, 197 (14 x 14)        212 / 114      121 / 102      869 / 394      517 / 341
-//   128 x 768, 197 (14 x 14)        387 / 196      197 / 169      1506 / 653     897 / 561
-//   30 x 384, 257 (16 x 16)         74 / 56        58 / 57        309 / 145      214 / 141
-//   35 x 384, 257 (16 x 16)         81 / 59        60 / 60        399 / 167      268 / 158
-//   32 x 384, 325 (18 x 18)         122 / 65       79 / 72        433 / 176      260 / 164
-//   4 x 768, 1025 (32 x 32)         160 / 73       96 / 72        264 / 151      211 / 150
-//   1 x 768, 4096 (64 x 64)         104 / 84       104 / 85       239 / 168      229 / 172
-//   119 x 384, 197 (2 x 98)         91 / 102       99 / 92        354 / 335      357 / 291
-//   119 x 384, 197 (65 x 3)         121 / 100      99 / 92        395 / 336      349 / 293
-//   8 x 384, 1025 (4 x 256)         50 / 72        56 / 72        148 / 150      148 / 148
-//   30 x 384, 1025 (4 x 256)        241 / 176      190 / 166      634 / 456      617 / 423
-//   6 x 384, 1025 (8 x 128)         48 / 62        54 / 64        188 / 133      169 / 134
-//   8 x 384, 1025 (8 x 128)         57 / 72        60 / 72        175 / 149      165 / 147
-//   11 x 384, 1025 (8 x 128)        130 / 83       103 / 85       394 / 206      371 / 196
-//   3 x 384, 2049 (8 x 256)         57 / 68        55 / 70        212 / 148      191 / 150
-//   4 x 384, 2049 (8 x 256)         55 / 77        59 / 77        169 / 165      158 / 168
-//   8 x 768, 4096 (64 x 64)         1872 / 378     1913 / 416     4210 / 945     3798 / 931
-// (The lines stand where the kernels before the wave tiles put them.  On the wrong side are now,
-// forward: fp32 at 8 x 128 and 8 x 256 below 4 million elements (they copy) and at 72 x 384 x 145,
-// bf16 at 106 x 384 x 197 (they gather); backward: fp32 at 2 x 98, by 5%.)
+//   128 x 384, 50 (7 x 7)           21 / 39        21 / 39        92 / 110       88 / 105
+//   1042 x 384, 50 (7 x 7)          138 / 219      133 / 198      616 / 686      554 / 610
+//   88 x 384, 65 (8 x 8)            25 / 42        25 / 42        108 / 120      110 / 119
+//   127 x 384, 82 (9 x 9)           38 / 55        31 / 53        162 / 152      133 / 141
+//   103 x 384, 101 (10 x 10)        44 / 54        34 / 52        207 / 164      158 / 157
+//   72 x 384, 145 (12 x 12)         62 / 54        38 / 52        237 / 154      161 / 141
+//   90 x 384, 145 (12 x 12)         78 / 64        45 / 58        341 / 208      235 / 198
+//   29 x 384, 197 (14 x 14)         47 / 42        35 / 42        206 / 119      151 / 115
+//   106 x 384, 197 (14 x 14)        151 / 90       78 / 74        632 / 296      388 / 259
+//   132 x 384, 197 (14 x 14)        199 / 109      104 / 94       811 / 370      482 / 318
+//   128 x 768, 197 (14 x 14)        351 / 188      177 / 149      1408 / 604     833 / 525
+//   30 x 384, 257 (16 x 16)         70 / 53        44 / 51        302 / 146      190 / 128
+//   35 x 384, 257 (16 x 16)         80 / 56        45 / 53        370 / 157      234 / 145
+//   32 x 384, 325 (18 x 18)         118 / 60       60 / 64        417 / 167      231 / 151
+//   4 x 768, 1025 (32 x 32)         130 / 67       89 / 66        259 / 140      185 / 132
+//   1 x 768, 4096 (64 x 64)         100 / 78       99 / 78        223 / 152      209 / 151
+//   119 x 384, 197 (2 x 98)         90 / 97        72 / 86        334 / 312      302 / 274
+//   119 x 384, 197 (65 x 3)         117 / 98       75 / 86        388 / 311      296 / 275
+//   8 x 384, 1025 (4 x 256)         44 / 67        41 / 66        136 / 139      116 / 132
+//   30 x 384, 1025 (4 x 256)        220 / 165      167 / 156      624 / 415      553 / 388
+//   6 x 384, 1025 (8 x 128)         44 / 58        41 / 59        182 / 121      153 / 119
+//   8 x 384, 1025 (8 x 128)         52 / 67        47 / 66        170 / 139      140 / 132
+//   11 x 384, 1025 (8 x 128)        87 / 78        70 / 76        356 / 189      336 / 179
+//   3 x 384, 2049 (8 x 256)         44 / 63        42 / 64        198 / 131      177 / 132
+//   4 x 384, 2049 (8 x 256)         50 / 71        46 / 70        159 / 151      129 / 150
+//   8 x 768, 4096 (64 x 64)         1850 / 347     1883 / 375     4507 / 870     4075 / 839
+// (The lines stand where the kernels before the wave tiles put them, and callers size their scratch
+// by them.  On the wrong side are now, forward, where calls copy: fp32 at 8 x 128 and 8 x 256 below 4 million
+// elements, bf16 at 35 x 384 x 257, 32 x 384 x 325 and 11 x 384 x 1025; where they gather: fp32 at
+// 72 x 384 x 145, bf16 at 106 x 384 x 197.  Backward, where they copy: bf16 at 65 and 82 tokens, by 6 and 8%, and
+// at 4 x 256 and 4 x 384 x 2049, by 14 and 16%; where they gather: fp32 at 2 x 98, by 7%.)
 // The copies ask for an fp32 result, which the chunk-per-lane kernel gives for bf16 only
 // with window 1: bf16 images of 4096 tokens run the wave-tile kernels here.
 namespace {
